@@ -346,8 +346,7 @@ int queue_cap(long long cap, int nent) {
 size_t queue_bytes(int cap, int nent) {
     const size_t per = 256;
     const size_t words = 2 * QNCOL + 2 + 3 + 4 + 8 * (size_t)std::max(nent, 1);
-    return (size_t)cap * 4 * words + (size_t)cap * std::max(nent, 1) + (words + 10) * per + 64 * 4 +
-           FETCH_INTS * sizeof(int);
+    return (size_t)cap * 4 * words + (size_t)cap * std::max(nent, 1) + (words + 10) * per + 64 * 4;
 }
 
 constexpr size_t SPILL_BYTES = (size_t)SPILL_STACK * TRACE_GRID * TRACE_BLOCK * sizeof(uint32_t);
@@ -380,7 +379,6 @@ void carve_queues(char* base, int cap, int nent, float* L, uint32_t* spill, Queu
     q.socc = c.take<uint8_t>((size_t)cap * std::max(nent, 1));
     q.slist = c.take<uint32_t>((size_t)cap * std::max(nent, 1));
     q.cnt = c.take<int>(64);
-    q.fetch = c.take<int>(FETCH_INTS);
     q.spill = spill;
     q.L = L;
     q.cap = cap;
@@ -435,6 +433,8 @@ int render_impl(st_scene* owner, st_scene* const* scenes, int nscenes, const st_
     p.dbg_hash = o.debug_decision_hash;
     p.err = owner->d.err;
     p.work = (o.flags & ST_COUNT_WORK) ? owner->d.work : nullptr;
+    p.fast = p.work ? 0 : 1;
+    for (int i = 0; i < nscenes; ++i) p.fast &= scenes[i]->d.nf <= TRAV_FAST_FACES ? 1 : 0;
     p.hash_by_q = nullptr;
     p.rec_face = nullptr;
     p.rec_occ = nullptr;
@@ -647,7 +647,8 @@ int st_scene_create(const float* V, int32_t nv, const int32_t* F, int32_t nf, co
     A(dalloc(&d.tleaves, (size_t)nf));
     A(dalloc(&d.nodes4, 8 * (size_t)std::max(nf - 1, 1)));
     A(dalloc(&d.flag4, (size_t)std::max(nf - 1, 1)));
-    A(dalloc(&d.id4, (size_t)std::max(nf - 1, 1)));
+    A(dalloc(&d.slots4, (size_t)std::max(nf - 1, 1)));
+    A(dalloc(&d.tiles4, (size_t)(nf + PACK_TILE - 1) / PACK_TILE));
     A(dalloc(&d.ccost, (size_t)std::max(nf - 1, 1)));
     A(dalloc(&d.cdec, (size_t)std::max(nf - 1, 1)));
     A(dalloc(&d.tri, 3 * (size_t)nf));
@@ -1022,6 +1023,7 @@ int st_render_noalloc(st_scene* sc, const st_camera* cams, int32_t ncam, int32_t
     p.dbg_hash = o.debug_decision_hash;
     p.err = sc->d.err;
     p.work = (o.flags & ST_COUNT_WORK) ? sc->d.work : nullptr;
+    p.fast = !p.work && sc->d.nf <= TRAV_FAST_FACES ? 1 : 0;
     p.hash_by_q = nullptr;
     p.rec_face = nullptr;        // no hit records: the scene's record buffer is not touched
     p.rec_occ = nullptr;
@@ -1130,6 +1132,7 @@ int st_render_backward(st_scene* sc, const st_camera* cams, int32_t ncam, int32_
     p.dbg_edge_hash = o.debug_edge_hash;
     p.err = sc->d.err;
     p.work = (o.flags & ST_COUNT_WORK) ? sc->d.work : nullptr;
+    p.fast = !p.work && sc->d.nf <= TRAV_FAST_FACES ? 1 : 0;
     p.spill = (uint32_t*)sc->spillbuf.p;
     p.pw = c.take<double>((size_t)ncam * ne);
     p.pcdf = c.take<double>((size_t)ncam * (ne + 1));
@@ -1249,6 +1252,7 @@ int st_render_backward(st_scene* sc, const st_camera* cams, int32_t ncam, int32_
         fp.dbg_hash = nullptr;
         fp.err = sc->d.err;
         fp.work = p.work;
+        fp.fast = p.fast;
         fp.hash_by_q = hside;
         fp.rec_face = nullptr;
         fp.rec_occ = nullptr;
@@ -1438,7 +1442,7 @@ int st_trace_rays(st_scene* sc, const float* o, const float* d, int32_t n, float
     if (n > 0 && (!o || !d || !of || !ot)) return fail(ST_ERR_INVALID_ARG, "NULL array");
     rc = ensure_spill(sc);
     if (rc) return rc;
-    launch_trace_debug(sc->d.dscene, o, d, n, tmin, brute, of, ot, (uint32_t*)sc->spillbuf.p, sc->d.err, s);
+    launch_trace_debug(sc->d.dscene, sc->d.nf, o, d, n, tmin, brute, of, ot, (uint32_t*)sc->spillbuf.p, sc->d.err, s);
     HIPCHK(hipGetLastError());
     return ST_OK;
 }
@@ -1449,7 +1453,7 @@ void st_scene_destroy(st_scene* sc) {
     SceneDev& d = sc->d;
     void* ptrs[] = {d.V, d.F, d.mat, d.lights, d.env, d.fnorm, d.bmin, d.bmax, d.cen, d.bounds, d.mkeys[0], d.mkeys[1],
                     d.mvals[0], d.mvals[1], d.rs_hist, d.keys64, d.child, d.parent, d.aabb, d.refit_cnt, d.tcost, d.tleaves, d.ebmin, d.ebmax, d.ecen, d.ebounds, d.emkeys[0], d.emkeys[1],
-                    d.emvals[0], d.emvals[1], d.ers_hist, d.ekeys64, d.echild, d.eparent, d.ecnt, d.eaabb, d.elen, d.enbox, d.enode, d.nodes4, d.flag4, d.id4, d.ccost, d.cdec,
+                    d.emvals[0], d.emvals[1], d.ers_hist, d.ekeys64, d.echild, d.eparent, d.ecnt, d.eaabb, d.elen, d.enbox, d.enode, d.nodes4, d.flag4, d.slots4, d.tiles4, d.ccost, d.cdec,
                     d.tri, d.fleaf, d.edges, d.edge_w, d.eguide, d.mguide, d.cguide, d.ecdf, d.etotal_d, d.etotal_f, d.row_dom, d.rowcos, d.cond, d.marg,
                     d.env_rows, d.env_total, d.texpdf, d.err, d.work, d.dscene, d.vf_off, d.vf_idx, d.facc, d.macc, d.fe,
                     d.ealias, d.rec_key};

@@ -182,7 +182,8 @@ __device__ __forceinline__ void face_reduce_add(bool has, int f, int tx, const f
 // secondary-edge hierarchy's descent, RECM = 2 with it); it does nothing when
 // the records turn out stale on the device, and the RECM = 0 pass launched after
 // it then traces (that pass returns at once when the records pass ran).
-template <int BM, bool JOBS, int RECM = 0>
+// FAST: the traversal variant (st_device.h), for the passes that trace.
+template <int BM, bool JOBS, int RECM = 0, bool FAST = false>
 __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(ST_ADJ_WAVES)))
 k_adjoint(BwdParams p, long long total) {
     constexpr bool REC = RECM > 0;
@@ -190,6 +191,7 @@ k_adjoint(BwdParams p, long long total) {
     __shared__ float red_s[TRACE_BLOCK / 64][64 * FACC];
     float* const red = red_s[threadIdx.x >> 6];
     TravStack st = make_trav_stack(lds, p.spill, p.err, p.work ? p.work + 3 * WORK_ADJOINT : nullptr);
+    const TraceGeo G = trace_geo(p.scenes[0]);     // a backward has one scene
     const RecMem rm{p.vrec, (size_t)gridDim.x * blockDim.x, (size_t)blockIdx.x * blockDim.x + threadIdx.x};
     const bool want_interior = !JOBS && (p.flags & 1u), want_secondary = p.flags & 4u;
     const bool sec_interior = p.flags & ST_EDGE_SECONDARY_INTERIOR;   // creases / material edges too
@@ -257,7 +259,7 @@ k_adjoint(BwdParams p, long long total) {
                     f = qld(rec_face + ri);
                     t = f >= 0 ? face_hit_t(S, f, o, d) : __int_as_float(0x7f800000);
                 } else {
-                    f = trace_closest(S, o, d, TMIN, excl, t, st);
+                    f = trace_closest<FAST>(G, o, d, TMIN, excl, t, st);
                 }
                 push_face(h, f);
                 if (f < 0) {
@@ -290,7 +292,7 @@ k_adjoint(BwdParams p, long long total) {
                         const V3 wl = dl * (1.0f / rr);
                         if (dot(n, wl) > 0.0f) {
                             const bool occ = (REC || rec_occ) ? ((rocc >> l) & 1u) != 0u
-                                                       : trace_any(S, xh, wl, TMIN, rr * (1.0f - SHADOW_SHRINK), f, st);
+                                                       : trace_any<FAST>(G, xh, wl, TMIN, rr * (1.0f - SHADOW_SHRINK), f, st);
                             code = occ ? 1u : 2u;
                             if (!occ) fl |= 1u << (8 + l);
                         }
@@ -306,7 +308,7 @@ k_adjoint(BwdParams p, long long total) {
                     uint32_t code = 0;
                     if (ce > 0.0f && pe > 0.0f) {
                         const bool occ = (REC || rec_occ) ? ((rocc >> S.nl) & 1u) != 0u
-                                                   : trace_any(S, xh, we, TMIN, __int_as_float(0x7f800000), f, st);
+                                                   : trace_any<FAST>(G, xh, we, TMIN, __int_as_float(0x7f800000), f, st);
                         code = occ ? 1u : 2u;
                         if (!occ) {
                             fl |= R_ENV;
@@ -403,7 +405,7 @@ k_adjoint(BwdParams p, long long total) {
                 V3 Ls[2];
                 for (int side = 0; side < 2; ++side) {
                     const V3 dir = normalize(ud + mm * (side == 0 ? -EPS_SECONDARY : EPS_SECONDARY));
-                    Ls[side] = trace_estimator(S, xh, dir, f, p.B - (k + 1), true, sc, key, h, st);
+                    Ls[side] = trace_estimator<FAST>(S, G, xh, dir, f, p.B - (k + 1), true, sc, key, h, st);
                 }
                 const V3 dirk = k == 0 ? d0 : sel(rwi, k - 1);
                 const Mat m = load_mat(S.mat + 7 * (size_t)texel_of(S, f, xh));
@@ -927,6 +929,7 @@ __device__ __forceinline__ void project_jac(const DevCam& c, const double z[3], 
     }
 }
 
+template <bool FAST>
 __device__ void shadow_edge_one(const BwdParams& p, const DevScene& S, const DevCam& c, int v, int l, long long si,
                                 long long nsv, Hash& h, TravStack& st) {
 #pragma clang fp contract(off)
@@ -944,13 +947,14 @@ __device__ void shadow_edge_one(const BwdParams& p, const DevScene& S, const Dev
     const V3 y = va + (vb - va) * t;
     const V3 w = normalize(y - pl);
     float tr;
-    const int fr = trace_closest(S, y, w, TMIN, E.z, tr, st);
+    const TraceGeo G = trace_geo(S);
+    const int fr = trace_closest<FAST>(G, y, w, TMIN, E.z, tr, st);
     h.push(fr < 0 ? 0xFFFFFFFFu : (uint32_t)fr);
     if (fr < 0 || fr == E.w) return;
     const V3 zt = y + w * tr;
     const V3 eye = ld3(c.eye);
     float tc;
-    const int fc = trace_closest(S, eye, normalize(zt - eye), TMIN, -1, tc, st);
+    const int fc = trace_closest<FAST>(G, eye, normalize(zt - eye), TMIN, -1, tc, st);
     const bool vis = fc == fr;
     h.push(vis ? 2u : 1u);
     if (!vis) return;
@@ -999,7 +1003,7 @@ __device__ void shadow_edge_one(const BwdParams& p, const DevScene& S, const Dev
         const double r = sqrt(wl[0] * wl[0] + wl[1] * wl[1] + wl[2] * wl[2]);
         const V3 zf{(float)zs[0], (float)zs[1], (float)zs[2]};
         const V3 wf{(float)(wl[0] / r), (float)(wl[1] / r), (float)(wl[2] / r)};
-        vsd[side] = trace_any(S, zf, wf, TMIN, (float)(r * (1.0 - (double)SHADOW_SHRINK)), fr, st) ? 0 : 1;
+        vsd[side] = trace_any<FAST>(G, zf, wf, TMIN, (float)(r * (1.0 - (double)SHADOW_SHRINK)), fr, st) ? 0 : 1;
         h.push((uint32_t)vsd[side]);
     }
     if (vsd[0] == vsd[1]) return;
@@ -1048,6 +1052,7 @@ __device__ void shadow_edge_one(const BwdParams& p, const DevScene& S, const Dev
 
 // one thread per shadow-edge sample; sample gs of (view v, light l, index i) is
 // nl eoff[v] + l N_e(v) + i, and its hash / mask slot follows the primary edge samples
+template <bool FAST>
 __global__ void __launch_bounds__(TRACE_BLOCK) k_shadow_edges(BwdParams p, long long total_edges, long long nsh) {
     __shared__ uint32_t lds[LDS_STACK * TRACE_BLOCK];
     TravStack st = make_trav_stack(lds, p.spill, p.err, nullptr);
@@ -1067,7 +1072,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) k_shadow_edges(BwdParams p, long 
         const long long si = rem - (long long)l * nsv;
         if (p.edge_mask && !p.edge_mask[total_edges + gs]) continue;
         Hash h{FNV_INIT, p.dbg_edge_hash != nullptr};
-        shadow_edge_one(p, S, c, lo, l, si, nsv, h, st);
+        shadow_edge_one<FAST>(p, S, c, lo, l, si, nsv, h, st);
         if (p.dbg_edge_hash) p.dbg_edge_hash[total_edges + gs] = h.h;
     }
 }
@@ -1090,7 +1095,6 @@ void launch_primary_edges(const BwdParams& p, const FwdParams& fp, Queues& q, fl
     for (long long e0 = 0; e0 < total_edges; e0 += per) {
         const int n = (int)((total_edges - e0) < per ? (total_edges - e0) : per);
         launch_fill_u32((uint32_t*)q.cnt, 64, 0u, st);
-        launch_fill_u32((uint32_t*)q.fetch, FETCH_INTS, 0u, st);
         ST_LAUNCH("k_edge_camera", k_edge_camera, dim3(gridb(n, EDGE_CAM_BLOCK, 1 << 20)), dim3(EDGE_CAM_BLOCK), 0, st,
                   p, q, e0, n);
         if (hook) hook->tick();
@@ -1193,12 +1197,14 @@ static void launch_adjoint(const BwdParams& p, long long total_paths, int grid, 
     else if (p.rec_split)
         ST_LAUNCH(name, (k_adjoint<BM, false, 1>), gd, bd, 0, st, p, total_paths);
     // (returns at once when the records pass above found its records valid)
-    ST_LAUNCH(name, (k_adjoint<BM, false>), gd, bd, 0, st, p, total_paths);
+    const auto tracing = p.fast ? k_adjoint<BM, false, 0, true> : k_adjoint<BM, false, 0, false>;
+    ST_LAUNCH(name, tracing, gd, bd, 0, st, p, total_paths);
     if (p.sec_mask) {
         ST_LAUNCH("k_sec_jobs", k_sec_jobs, dim3(gridb(total_paths, 256 * SEC_JOBS_PER, 1 << 12)), dim3(256), 0, st, p.sec_mask,
                   total_paths, p.B, p.sec_jobs, p.sec_njobs, p.err);
         // the job count stays on the device: a fixed grid strides over it
-        ST_LAUNCH(name_jobs, (k_adjoint<BM, true>), dim3(1024), bd, 0, st, p, 0ll);
+        const auto jobs = p.fast ? k_adjoint<BM, true, 0, true> : k_adjoint<BM, true, 0, false>;
+        ST_LAUNCH(name_jobs, jobs, dim3(1024), bd, 0, st, p, 0ll);
     }
 }
 
@@ -1250,7 +1256,8 @@ void launch_shadow_edges(const BwdParams& p, long long total_edges, int nl, hipS
     ST_LAUNCH("k_light_cdf", k_light_cdf, dim3(nl), dim3(1024), 0, st, p);
     launch_guide(p.lcdf, p.ne, (size_t)(p.ne + 1), nl, p.lguide, p.pglog, st);
     const long long nsh = total_edges * nl;
-    ST_LAUNCH("k_shadow_edges", k_shadow_edges, dim3(gridb(nsh, TRACE_BLOCK, TRACE_GRID)), dim3(TRACE_BLOCK), 0, st, p,
+    const auto edges = p.fast ? k_shadow_edges<true> : k_shadow_edges<false>;
+    ST_LAUNCH("k_shadow_edges", edges, dim3(gridb(nsh, TRACE_BLOCK, TRACE_GRID)), dim3(TRACE_BLOCK), 0, st, p,
               total_edges, nsh);
 }
 

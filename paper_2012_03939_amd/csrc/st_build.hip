@@ -214,6 +214,18 @@ __global__ void k_karras(const uint32_t* __restrict__ m, const uint32_t* __restr
     if (i == 0) parent[0] = -1;
 }
 
+// triangle record i of face f
+__device__ __forceinline__ void put_tri(const float* __restrict__ V, const int* __restrict__ F, int f, uint32_t i,
+                                        float4* tri, int* fleaf) {
+    const V3 a = ld3(V + 3 * F[3 * f]), b = ld3(V + 3 * F[3 * f + 1]), c = ld3(V + 3 * F[3 * f + 2]);
+    const V3 e1 = b - a, e2 = c - a;
+    float4* const o = tri + 3 * (size_t)i;
+    o[0] = make_float4(a.x, a.y, a.z, __int_as_float(f));
+    o[1] = make_float4(e1.x, e1.y, e1.z, 0.f);
+    o[2] = make_float4(e2.x, e2.y, e2.z, 0.f);
+    fleaf[f] = (int)i;
+}
+
 __global__ void k_leaf_init(const uint32_t* __restrict__ sface, const float4* __restrict__ bmin,
                             const float4* __restrict__ bmax, const float* __restrict__ V, const int* __restrict__ F,
                             int n, float* aabb, float4* tri, int* fleaf, int* cnt) {
@@ -221,15 +233,10 @@ __global__ void k_leaf_init(const uint32_t* __restrict__ sface, const float4* __
     if (i < n - 1) cnt[i] = 0;
     if (i >= n) return;
     const int f = (int)sface[i];
-    fleaf[f] = i;
     float* b = aabb + 6 * ((size_t)(n - 1) + i);
     const float4 mn = bmin[f], mx = bmax[f];
     b[0] = mn.x; b[1] = mn.y; b[2] = mn.z; b[3] = mx.x; b[4] = mx.y; b[5] = mx.z;
-    const V3 a = ld3(V + 3 * F[3 * f]), bb = ld3(V + 3 * F[3 * f + 1]), c = ld3(V + 3 * F[3 * f + 2]);
-    const V3 e1 = bb - a, e2 = c - a;
-    tri[3 * i] = make_float4(a.x, a.y, a.z, __int_as_float(f));
-    tri[3 * i + 1] = make_float4(e1.x, e1.y, e1.z, 0.f);
-    tri[3 * i + 2] = make_float4(e2.x, e2.y, e2.z, 0.f);
+    if (n == 1) put_tri(V, F, f, 0, tri, fleaf);     // otherwise k_pack4 orders them by node
 }
 
 __device__ __forceinline__ float aload(const float* p) {
@@ -635,49 +642,132 @@ __global__ void k_collapse_flag(const int* __restrict__ parent, const int* __res
     flag[i] = k == 1 ? 1 : 0;
 }
 
-// 4-wide node of a binary node x that heads one: its children, every internal
-// one that does not head a node replaced by its own two children until only
-// leaves and heads remain (at most 4 by the costs above), in tree order (8
-// float4: min x, max x, min y, max y, min z, max z of the 4 slots, child codes,
-// pad)
-__global__ void k_pack4(const int* __restrict__ child, const float* __restrict__ aabb, const int* __restrict__ flag,
-                        const uint32_t* __restrict__ id4, int n, float4* nodes4, uint32_t* err) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n - 1 || !flag[i]) return;
-    int sl[4] = {child[2 * i], child[2 * i + 1], 0, 0};
+// The slots of the 4-wide node of a binary node x that heads one: its children,
+// every internal one that does not head a node replaced by its own two children
+// until only leaves and heads remain (at most 4 by the costs above), the internal
+// ones first, each kind in tree order; but a leaf that tree order puts before the
+// second of three internal ones comes first (lead), so that the traversal's order
+// of equally near children stays that of the children in tree order.  Returns
+// their number, ni of them internal.
+__device__ __forceinline__ int node4_slots(const int* __restrict__ child, const int* __restrict__ flag, int x, int sl[4],
+                                           int& ni, bool& lead, uint32_t* err) {
+    int t[4] = {child[2 * x], child[2 * x + 1], 0, 0};
     int m = 2;
     for (int pass = 0; pass < 3; ++pass) {
         int at = -1;
         for (int s = 0; s < m; ++s)
-            if (at < 0 && !(sl[s] & (int)LEAF_BIT) && !flag[sl[s]]) at = s;
+            if (at < 0 && !(t[s] & (int)LEAF_BIT) && !flag[t[s]]) at = s;
         if (at < 0) break;
         if (m == 4) { atomicOr(err, ERR_LOOP); break; }   // cannot happen: the costs allow at most 4 slots
-        const int x = sl[at];
-        for (int s = m; s > at + 1; --s) sl[s] = sl[s - 1];
-        sl[at] = child[2 * x];
-        sl[at + 1] = child[2 * x + 1];
+        const int y = t[at];
+        for (int s = m; s > at + 1; --s) t[s] = t[s - 1];
+        t[at] = child[2 * y];
+        t[at + 1] = child[2 * y + 1];
         ++m;
     }
+    ni = 0;
+    for (int s = 0; s < m; ++s) ni += t[s] & (int)LEAF_BIT ? 0 : 1;
+    lead = m == 4 && ni == 3 && ((t[0] | t[1]) & (int)LEAF_BIT);
+    int in = lead ? 1 : 0, lf = lead ? 0 : ni;
+    for (int s = 0; s < m; ++s) sl[t[s] & (int)LEAF_BIT ? lf++ : in++] = t[s];
+    return m;
+}
+
+// Where the children of every 4-wide node start: the exclusive sums, over the
+// binary nodes in index order, of the internal slots (nodes, after the root) and
+// of the leaf slots (triangle records) of those that head one.  Tiles of
+// PACK_TILE nodes: k_pack_count leaves each node's sum inside its tile and the
+// tile's totals, k_pack_scan adds the tiles before.
+__device__ __forceinline__ uint2 block_scan_pair(uint2 v, uint2& total, uint2* lds) {
+    // exclusive over the block, in thread order; lds holds PACK_TILE / 64 + 1
+    uint2 inc = v;
+    const int lane = (int)__lane_id(), w = (int)(threadIdx.x >> 6);
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t x = __shfl_up(inc.x, o, 64), y = __shfl_up(inc.y, o, 64);
+        if (lane >= o) { inc.x += x; inc.y += y; }
+    }
+    if (lane == 63) lds[w] = inc;
+    __syncthreads();
+    uint2 before = make_uint2(0u, 0u), all = make_uint2(0u, 0u);
+    for (int j = 0; j < PACK_TILE / 64; ++j) {
+        const uint2 x = lds[j];
+        if (j < w) { before.x += x.x; before.y += x.y; }
+        all.x += x.x; all.y += x.y;
+    }
+    __syncthreads();
+    total = all;
+    return make_uint2(before.x + inc.x - v.x, before.y + inc.y - v.y);
+}
+
+__global__ void __launch_bounds__(PACK_TILE) k_pack_count(const int* __restrict__ child, const int* __restrict__ flag, int n,
+                                                          uint2* slots, uint2* tiles, uint32_t* err) {
+    __shared__ uint2 lds[PACK_TILE / 64];
+    const int i = blockIdx.x * PACK_TILE + threadIdx.x;
+    uint2 v = make_uint2(0u, 0u);
+    if (i < n - 1 && flag[i]) {
+        int sl[4], ni;
+        bool lead;
+        const int m = node4_slots(child, flag, i, sl, ni, lead, err);
+        v = make_uint2((uint32_t)ni, (uint32_t)(m - ni));
+    }
+    uint2 tot;
+    const uint2 e = block_scan_pair(v, tot, lds);
+    if (i < n - 1) slots[i] = e;
+    if (threadIdx.x == 0) tiles[blockIdx.x] = tot;
+}
+
+__global__ void __launch_bounds__(PACK_TILE) k_pack_scan(int n, uint2* slots, const uint2* __restrict__ tiles) {
+    __shared__ uint2 lds[PACK_TILE / 64];
+    uint2 v = make_uint2(0u, 0u), before;
+    for (unsigned t = threadIdx.x; t < blockIdx.x; t += PACK_TILE) { v.x += tiles[t].x; v.y += tiles[t].y; }
+    block_scan_pair(v, before, lds);
+    const int i = blockIdx.x * PACK_TILE + threadIdx.x;
+    if (i < n - 1) { slots[i].x += before.x + 1u; slots[i].y += before.y; }     // node 0 is the root
+}
+
+// 4-wide node of a binary node that heads one (8 float4: min x, max x, min y,
+// max y, min z, max z of the 4 slots; byte offsets of slot 0's node and triangle
+// record, internal slots (-1: slots 1..3, after a leaf); the same as indices) and
+// the records of its triangles.  Slot 0's node or triangle is as if the kind's
+// slots began there.  Its own place follows from its parent's.
+__global__ void k_pack4(const int* __restrict__ child, const int* __restrict__ parent, const float* __restrict__ aabb,
+                        const int* __restrict__ flag, const uint2* __restrict__ slots, const uint32_t* __restrict__ sface,
+                        const float* __restrict__ V, const int* __restrict__ F, int n, float4* nodes4, float4* tri,
+                        int* fleaf, uint32_t* err) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n - 1 || !flag[i]) return;
+    int sl[4], ni;
+    bool lead;
+    uint32_t id = 0;
+    if (parent[i] >= 0) {
+        int h = parent[i];
+        while (!flag[h]) h = parent[h];
+        node4_slots(child, flag, h, sl, ni, lead, err);
+        id = slots[h].x;
+        for (int s = lead ? 1 : 0; s < 3 && sl[s] != i; ++s) ++id;
+    }
+    const int m = node4_slots(child, flag, i, sl, ni, lead, err);
+    const uint32_t first = slots[i].x - (lead ? 1u : 0u), tri0 = slots[i].y - (lead ? 0u : (uint32_t)ni);
+    const int inner = lead ? -1 : ni;
     float v[6][4];
-    int cc[4];
     for (int s = 0; s < 4; ++s) {
         if (s < m) {
             const int c = sl[s];
-            const size_t bi = (c & (int)LEAF_BIT) ? (size_t)(n - 1) + (c & 0x7FFFFFFF) : (size_t)c;
-            const float* bb = aabb + 6 * bi;
+            const bool is_leaf = c & (int)LEAF_BIT;
+            const float* bb = aabb + 6 * (is_leaf ? (size_t)(n - 1) + (c & 0x7FFFFFFF) : (size_t)c);
             v[0][s] = bb[0]; v[1][s] = bb[3]; v[2][s] = bb[1]; v[3][s] = bb[4]; v[4][s] = bb[2]; v[5][s] = bb[5];
-            cc[s] = (c & (int)LEAF_BIT) ? c : (int)id4[c];
+            if (is_leaf) put_tri(V, F, (int)sface[c & 0x7FFFFFFF], tri0 + (uint32_t)s, tri, fleaf);
         } else {
-            // an empty slot is a box at +infinity on every axis: its slab test
-            // gives an entry distance of +inf or an empty interval, a miss either way
-            v[0][s] = v[1][s] = v[2][s] = v[3][s] = v[4][s] = v[5][s] = __int_as_float(0x7f800000);
-            cc[s] = -1;
+            // an empty slot is an inverted box, min +inf and max -inf on every axis:
+            // its near planes are at +inf and its far planes at -inf for any ray
+            v[0][s] = v[2][s] = v[4][s] = __int_as_float(0x7f800000);
+            v[1][s] = v[3][s] = v[5][s] = -__int_as_float(0x7f800000);
         }
     }
-    float4* o = nodes4 + 8 * (size_t)id4[i];
+    float4* o = nodes4 + 8 * (size_t)id;
     for (int k = 0; k < 6; ++k) o[k] = make_float4(v[k][0], v[k][1], v[k][2], v[k][3]);
-    o[6] = make_float4(__int_as_float(cc[0]), __int_as_float(cc[1]), __int_as_float(cc[2]), __int_as_float(cc[3]));
-    o[7] = make_float4(0.f, 0.f, 0.f, 0.f);
+    o[6] = make_float4(__uint_as_float(first * NODE_BYTES), __uint_as_float(tri0 * TRI_BYTES), __int_as_float(inner), 0.f);
+    o[7] = make_float4(__uint_as_float(first), __uint_as_float(tri0), __int_as_float(inner), 0.f);
 }
 
 __global__ void k_keys64(const uint32_t* __restrict__ m, const uint32_t* __restrict__ fa, int n, uint64_t* out) {
@@ -1004,10 +1094,12 @@ void launch_scene_geometry(SceneDev& s, hipStream_t st) {
                   nf, s.refit_cnt, (float*)s.ccost, s.cdec);
         ST_LAUNCH("k_collapse_flag", k_collapse_flag, dim3(nb(nf - 1, 256)), dim3(256), 0, st, s.parent, s.child,
                   s.cdec, nf, s.flag4, s.err);
-        hipMemcpyAsync(s.id4, s.flag4, sizeof(int) * (nf - 1), hipMemcpyDeviceToDevice, st);
-        ST_LAUNCH("k_rs_scan", k_rs_scan, dim3(1), dim3(1024), 0, st, s.id4, nf - 1);
-        ST_LAUNCH("k_pack4", k_pack4, dim3(nb(nf - 1, 256)), dim3(256), 0, st, s.child, s.aabb, s.flag4, s.id4, nf,
-                  s.nodes4, s.err);
+        const unsigned tiles = nb(nf - 1, PACK_TILE);
+        ST_LAUNCH("k_pack_count", k_pack_count, dim3(tiles), dim3(PACK_TILE), 0, st, s.child, s.flag4, nf, s.slots4,
+                  s.tiles4, s.err);
+        ST_LAUNCH("k_pack_scan", k_pack_scan, dim3(tiles), dim3(PACK_TILE), 0, st, nf, s.slots4, s.tiles4);
+        ST_LAUNCH("k_pack4", k_pack4, dim3(nb(nf - 1, 256)), dim3(256), 0, st, s.child, s.parent, s.aabb, s.flag4,
+                  s.slots4, sf, s.V, s.F, nf, s.nodes4, s.tri, s.fleaf, s.err);
     }
     if (s.ne > 0) {
         ST_LAUNCH("k_edge_len", k_edge_len, dim3(nb(s.ne, 256)), dim3(256), 0, st, s.edges, s.ne, s.V, s.edge_w);

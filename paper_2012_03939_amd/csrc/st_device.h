@@ -122,9 +122,9 @@ struct DevScene {
     const float* mat;     // [nf,7]
     const float* lights;  // [nl,6]
     const float4* fnorm;  // [nf] unit geometric normal
-    const float4* tri;    // [nf*3] leaf-ordered (v0, face bits) (e1) (e2)
-    const int* fleaf;     // [nf] leaf index of each face
-    const float4* nodes4; // 4-wide nodes, 8 float4 each: SoA child boxes + child codes
+    const float4* tri;    // [nf*3] node-ordered (v0, face bits) (e1) (e2)
+    const int* fleaf;     // [nf] record of each face in tri
+    const float4* nodes4; // 4-wide nodes, 8 float4 each: SoA child boxes + where the children start
     const float* env;     // [he,we,3]
     const double* marg;   // [he+1]
     const double* cond;   // [he,we+1]
@@ -176,6 +176,11 @@ struct TravStack {
         if (i < LDS_STACK) return lds[i * TRAV_BLOCK];
         return spill[(i - LDS_STACK) * gstride + gid];
     }
+    __device__ __forceinline__ bool push1(int& sp, uint32_t v) {
+        if (sp >= LDS_STACK + SPILL_STACK) return false;
+        put(sp++, v);
+        return true;
+    }
     // pushes m (0..3) entries: a, then b, then c; entries beyond the m-th are
     // written too when they stay in LDS (above the new top, so never read)
     __device__ __forceinline__ bool push3(int& sp, int m, uint32_t a, uint32_t b, uint32_t c) {
@@ -209,35 +214,78 @@ __device__ __forceinline__ TravStack make_trav_stack(uint32_t* lds, uint32_t* sp
     return s;
 }
 
-// the geometry one traversal reads, held in registers for the whole traversal
+// The geometry one traversal reads.  The pointers are wave-uniform (scalar
+// registers): a node or triangle load is then one base plus a 32-bit lane offset.
+typedef __attribute__((address_space(1))) const char gchar;
 struct TraceGeo {
-    const gfloat4* nodes4;
-    const gfloat4* tri;
+    const gchar* nodes;
+    const gchar* tri;
     int nf;
 };
+__device__ __forceinline__ const gchar* uniform_ptr(const void* p) {
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+    return (const gchar*)(((uint64_t)hi << 32) | lo);
+}
+// of a scene that is the same for every active lane
 __device__ __forceinline__ TraceGeo trace_geo(const DevScene& S) {
-    return TraceGeo{(const gfloat4*)S.nodes4, (const gfloat4*)S.tri, S.nf};
+    return TraceGeo{uniform_ptr(S.nodes4), uniform_ptr(S.tri), __builtin_amdgcn_readfirstlane(S.nf)};
+}
+// fn(scene) once per distinct scene among the active lanes, with the lanes of
+// that scene (views of several scenes meet in one wave only at their borders).
+// The loop leaves by a ballot: by a lane's own condition the compiler may move
+// fn behind the loop, where lanes of different scenes run it together.
+template <class Fn>
+__device__ __forceinline__ void for_scene(const DevScene* scenes, int sc, Fn fn) {
+    bool todo = true;
+    for (;;) {
+        const uint64_t m = __ballot(todo);
+        if (!m) break;
+        const int u = __builtin_amdgcn_readlane(sc, __ffsll((long long)m) - 1);
+        if (todo && sc == u) {
+            fn(scenes[u]);
+            todo = false;
+        }
+    }
 }
 
-// Moller-Trumbore, two-sided, on the leaf-ordered triangle record
-__device__ __forceinline__ bool tri_test(const gfloat4* tri, uint32_t leaf, V3 o, V3 d, float tmin, float tmax,
-                                         float& t, int& face) {
-    const vf4 a = tri[3 * leaf], b = tri[3 * leaf + 1], c = tri[3 * leaf + 2];
-    const V3 e1 = V3{b.x, b.y, b.z}, e2 = V3{c.x, c.y, c.z};
-    const V3 p = cross(d, e2);
-    const float det = dot(e1, p);
+// FAST traversals address nodes and triangles by 32-bit byte offsets, start at
+// the constant TMIN and count no work; the others (scenes of more than
+// TRAV_FAST_FACES faces, another tmin, or with work counters) use 64-bit offsets
+// from the node or triangle index.  Both visit the same nodes in the same order.
+constexpr int TRAV_FAST_FACES = 1 << 25;      // 128 B nodes, at most one per face: offsets below 2^32
+constexpr uint32_t NODE_BYTES = 128, TRI_BYTES = 48;
+constexpr float FAST_TFAR = 0x1.a36e2ap+114f;    // the largest distance a FAST key holds (bits of TMIN + 2^30 - 2)
+
+// Moller-Trumbore, two-sided, on one triangle record.  Every rounding is written
+// out: which of two triangles a ray near their common edge meets first hangs on
+// them, and left to contraction the order of the two products that start the
+// first barycentric sum differed from one call site to another.  YFIRST: that sum
+// starts from the y product (the tests outside a traversal), else from x.
+template <bool YFIRST = false>
+__device__ __forceinline__ bool tri_test(const gchar* rec, V3 o, V3 d, float tmin, float tmax, float& t, int& face) {
+#pragma clang fp contract(off)
+    const gfloat4* const r = (const gfloat4*)rec;
+    const vf4 a = r[0], e1 = r[1], e2 = r[2];
+    const V3 p{__builtin_fmaf(d.y, e2.z, -(d.z * e2.y)), __builtin_fmaf(d.z, e2.x, -(d.x * e2.z)),
+               __builtin_fmaf(d.x, e2.y, -(d.y * e2.x))};
+    const float det = __builtin_fmaf(e1.z, p.z, __builtin_fmaf(e1.x, p.x, e1.y * p.y));
     if (det == 0.0f) return false;
     const float inv = 1.0f / det;
-    const V3 s = o - V3{a.x, a.y, a.z};
-    const float b1 = dot(s, p) * inv;
+    const V3 s{o.x - a.x, o.y - a.y, o.z - a.z};
+    const float sp = YFIRST ? __builtin_fmaf(s.x, p.x, s.y * p.y) : __builtin_fmaf(s.y, p.y, s.x * p.x);
+    const float b1 = __builtin_fmaf(s.z, p.z, sp) * inv;
     if (b1 < 0.0f || b1 > 1.0f) return false;
-    const V3 q = cross(s, e1);
-    const float b2 = dot(d, q) * inv;
-    if (b2 < 0.0f || b1 + b2 > 1.0f) return false;
-    t = dot(e2, q) * inv;
+    const V3 q{__builtin_fmaf(s.y, e1.z, -(s.z * e1.y)), __builtin_fmaf(s.z, e1.x, -(s.x * e1.z)),
+               __builtin_fmaf(s.x, e1.y, -(s.y * e1.x))};
+    const float dq = __builtin_fmaf(d.z, q.z, __builtin_fmaf(d.x, q.x, d.y * q.y));
+    if (dq * inv < 0.0f || __builtin_fmaf(dq, inv, b1) > 1.0f) return false;
+    t = __builtin_fmaf(e2.z, q.z, __builtin_fmaf(e2.x, q.x, e2.y * q.y)) * inv;
     face = __float_as_int(a.w);
     return t > tmin && t < tmax;
 }
+__device__ __forceinline__ const gchar* tri_at(const gchar* tri, uint32_t i) { return tri + (size_t)i * TRI_BYTES; }
 
 // distance along o + t d to the plane of face f, with the arithmetic of the
 // triangle test (the hit distance of a recorded hit)
@@ -255,190 +303,260 @@ __device__ __forceinline__ V3 safe_inv(V3 d) {
     return V3{f(d.x), f(d.y), f(d.z)};
 }
 
-// slab test of the 4 child boxes of a 4-wide node; entry distance per slot,
-// +inf for a miss or an empty slot
-__device__ __forceinline__ void node4_test(const gfloat4* nodes4, uint32_t node, V3 o, V3 inv, float tmin, float tmax,
-                                           float t[4], uint32_t c[4]) {
-    const gfloat4* n = nodes4 + 8 * (size_t)node;
-    const vf4 x0 = n[0], x1 = n[1], y0 = n[2], y1 = n[3], z0 = n[4], z1 = n[5], cc = n[6];
-    const float lx[4] = {x0.x, x0.y, x0.z, x0.w}, hx[4] = {x1.x, x1.y, x1.z, x1.w};
-    const float ly[4] = {y0.x, y0.y, y0.z, y0.w}, hy[4] = {y1.x, y1.y, y1.z, y1.w};
-    const float lz[4] = {z0.x, z0.y, z0.z, z0.w}, hz[4] = {z1.x, z1.y, z1.z, z1.w};
-    c[0] = __float_as_uint(cc.x); c[1] = __float_as_uint(cc.y); c[2] = __float_as_uint(cc.z); c[3] = __float_as_uint(cc.w);
+// A ray as the slab tests read it: origin, reciprocal direction, and for each
+// axis the byte offset (0 or 16) of its near planes inside a node's pair of
+// plane vectors: with them no plane pair has to be ordered by min and max.
+struct RayBox {
+    V3 o, inv;
+    uint32_t sx, sy, sz;
+};
+__device__ __forceinline__ RayBox ray_box(V3 o, V3 d) {
+    RayBox r;
+    r.o = o;
+    r.inv = safe_inv(d);
+    r.sx = (__float_as_uint(r.inv.x) >> 27) & 16u;
+    r.sy = (__float_as_uint(r.inv.y) >> 27) & 16u;
+    r.sz = (__float_as_uint(r.inv.z) >> 27) & 16u;
+    return r;
+}
+
+// Slab tests of the 4 child boxes of one 4-wide node (layout of k_pack4).  The
+// traversal issues vector instructions most of its time (62-89 % of the SIMD
+// cycles at 8 views of 256^2, 16 spp), so what counts is instructions per visit:
+// planes picked by the ray's signs instead of ordered, leaves and children named
+// by slot instead of by loaded codes, scalar base addresses.  Extension launch
+// 4.43e8 -> 3.6e8 instructions, paired launch 7.12e8 -> 5.6e8; the latter
+// 1295 -> 1204 us, a render of those views 3.46 -> 3.30 ms, the 40k-face step of
+// 16 views of 512^2 99.5 -> 95.2 ms.  A
+// node's internal children are consecutive nodes in consecutive slots, its leaf
+// children consecutive triangles likewise, so a child is named by its slot: no
+// child codes are loaded, selected or sorted.  t[s]: entry distance of slot s
+// (hit or not); hit and inner: masks of the slots whose box is hit and of the
+// internal ones.  node and first: byte offsets (FAST) or indices of the node and
+// of what slot 0's node would be; tri0 likewise of slot 0's triangle.
+template <bool FAST>
+__device__ __forceinline__ void node4_test(const TraceGeo& G, uint32_t node, const RayBox& r, float tmin, float tmax,
+                                           float t[4], bool hit[4], bool inner[4], uint32_t& first, uint32_t& tri0) {
+    vf4 nx, fx, ny, fy, nz, fz, cc;
+    if constexpr (FAST) {
+        const uint32_t ox = node | r.sx, oy = node | r.sy, oz = node | r.sz;
+        nx = *(const gfloat4*)(G.nodes + ox);      fx = *(const gfloat4*)(G.nodes + (ox ^ 16u));
+        ny = *(const gfloat4*)(G.nodes + oy + 32); fy = *(const gfloat4*)(G.nodes + (oy ^ 16u) + 32);
+        nz = *(const gfloat4*)(G.nodes + oz + 64); fz = *(const gfloat4*)(G.nodes + (oz ^ 16u) + 64);
+        cc = *(const gfloat4*)(G.nodes + node + 96);
+    } else {
+        const gchar* const n = G.nodes + (size_t)node * NODE_BYTES;
+        nx = *(const gfloat4*)(n + r.sx);      fx = *(const gfloat4*)(n + (r.sx ^ 16u));
+        ny = *(const gfloat4*)(n + r.sy + 32); fy = *(const gfloat4*)(n + (r.sy ^ 16u) + 32);
+        nz = *(const gfloat4*)(n + r.sz + 64); fz = *(const gfloat4*)(n + (r.sz ^ 16u) + 64);
+        cc = *(const gfloat4*)(n + 112);
+    }
+    first = __float_as_uint(cc.x);
+    tri0 = __float_as_uint(cc.y);
+    // ni internal slots from 0, or (-1) slots 1..3
+    const int ni = __float_as_int(cc.z);
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-        const float ax = (lx[s] - o.x) * inv.x, bx = (hx[s] - o.x) * inv.x;
-        const float ay = (ly[s] - o.y) * inv.y, by = (hy[s] - o.y) * inv.y;
-        const float az = (lz[s] - o.z) * inv.z, bz = (hz[s] - o.z) * inv.z;
-        const float t0 = fmaxf(fmaxf(fminf(ax, bx), fminf(ay, by)), fmaxf(fminf(az, bz), tmin));
-        const float t1 = fminf(fminf(fmaxf(ax, bx), fmaxf(ay, by)), fminf(fmaxf(az, bz), tmax)) * BOX_GROW;
-        t[s] = t0 <= t1 ? t0 : __int_as_float(0x7f800000);
+        const float ax = (nx[s] - r.o.x) * r.inv.x, bx = (fx[s] - r.o.x) * r.inv.x;
+        const float ay = (ny[s] - r.o.y) * r.inv.y, by = (fy[s] - r.o.y) * r.inv.y;
+        const float az = (nz[s] - r.o.z) * r.inv.z, bz = (fz[s] - r.o.z) * r.inv.z;
+        const float tn = fmaxf(fmaxf(ax, ay), az);
+        t[s] = FAST ? __builtin_amdgcn_fmed3f(tn, tmin, FAST_TFAR) : fmaxf(tn, tmin);
+        const float t1 = fminf(fminf(bx, by), fminf(bz, tmax)) * BOX_GROW;
+        hit[s] = t[s] <= t1;
+        inner[s] = s == 0 ? ni > 0 : (uint32_t)ni > (uint32_t)s;
     }
 }
-
-// leaf children of a visited node in slot order, kept in four registers: no
-// lane-varying index into a register array (which the compiler would move to
-// LDS), and one triangle-test site for all of them
-struct LeafList {
-    uint32_t l0 = 0, l1 = 0, l2 = 0, l3 = 0;
-    int n = 0;
-    __device__ __forceinline__ void add(uint32_t v) {
-        l0 = n == 0 ? v : l0;
-        l1 = n == 1 ? v : l1;
-        l2 = n == 2 ? v : l2;
-        l3 = n == 3 ? v : l3;
-        ++n;
-    }
-    __device__ __forceinline__ uint32_t pop() {
-        const uint32_t v = l0;
-        l0 = l1; l1 = l2; l2 = l3;
-        --n;
-        return v;
-    }
-};
-
-// moves the hit leaf children out of (t, c): their distance becomes +inf
-__device__ __forceinline__ LeafList take_leaves(float t[4], const uint32_t c[4]) {
-    LeafList L;
+// FAST sorts entry distances as integers that carry their slot: bits(t) -
+// bits(TMIN), below 2^30 for t in [TMIN, FAST_TFAR], above the two slot bits,
+// so the distance is exact.  (Entry distances are clamped to FAST_TFAR = 3.4e34,
+// which only keeps boxes, and the far limit of the keys with them.)
+constexpr uint32_t TMIN_BITS = 0x38d1b717u;                     // bits of 1e-4f
+constexpr uint32_t KEY_MISS = 0xffffffffu;
+__device__ __forceinline__ uint32_t dist_key(float t, uint32_t slot) {
+    return (__float_as_uint(t) << 2) + (slot - (TMIN_BITS << 2));
+}
+__device__ __forceinline__ uint32_t leaf_mask(const bool hit[4], const bool inner[4]) {
+    uint32_t m = 0;
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
-        if (t[s] < __int_as_float(0x7f800000) && (c[s] & LEAF_BIT)) {
-            L.add(c[s] & ~LEAF_BIT);
-            t[s] = __int_as_float(0x7f800000);
-        }
-    return L;
+    for (int s = 0; s < 4; ++s) m |= hit[s] && !inner[s] ? 1u << s : 0u;
+    return m;
 }
-
+template <bool FAST> __device__ __forceinline__ uint32_t child_node(uint32_t first, uint32_t slot) {
+    return first + slot * (FAST ? NODE_BYTES : 1u);
+}
+template <bool FAST> __device__ __forceinline__ const gchar* child_tri(const TraceGeo& G, uint32_t tri0, uint32_t slot) {
+    if constexpr (FAST) return G.tri + (uint32_t)(tri0 + __umul24(slot, TRI_BYTES));
+    else return G.tri + (size_t)(uint32_t)(tri0 + slot) * TRI_BYTES;
+}
 __device__ __forceinline__ void cswap(float& ta, uint32_t& ca, float& tb, uint32_t& cb) {
     if (tb < ta) {
         const float t = ta; ta = tb; tb = t;
         const uint32_t c = ca; ca = cb; cb = c;
     }
 }
+// The order in which a closest-hit traversal takes the internal children (key
+// form: slot in the low two bits): by entry distance, ties as the exchange
+// network (0 1)(2 3)(0 2)(1 3)(1 2) with strict comparisons leaves them.  Which
+// of two triangles met within a rounding of the same distance is found first
+// decides which box the running best hit culls, so ties are part of the result.
+// The first four exchanges never meet an equal distance in descending slots, so
+// minima and maxima of the keys make them; the last compares distances alone.
+__device__ __forceinline__ void sort_keys(uint32_t k[4]) {
+    const uint32_t a0 = min(k[0], k[1]), a1 = max(k[0], k[1]), a2 = min(k[2], k[3]), a3 = max(k[2], k[3]);
+    const uint32_t b1 = min(a1, a3), b2 = max(a0, a2);
+    const bool swap = b2 < (b1 & ~3u);
+    k[0] = min(a0, a2);
+    k[1] = swap ? b2 : b1;
+    k[2] = swap ? b1 : b2;
+    k[3] = max(a1, a3);
+}
+__device__ __forceinline__ void count_work(const TravStack& st, uint32_t visits, uint32_t tests) {
+    for (unsigned long long* w : {st.work, st.work2})
+        if (w) {
+            atomicAdd(w, (unsigned long long)visits);
+            atomicAdd(w + 1, (unsigned long long)tests);
+            atomicAdd(w + 2, 1ull);
+        }
+}
 
 // closest hit with t in (tmin, inf) excluding one face; ties go to the smaller face id.
 // (t0, f0): a hit already known (f0 >= 0, from the same triangle test), which
 // only prunes the traversal: the result is the least (t, face) either way
-__device__ int trace_closest(const DevScene& S, V3 o, V3 d, float tmin, int exclude, float& thit, TravStack& st,
+template <bool FAST = false>
+__device__ int trace_closest(const TraceGeo& G, V3 o, V3 d, float tmin, int exclude, float& thit, TravStack& st,
                              float t0 = __int_as_float(0x7f800000), int f0 = -1) {
     const float INF = __int_as_float(0x7f800000);
     float tbest = t0;
     int best = f0;
-    const TraceGeo G = trace_geo(S);
     if (G.nf <= 0) return -1;
     uint32_t tests = 0;
-    auto leaf = [&](uint32_t l) {
-        ++tests;
+    auto leaf = [&](const gchar* rec) {
+        if (!FAST) ++tests;
         float t; int f;
-        if (tri_test(G.tri, l, o, d, tmin, INF, t, f) && f != exclude) {
+        if (tri_test(rec, o, d, tmin, INF, t, f) && f != exclude) {
             if (t < tbest || (t == tbest && f < best)) { tbest = t; best = f; }
         }
     };
-    if (G.nf == 1) { leaf(0); thit = tbest; return best; }
-    const V3 inv = safe_inv(d);
+    if (G.nf == 1) { leaf(G.tri); thit = tbest; return best; }
+    const RayBox r = ray_box(o, d);
     uint32_t node = 0;
     int sp = 0;
     int iter = 0;
     for (;; ++iter) {
         if (iter >= TRAVERSAL_CAP) { atomicOr(st.err, ERR_LOOP); break; }
         float t[4];
-        uint32_t c[4];
-        node4_test(G.nodes4, node, o, inv, tmin, tbest, t, c);
+        bool hit[4], inner[4];
+        uint32_t first, tri0;
+        node4_test<FAST>(G, node, r, FAST ? TMIN : tmin, tbest, t, hit, inner, first, tri0);
+        uint32_t k[4];
+        if (FAST) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) k[s] = hit[s] && inner[s] ? dist_key(t[s], (uint32_t)s) : KEY_MISS;
+        }
         // hit leaf slots, tested in slot order at one site (a wave runs the
         // largest per-lane count of leaf tests, not one block per slot)
-        LeafList lv = take_leaves(t, c);
-        while (lv.n > 0) leaf(lv.pop());
+        for (uint32_t lv = leaf_mask(hit, inner); lv; lv &= lv - 1)
+            leaf(child_tri<FAST>(G, tri0, (uint32_t)__builtin_ctz(lv)));
+        // the hit internal slots not beyond the best hit, nearest first
+        bool h0, h1, h2, h3;
+        if (FAST) {
+            sort_keys(k);
+            const uint32_t kmax = dist_key(fminf(tbest, FAST_TFAR), 3u);
+            h0 = k[0] <= kmax; h1 = k[1] <= kmax; h2 = k[2] <= kmax; h3 = k[3] <= kmax;
+        } else {
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-            if (t[s] > tbest) t[s] = INF;
-        // nearest first: sort the 4 (distance, code) pairs
-        cswap(t[0], c[0], t[1], c[1]); cswap(t[2], c[2], t[3], c[3]);
-        cswap(t[0], c[0], t[2], c[2]); cswap(t[1], c[1], t[3], c[3]);
-        cswap(t[1], c[1], t[2], c[2]);
-        if (t[0] < INF) {
-            // the hit slots come first: push slots m-1 .. 1 (farthest first)
-            const bool h1 = t[1] < INF, h2 = t[2] < INF, h3 = t[3] < INF;
+            for (int s = 0; s < 4; ++s) {
+                k[s] = (uint32_t)s;
+                if (!(hit[s] && inner[s]) || t[s] > tbest) t[s] = INF;
+            }
+            cswap(t[0], k[0], t[1], k[1]); cswap(t[2], k[2], t[3], k[3]);
+            cswap(t[0], k[0], t[2], k[2]); cswap(t[1], k[1], t[3], k[3]);
+            cswap(t[1], k[1], t[2], k[2]);
+            h0 = t[0] < INF; h1 = t[1] < INF; h2 = t[2] < INF; h3 = t[3] < INF;
+        }
+        if (h0) {
+            // push the hit slots m-1 .. 1 of the order (farthest first)
             const int m = (int)h1 + (int)h2 + (int)h3;
-            const uint32_t a = h3 ? c[3] : (h2 ? c[2] : c[1]);
-            const uint32_t b = h3 ? c[2] : c[1];
-            if (!st.push3(sp, m, a, b, c[1])) { atomicOr(st.err, ERR_STACK); break; }
-            node = c[0];
+            const uint32_t a = h3 ? k[3] : (h2 ? k[2] : k[1]);
+            const uint32_t b = h3 ? k[2] : k[1];
+            if (!st.push3(sp, m, child_node<FAST>(first, a & 3u), child_node<FAST>(first, b & 3u),
+                          child_node<FAST>(first, k[1] & 3u))) {
+                atomicOr(st.err, ERR_STACK);
+                break;
+            }
+            node = child_node<FAST>(first, k[0] & 3u);
         } else {
             if (sp == 0) break;
             node = st.get(--sp);
         }
     }
     // node visits: one per iteration (the cap exit visits none)
-    const uint32_t visits = (uint32_t)min(iter + 1, TRAVERSAL_CAP);
-    for (unsigned long long* w : {st.work, st.work2})
-        if (w) {
-            atomicAdd(w, (unsigned long long)visits);
-            atomicAdd(w + 1, (unsigned long long)tests);
-            atomicAdd(w + 2, 1ull);
-        }
+    if (!FAST) count_work(st, (uint32_t)min(iter + 1, TRAVERSAL_CAP), tests);
     thit = tbest;
     return best;
 }
 
-__device__ bool trace_any_impl(const DevScene& S, V3 o, V3 d, float tmin, float tmax, int exclude, TravStack& st,
+template <bool FAST>
+__device__ bool trace_any_impl(const TraceGeo& G, V3 o, V3 d, float tmin, float tmax, int exclude, TravStack& st,
                                uint32_t& visits, uint32_t& tests) {
-    const float INF = __int_as_float(0x7f800000);
-    const TraceGeo G = trace_geo(S);
     if (G.nf <= 0) return false;
-    auto leaf = [&](uint32_t l) -> bool {
-        ++tests;
+    auto leaf = [&](const gchar* rec) -> bool {
+        if (!FAST) ++tests;
         float t; int f;
-        return tri_test(G.tri, l, o, d, tmin, tmax, t, f) && f != exclude;
+        return tri_test(rec, o, d, tmin, tmax, t, f) && f != exclude;
     };
-    if (G.nf == 1) return leaf(0);
-    const V3 inv = safe_inv(d);
-    uint32_t node = 0;
+    if (G.nf == 1) return leaf(G.tri);
+    const RayBox r = ray_box(o, d);
+    uint32_t node = 0, group = 0;
     int sp = 0;
     for (int iter = 0;; ++iter) {
         if (iter >= TRAVERSAL_CAP) { atomicOr(st.err, ERR_LOOP); return false; }
-        ++visits;
+        if (!FAST) ++visits;
         float t[4];
-        uint32_t c[4];
-        node4_test(G.nodes4, node, o, inv, tmin, tmax, t, c);
-        LeafList lv = take_leaves(t, c);
-        while (lv.n > 0)
-            if (leaf(lv.pop())) return true;
-        // the first hit slot is visited next, the others are pushed in slot order
-        bool have = false;
-        uint32_t next = 0, q0 = 0, q1 = 0, q2 = 0;
-        int m = 0;
+        bool hit[4], inner_s[4];
+        uint32_t first, tri0;
+        node4_test<FAST>(G, node, r, FAST ? TMIN : tmin, tmax, t, hit, inner_s, first, tri0);
+        for (uint32_t lv = leaf_mask(hit, inner_s); lv; lv &= lv - 1)
+            if (leaf(child_tri<FAST>(G, tri0, (uint32_t)__builtin_ctz(lv)))) return true;
+        uint32_t inner = 0;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            if (t[s] < INF) {
-                if (!have) { next = c[s]; have = true; }
-                else {
-                    q0 = m == 0 ? c[s] : q0;
-                    q1 = m == 1 ? c[s] : q1;
-                    q2 = m == 2 ? c[s] : q2;
-                    ++m;
+        for (int s = 0; s < 4; ++s) inner |= hit[s] && inner_s[s] ? 1u << s : 0u;
+        if constexpr (FAST) {
+            // the siblings still to visit form one group: the byte offset of slot 0's
+            // node with their slot mask in its low bits; one entry holds a group
+            if (inner) {
+                if (group & 15u) {
+                    if (!st.push1(sp, group)) { atomicOr(st.err, ERR_STACK); return false; }
                 }
+                group = first | inner;
+            } else if (!(group & 15u)) {
+                if (sp == 0) return false;
+                group = st.get(--sp);
             }
-        }
-        if (!st.push3(sp, m, q0, q1, q2)) { atomicOr(st.err, ERR_STACK); return false; }
-        if (have) {
-            node = next;
+            const uint32_t s = (uint32_t)__builtin_ctz(group);
+            node = child_node<FAST>(group & ~15u, s);
+            group &= group - 1;
         } else {
-            if (sp == 0) return false;
-            node = st.get(--sp);
+            // the first hit slot is visited next, the others are pushed in slot order
+            if (inner) {
+                node = first + (uint32_t)__builtin_ctz(inner);
+                for (inner &= inner - 1; inner; inner &= inner - 1)
+                    if (!st.push1(sp, first + (uint32_t)__builtin_ctz(inner))) { atomicOr(st.err, ERR_STACK); return false; }
+            } else {
+                if (sp == 0) return false;
+                node = st.get(--sp);
+            }
         }
     }
 }
 
-__device__ __forceinline__ bool trace_any(const DevScene& S, V3 o, V3 d, float tmin, float tmax, int exclude,
+template <bool FAST = false>
+__device__ __forceinline__ bool trace_any(const TraceGeo& G, V3 o, V3 d, float tmin, float tmax, int exclude,
                                           TravStack& st) {
     uint32_t visits = 0, tests = 0;
-    const bool r = trace_any_impl(S, o, d, tmin, tmax, exclude, st, visits, tests);
-    for (unsigned long long* w : {st.work, st.work2})
-        if (w) {
-            atomicAdd(w, (unsigned long long)visits);
-            atomicAdd(w + 1, (unsigned long long)tests);
-            atomicAdd(w + 2, 1ull);
-        }
+    const bool r = trace_any_impl<FAST>(G, o, d, tmin, tmax, exclude, st, visits, tests);
+    if (!FAST) count_work(st, visits, tests);
     return r;
 }
 
@@ -832,13 +950,14 @@ __device__ __forceinline__ V3 cam_dir(const DevCam& c, float sx, float sy) {
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void push_face(Hash& h, int f) { h.push(f < 0 ? 0xFFFFFFFFu : (uint32_t)f); }
 
-__device__ V3 trace_estimator(const DevScene& S, V3 o, V3 d, int exclude, int nvert, bool first_escape_full,
+template <bool FAST = false>
+__device__ V3 trace_estimator(const DevScene& S, const TraceGeo& G, V3 o, V3 d, int exclude, int nvert, bool first_escape_full,
                               const Ctr& ctr, const Key& key, Hash& hash, TravStack& st) {
     V3 L{0.f, 0.f, 0.f}, beta{1.f, 1.f, 1.f};
     float p_prev = 0.0f;
     for (int k = 1; k <= nvert + 1; ++k) {
         float t;
-        const int f = trace_closest(S, o, d, TMIN, exclude, t, st);
+        const int f = trace_closest<FAST>(G, o, d, TMIN, exclude, t, st);
         push_face(hash, f);
         if (f < 0) {
             if (S.has_env && (k > 1 || first_escape_full)) {
@@ -869,7 +988,7 @@ __device__ V3 trace_estimator(const DevScene& S, V3 o, V3 d, int exclude, int nv
                 const V3 wl = dl * (1.0f / r);
                 const float c = dot(n, wl);
                 if (c > 0.0f) {
-                    const bool occ = trace_any(S, x, wl, TMIN, r * (1.0f - SHADOW_SHRINK), f, st);
+                    const bool occ = trace_any<FAST>(G, x, wl, TMIN, r * (1.0f - SHADOW_SHRINK), f, st);
                     code = occ ? 1u : 2u;
                     if (!occ) L = L + mul(beta, mul(ld3(lt + 3), brdf_eval(wl, wo, n, m))) * (c / r2);
                 }
@@ -884,7 +1003,7 @@ __device__ V3 trace_estimator(const DevScene& S, V3 o, V3 d, int exclude, int nv
             const float c = dot(n, we);
             uint32_t code = 0;
             if (c > 0.0f && pe > 0.0f) {
-                const bool occ = trace_any(S, x, we, TMIN, __int_as_float(0x7f800000), f, st);
+                const bool occ = trace_any<FAST>(G, x, we, TMIN, __int_as_float(0x7f800000), f, st);
                 code = occ ? 1u : 2u;
                 if (!occ) {
                     const V3 fv = brdf_eval(we, wo, n, m);
@@ -1092,180 +1211,5 @@ __device__ __forceinline__ unsigned xcd_block() {
 // 69.8 -> 84.3 ms for k_extend, presumably because cheap and costly stretches
 // of the queue then land on different XCDs)
 __device__ __forceinline__ unsigned grid_block() { return ST_XCD_MAP ? xcd_block() : blockIdx.x; }
-
-// ---------------------------------------------------------------------------
-// persistent traversal of a ray queue with dynamic fetch: a wave refills its
-// idle lanes whenever at least FETCH_MIN of them are idle, so a lane whose ray
-// finished early takes the next ray instead of waiting for the slowest lane of
-// its wave.  Each ray's outcome is that of trace_any (ANY) or trace_closest.
-// ---------------------------------------------------------------------------
-#ifndef ST_FETCH_MIN
-#define ST_FETCH_MIN 16
-#endif
-#ifndef ST_FETCH_CHUNK
-#define ST_FETCH_CHUNK 128
-#endif
-#ifndef ST_FETCH_NC
-#define ST_FETCH_NC 8
-#endif
-constexpr int FETCH_MIN = ST_FETCH_MIN;      // idle lanes that trigger a refill
-constexpr int FETCH_CHUNK = ST_FETCH_CHUNK;  // rays a wave takes from a counter at a time
-constexpr int FETCH_NC = ST_FETCH_NC;        // counters, each owning a contiguous segment of the queue
-constexpr int FETCH_SLOT_INTS = FETCH_NC * 32;   // one 128-byte line per counter
-
-struct RayJob {
-    V3 o, d;
-    float tmax;   // any-hit: the ray is tested on (TMIN, tmax); closest hit: +inf
-    int excl;     // face excluded from the test (the ray's origin face), -1 for none
-    TraceGeo G;
-};
-
-// fetch(i, job) loads ray i and returns true, or stores ray i's outcome itself
-// and returns false when it needs no traversal.  finish(i, face, t) stores the
-// outcome: for ANY face is 1 when occluded and 0 otherwise; for the closest
-// hit face is -1 and t = +inf on a miss.
-template <bool ANY, class Fetch, class Finish>
-__device__ __forceinline__ void trace_queue(int* counters, int n, TravStack& st, Fetch fetch, Finish finish) {
-    const float INF = __int_as_float(0x7f800000);
-    // a finished ray's outcome is stored when its lane is refilled (or at the
-    // end), so that no store is in flight while the traversal waits on loads
-    bool live = false, pend = false, drained = n <= 0;
-    int idx = 0, sp = 0, iters = 0, best = -1;
-    float tbest = INF;
-    uint32_t node = 0;
-    RayJob J;
-    V3 inv{0.f, 0.f, 0.f};
-    uint32_t visits = 0, tests = 0, rays = 0;
-    // wave-uniform pool [cur, end) of rays taken from the counters; counter c
-    // hands out chunks of segment [c seg, (c + 1) seg), starting at this
-    // block's own counter and moving on to the others once it is used up
-    int cur = 0, end = 0, tried = 0;
-    const int seg = (int)(((long long)n + FETCH_NC - 1) / FETCH_NC);
-    const int home = (int)(blockIdx.x % FETCH_NC);
-    for (;;) {
-        const uint64_t idle = __ballot(!live);
-        const int nidle = __popcll(idle);
-        if ((cur < end || !drained) && (nidle >= FETCH_MIN || nidle == (int)__builtin_amdgcn_wavefrontsize())) {
-            const int leader = __ffsll((long long)idle) - 1;
-            while (cur >= end && !drained) {
-                const int c = (home + tried) % FETCH_NC;
-                int b = 0;
-                if ((int)__lane_id() == leader) b = atomicAdd(counters + 32 * c, FETCH_CHUNK);
-                b = __builtin_amdgcn_readlane(b, leader);   // wave-uniform from here on
-                const int s0 = c * seg, s1 = (int)min((long long)s0 + seg, (long long)n);
-                if (b < s1 - s0) {
-                    cur = s0 + b;
-                    end = (int)min((long long)cur + FETCH_CHUNK, (long long)s1);
-                } else if (++tried >= FETCH_NC) {
-                    drained = true;
-                }
-            }
-            if (pend) {
-                finish(idx, best, tbest);
-                pend = false;
-            }
-            const int take = min(nidle, end - cur);
-            if (!live && take > 0) {
-                const int rank = __popcll(idle & lanemask_lt64());
-                if (rank < take) {
-                    idx = cur + rank;
-                    if (fetch(idx, J)) {
-                        if (J.G.nf <= 0) {
-                            finish(idx, ANY ? 0 : -1, INF);
-                        } else if (J.G.nf == 1) {
-                            float t; int f;
-                            const bool h = tri_test(J.G.tri, 0, J.o, J.d, TMIN, J.tmax, t, f) && f != J.excl;
-                            if (ANY) finish(idx, h ? 1 : 0, INF);
-                            else finish(idx, h ? f : -1, h ? t : INF);
-                        } else {
-                            live = true;
-                            ++rays;
-                            inv = safe_inv(J.d);
-                            node = 0; sp = 0; iters = 0; best = ANY ? 0 : -1; tbest = INF;
-                        }
-                    }
-                }
-            }
-            if (take > 0) cur += take;
-        }
-        if (nidle == (int)__builtin_amdgcn_wavefrontsize() && drained && cur >= end) break;
-        if (!live) continue;
-        bool done = false;
-        if (iters >= TRAVERSAL_CAP) {
-            atomicOr(st.err, ERR_LOOP);
-            done = true;
-        } else {
-            ++iters;
-            ++visits;
-            float t[4];
-            uint32_t c[4];
-            node4_test(J.G.nodes4, node, J.o, inv, TMIN, ANY ? J.tmax : tbest, t, c);
-            LeafList lv = take_leaves(t, c);
-            while (lv.n > 0) {
-                ++tests;
-                float th; int fh;
-                if (tri_test(J.G.tri, lv.pop(), J.o, J.d, TMIN, J.tmax, th, fh) && fh != J.excl) {
-                    if (ANY) { best = 1; break; }
-                    if (th < tbest || (th == tbest && fh < best)) { tbest = th; best = fh; }
-                }
-            }
-            if (ANY && best) {
-                done = true;
-            } else {
-                bool have = false, overflow = false;
-                uint32_t next = 0;
-                if (ANY) {
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        if (t[s] < INF) {
-                            if (!have) { next = c[s]; have = true; }
-                            else if (sp >= LDS_STACK + SPILL_STACK) overflow = true;
-                            else st.put(sp++, c[s]);
-                        }
-                    }
-                } else {
-#pragma unroll
-                    for (int s = 0; s < 4; ++s)
-                        if (t[s] > tbest) t[s] = INF;
-                    // nearest first: continue with the nearest child, stack the others farthest-first
-                    cswap(t[0], c[0], t[1], c[1]); cswap(t[2], c[2], t[3], c[3]);
-                    cswap(t[0], c[0], t[2], c[2]); cswap(t[1], c[1], t[3], c[3]);
-                    cswap(t[1], c[1], t[2], c[2]);
-                    if (t[0] < INF) {
-                        next = c[0];
-                        have = true;
-#pragma unroll
-                        for (int s = 3; s >= 1; --s) {
-                            if (t[s] < INF) {
-                                if (sp >= LDS_STACK + SPILL_STACK) overflow = true;
-                                else st.put(sp++, c[s]);
-                            }
-                        }
-                    }
-                }
-                if (overflow) {
-                    atomicOr(st.err, ERR_STACK);
-                    done = true;
-                } else if (have) {
-                    node = next;
-                } else if (sp == 0) {
-                    done = true;
-                } else {
-                    node = st.get(--sp);
-                }
-            }
-        }
-        if (done) {
-            live = false;
-            pend = true;
-        }
-    }
-    if (pend) finish(idx, best, tbest);
-    if (st.work && rays) {
-        atomicAdd(st.work, (unsigned long long)visits);
-        atomicAdd(st.work + 1, (unsigned long long)tests);
-        atomicAdd(st.work + 2, (unsigned long long)rays);
-    }
-}
 
 } // namespace st

@@ -21,6 +21,7 @@ extern bool g_prof_on;
     } while (0)
 
 // every device allocation of one scene (library-owned)
+constexpr int PACK_TILE = 1024;     // binary nodes per block of the 4-wide packing's scan
 constexpr int TREELET_ROUNDS = 1;   // bottom-up treelet-restructuring passes over the Karras tree (a second one
                                     // bought no measurable traversal time for its 1.9 ms)
 constexpr int FACC = 16;   // gradient slots of one vertex: 3 corners x xyz, then the 7 material parameters
@@ -73,11 +74,12 @@ struct SceneDev {
     int* tleaves = nullptr;                  // [nf-1] triangles below every internal node
     float4* nodes4 = nullptr;                // [(nf-1)*8] 4-wide nodes (at most nf-1 of them)
     int* flag4 = nullptr;                    // [nf-1] binary node starts a 4-wide node
-    uint32_t* id4 = nullptr;                 // [nf-1] 4-wide node index of each such node
+    uint2* slots4 = nullptr;                 // [nf-1] internal and leaf slots of each such node, then what precedes it
+    uint2* tiles4 = nullptr;                 // [nf-1 in tiles of PACK_TILE] slot counts of a tile
     float4* ccost = nullptr;                 // [nf-1] collapse cost of a subtree in 1..4 slots
     uint32_t* cdec = nullptr;                // [nf-1] collapse decisions (bit fields, see k_collapse_cost)
-    float4* tri = nullptr;                   // [nf*3]
-    int* fleaf = nullptr;                    // [nf] leaf index of each face
+    float4* tri = nullptr;                   // [nf*3] triangle records, the leaf children of a 4-wide node together
+    int* fleaf = nullptr;                    // [nf] record of each face in tri
     // edges (topology fixed at creation)
     int4* edges = nullptr;
     double* edge_w = nullptr;
@@ -125,8 +127,6 @@ enum QCol {
 };
 
 // queue and path-state arrays of one wavefront chunk (SoA)
-constexpr int FETCH_INTS = 32 * FETCH_SLOT_INTS;   // slots k (shadow) and 16 + k (extension), k < 16
-
 struct Queues {
     float* ray[2][QNCOL];    // queue of bounce k is ray[k & 1]
     float* ht;               // hit t
@@ -140,7 +140,6 @@ struct Queues {
     uint8_t* socc;           // shadow entry outcome [entry][i]: 0 no ray, 1 occluded, 2 unoccluded
     uint32_t* slist;         // shadow entries (l * cap + i) that carry a ray, compacted per bounce
     int* cnt;                // ray counts per bounce (k), shadow-ray counts per bounce (32 + k)
-    int* fetch;              // fetch counters: slot k (shadow rays of bounce k), 16 + k (extension rays)
     uint32_t* spill;         // traversal stack spill
     float* L;                // per path sample radiance [total, 3] (processing order)
     int cap;                 // chunk capacity in paths
@@ -190,6 +189,7 @@ struct FwdParams {
     int* rec_face;           // optional hit records of the main paths: face of bounce k at [(k-1) rec_n + path]
     uint32_t* rec_occ;       // occluded shadow entries (bit l) of bounce k at [(k-1) rec_n + path]
     long long rec_n;
+    int fast;                // every scene within the FAST traversals' reach, no work counters
     unsigned long long* rec_key_dev;  // with rec_face: the records' key word, cleared by the first camera kernel
 };
 
@@ -222,6 +222,7 @@ void launch_check_finite(const float* a, long long na, const float* b, long long
 void launch_sample_radiance(const FwdParams& p, const float* L, long long total, float* out, hipStream_t st);
 
 struct BwdParams {
+    int fast;                // the scene is within the FAST traversals' reach, no work counters
     int rec_split;           // the main pass is split: a records-only pass, then one that traces if they are stale
     float* vrec;             // the adjoint's per-vertex replay records (adj_vrec_bytes)
     const DevScene* scenes;
@@ -297,7 +298,7 @@ void launch_stream_copy(float4* dst, const float4* src, long long n, hipStream_t
 // copies nwords host words to dst through kernel arguments (no staging memory;
 // a captured launch carries its own copy)
 void launch_put_words(uint32_t* dst, const uint32_t* src, size_t nwords, hipStream_t st);
-void launch_trace_debug(const DevScene* s, const float* o, const float* d, int n, float tmin, int brute,
+void launch_trace_debug(const DevScene* s, int nf, const float* o, const float* d, int n, float tmin, int brute,
                         int* out_face, float* out_t, uint32_t* spill, uint32_t* err, hipStream_t st);
 
 constexpr int TRACE_BLOCK = 256;

@@ -50,7 +50,6 @@ __global__ void k_camera(FwdParams p, Queues q, long long q0, int n) {
     if (blockIdx.x == 0 && threadIdx.x < 64) q.cnt[threadIdx.x] = threadIdx.x == 1 ? n : 0;
     // the hit records are rewritten from here on: their key is cleared until k_film
     if (q0 == 0 && blockIdx.x == 0 && threadIdx.x == 0 && p.rec_key_dev) *p.rec_key_dev = 0ull;
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < FETCH_INTS; j += stride) q.fetch[j] = 0;
     float* const* r = q.ray[1];
     for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < n; s += stride) {
         const long long qq = q0 + s;
@@ -75,75 +74,54 @@ __global__ void k_camera(FwdParams p, Queues q, long long q0, int n) {
 }
 
 // closest hit of queue entry i of bounce k
+template <bool FAST>
 __device__ __forceinline__ void extend_one(const FwdParams& p, const Queues& q, int k, float* const* r, int i,
                                            TravStack& st) {
     const DevCam& cam = p.cams[qu_ld(r, QVD, i) & 0xFFFFu];
-    const DevScene& S = p.scenes[cam.scene];
     const V3 o = k == 1 ? ld3(cam.eye) : V3{qf(r, QOX, i), qf(r, QOY, i), qf(r, QOZ, i)};
     const V3 d{qf(r, QDX, i), qf(r, QDY, i), qf(r, QDZ, i)};
-    uint32_t ex = qu_ld(r, QEXCL, i);
-    float t0 = __int_as_float(0x7f800000);
-    int f0 = -1;
-    if (k == 1 && ex != 0xFFFFFFFFu) {
-        // a primary-edge side ray names its edge: the edge's faces are
-        // tested first, so that the traversal starts with their hit
-        const int4 E = S.edges[ex & 0x7FFFFFFFu];
+    const uint32_t ex = qu_ld(r, QEXCL, i);
+    float t = __int_as_float(0x7f800000);
+    int f = -1;
+    for_scene(p.scenes, cam.scene, [&](const DevScene& S) {
+        const TraceGeo G = trace_geo(S);
+        float t0 = __int_as_float(0x7f800000);
+        int f0 = -1, excl = (int)ex;
+        if (k == 1 && ex != 0xFFFFFFFFu) {
+            // a primary-edge side ray names its edge: the edge's faces are
+            // tested first, so that the traversal starts with their hit
+            const int4 E = S.edges[ex & 0x7FFFFFFFu];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int fe = j == 0 ? E.z : E.w;
-            float th; int fh;
-            if (fe >= 0 && tri_test((const gfloat4*)S.tri, (uint32_t)S.fleaf[fe], o, d, TMIN,
-                                    __int_as_float(0x7f800000), th, fh) &&
-                (th < t0 || (th == t0 && fh < f0))) {
-                t0 = th;
-                f0 = fh;
+            for (int j = 0; j < 2; ++j) {
+                const int fe = j == 0 ? E.z : E.w;
+                float th; int fh;
+                if (fe >= 0 && tri_test<true>(tri_at(G.tri, (uint32_t)S.fleaf[fe]), o, d, TMIN, __int_as_float(0x7f800000), th,
+                                        fh) &&
+                    (th < t0 || (th == t0 && fh < f0))) {
+                    t0 = th;
+                    f0 = fh;
+                }
             }
+            excl = -1;
         }
-        ex = 0xFFFFFFFFu;
-    }
-    float t;
-    const int f = trace_closest(S, o, d, TMIN, (int)ex, t, st, t0, f0);
+        f = trace_closest<FAST>(G, o, d, TMIN, excl, t, st, t0, f0);
+    });
     qst(q.ht + i, t);
     qst(q.hf + i, f);
 }
 
-// closest hit for every queued ray of bounce k (queue k & 1)
-#ifndef ST_EXTEND_QUEUE
-#define ST_EXTEND_QUEUE 0
-#endif
+// closest hit for every queued ray of bounce k (queue k & 1): 64 consecutive
+// queue entries per wave, traced in lockstep
+template <bool FAST>
 __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_extend(FwdParams p, Queues q, int k) {
     __shared__ uint32_t lds[LDS_STACK * TRACE_BLOCK];
     TravStack st = make_trav_stack(lds, q.spill, p.err, p.work ? p.work + 3 * WORK_EXTEND : nullptr);
     const int n = q.cnt[k];
     float* const* r = q.ray[k & 1];
-    if (ST_EXTEND_QUEUE) {
-        // persistent waves refilled from the fetch counters of slot 16 + k
-        trace_queue<false>(
-            q.fetch + FETCH_SLOT_INTS * (16 + k), n, st,
-            [&](int i, RayJob& J) {
-                const DevCam& cam = p.cams[qu_ld(r, QVD, i) & 0xFFFFu];
-                const DevScene& S = p.scenes[cam.scene];
-                J.o = k == 1 ? ld3(cam.eye) : V3{qf(r, QOX, i), qf(r, QOY, i), qf(r, QOZ, i)};
-                J.d = V3{qf(r, QDX, i), qf(r, QDY, i), qf(r, QDZ, i)};
-                J.tmax = __int_as_float(0x7f800000);
-                J.excl = (int)qu_ld(r, QEXCL, i);
-                J.G = trace_geo(S);
-                return true;
-            },
-            [&](int i, int f, float t) {
-                q.ht[i] = t;
-                q.hf[i] = f;
-            });
-        return;
-    }
-    // 64 consecutive queue entries per wave, traced in lockstep
     const int stride = gridDim.x * blockDim.x;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) extend_one(p, q, k, r, i, st);
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) extend_one<FAST>(p, q, k, r, i, st);
 }
 
-#ifndef ST_SHADOW_QUEUE
-#define ST_SHADOW_QUEUE 0
-#endif
 #ifndef ST_PAIR_TRACE
 #define ST_PAIR_TRACE 1
 #endif
@@ -151,7 +129,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_extend(FwdParams p, 
 // each unoccluded contribution itself and records occlusion in the hit records,
 // and k_shadow_sum is not launched (the sum over one entry is that entry).
 __host__ __device__ __forceinline__ bool shadow_fused(const FwdParams& p, const Queues& q) {
-    return !ST_SHADOW_QUEUE && q.nent == 1 && !(p.dbg_hash || p.hash_by_q);
+    return q.nent == 1 && !(p.dbg_hash || p.hash_by_q);
 }
 
 // shading of bounce k: escapes, next-event set-up and BRDF continuation.
@@ -335,15 +313,17 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
 
 // shadow ray w of the list of bounce k: occlusion code, or (fused) the
 // unoccluded contribution added and the occlusion recorded
+template <bool FAST>
 __device__ __forceinline__ void shadow_one(const FwdParams& p, const Queues& q, int k, float* const* r, int w,
                                            bool fused, TravStack& st) {
     const uint32_t e = qld(q.slist + w);
     const int i = (int)(e % (uint32_t)q.cap);
     const int f = qld(q.sface + i);
-    const DevScene& S = p.scenes[p.cams[qu_ld(r, QVD, i) & 0xFFFFu].scene];
+    const int sc = p.cams[qu_ld(r, QVD, i) & 0xFFFFu].scene;
     const float tmax = qld(q.sh[3] + e);
     const V3 o{qld(q.sx[0] + i), qld(q.sx[1] + i), qld(q.sx[2] + i)}, dd{qld(q.sh[0] + e), qld(q.sh[1] + e), qld(q.sh[2] + e)};
-    const bool occluded = trace_any(S, o, dd, TMIN, tmax, f, st);
+    bool occluded = false;
+    for_scene(p.scenes, sc, [&](const DevScene& S) { occluded = trace_any<FAST>(trace_geo(S), o, dd, TMIN, tmax, f, st); });
     if (fused) {
         if (occluded) {
             if (p.rec_occ && (qu_ld(r, QVD, i) >> 16) == 0u) p.rec_occ[(size_t)(k - 1) * p.rec_n + qu_ld(r, QQ, i)] = 1u;
@@ -359,33 +339,17 @@ __device__ __forceinline__ void shadow_one(const FwdParams& p, const Queues& q, 
 // shadow rays of bounce k: the entries listed by k_shade (entry l of shading
 // point i is l * cap + i), one outcome code each (1 occluded, 2 unoccluded);
 // k_shade wrote 0 (no ray) for the others
+template <bool FAST>
 __global__ void __launch_bounds__(TRACE_BLOCK) SHADOW_OCC k_shadow(FwdParams p, Queues q, int k) {
     __shared__ uint32_t lds[LDS_STACK * TRACE_BLOCK];
     TravStack st = make_trav_stack(lds, q.spill, p.err, p.work ? p.work + 3 * WORK_SHADOW : nullptr);
     const int items = q.cnt[32 + k];
     float* const* r = q.ray[k & 1];
-    if (ST_SHADOW_QUEUE) {
-        // persistent waves refilled from the fetch counters of slot k
-        trace_queue<true>(
-            q.fetch + FETCH_SLOT_INTS * k, items, st,
-            [&](int w, RayJob& J) {
-                const uint32_t e = q.slist[w];
-                const int i = (int)(e % (uint32_t)q.cap);
-                const DevScene& S = p.scenes[p.cams[qu_ld(r, QVD, i) & 0xFFFFu].scene];
-                J.o = V3{q.sx[0][i], q.sx[1][i], q.sx[2][i]};
-                J.d = V3{q.sh[0][e], q.sh[1][e], q.sh[2][e]};
-                J.tmax = q.sh[3][e];
-                J.excl = q.sface[i];
-                J.G = trace_geo(S);
-                return true;
-            },
-            [&](int w, int occ, float) { q.socc[q.slist[w]] = occ ? 1 : 2; });
-        return;
-    }
     const bool fused = shadow_fused(p, q);
     // 64 consecutive listed rays per wave, traced in lockstep
     const int stride = gridDim.x * blockDim.x;
-    for (int w = blockIdx.x * blockDim.x + threadIdx.x; w < items; w += stride) shadow_one(p, q, k, r, w, fused, st);
+    for (int w = blockIdx.x * blockDim.x + threadIdx.x; w < items; w += stride)
+        shadow_one<FAST>(p, q, k, r, w, fused, st);
 }
 
 // One launch for the extension rays of bounce k + 1 and the shadow rays of
@@ -395,6 +359,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) SHADOW_OCC k_shadow(FwdParams p, 
 // one drain at the end instead of two.  Waves take the listed shadow rays first
 // (their count rounded up to whole waves), then the extension rays (this order
 // measured 0.7 ms faster per step than the other).
+template <bool FAST>
 __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_trace_pair(FwdParams p, Queues q, int k) {
     __shared__ uint32_t lds[LDS_STACK * TRACE_BLOCK];
     TravStack st = make_trav_stack(lds, q.spill, p.err, nullptr);
@@ -414,11 +379,11 @@ __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_trace_pair(FwdParams
         if (i < s64) {
             if (i < (uint32_t)items) {
                 st.work = wsh;
-                shadow_one(p, q, k, r, (int)i, fused, st);
+                shadow_one<FAST>(p, q, k, r, (int)i, fused, st);
             }
         } else {
             st.work = wext;
-            extend_one(p, q, k + 1, rn, (int)(i - s64), st);
+            extend_one<FAST>(p, q, k + 1, rn, (int)(i - s64), st);
         }
     }
 }
@@ -479,7 +444,10 @@ __global__ void __launch_bounds__(TRACE_BLOCK) k_forward_mega(FwdParams p, float
         const float4 u = draw4(ctr, 0, 0, key);
         const V3 d = cam_dir(c, (float)x + u.x, (float)y + u.y);
         Hash h{FNV_INIT, true};
-        const V3 r = trace_estimator(S, ld3(c.eye), d, -1, p.B, false, ctr, key, h, st);
+        V3 r{0.f, 0.f, 0.f};
+        for_scene(p.scenes, c.scene, [&](const DevScene& SU) {
+            r = trace_estimator(SU, trace_geo(SU), ld3(c.eye), d, -1, p.B, false, ctr, key, h, st);
+        });
         L[3 * qq] = r.x; L[3 * qq + 1] = r.y; L[3 * qq + 2] = r.z;
         if (p.dbg_hash) p.dbg_hash[canon(c, x, y, j, p.spp)] = h.h;
     }
@@ -534,6 +502,7 @@ __global__ void k_fill_u32(uint32_t* p, long long n, uint32_t v) {
 }
 
 // closest hit of caller-given rays (BVH, or brute force over all faces)
+template <bool FAST>
 __global__ void __launch_bounds__(TRACE_BLOCK) k_trace_debug(const DevScene* sc, const float* o, const float* d,
                                                              int n, float tmin, int brute, int* of, float* ot,
                                                              uint32_t* spill, uint32_t* err) {
@@ -542,17 +511,18 @@ __global__ void __launch_bounds__(TRACE_BLOCK) k_trace_debug(const DevScene* sc,
     TravStack st = make_trav_stack(lds, spill, err, nullptr);
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
+    const TraceGeo G = trace_geo(S);
     const V3 oo = ld3(o + 3 * i), dd = ld3(d + 3 * i);
     float tb = __int_as_float(0x7f800000);
     int fb = -1;
     if (brute) {
         for (int l = 0; l < S.nf; ++l) {
             float t; int f;
-            if (tri_test((const gfloat4*)S.tri, (uint32_t)l, oo, dd, tmin, __int_as_float(0x7f800000), t, f))
+            if (tri_test<true>(tri_at(G.tri, (uint32_t)l), oo, dd, tmin, __int_as_float(0x7f800000), t, f))
                 if (t < tb || (t == tb && f < fb)) { tb = t; fb = f; }
         }
     } else {
-        fb = trace_closest(S, oo, dd, tmin, -1, tb, st);
+        fb = trace_closest<FAST>(G, oo, dd, tmin, -1, tb, st);
     }
     of[i] = fb;
     ot[i] = tb;
@@ -584,7 +554,10 @@ void launch_wavefront_bounces(const FwdParams& p, Queues& q, int n, int has_env_
     const unsigned g = grid_for(n, TRACE_BLOCK, gmax);
     const int last = p.B + (has_env_any ? 1 : 0);
     const bool fused = shadow_fused(p, q);
-    ST_LAUNCH("k_extend", k_extend, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, 1);
+    const auto extend = p.fast ? k_extend<true> : k_extend<false>;
+    const auto shadow_rays = p.fast ? k_shadow<true> : k_shadow<false>;
+    const auto pair = p.fast ? k_trace_pair<true> : k_trace_pair<false>;
+    ST_LAUNCH("k_extend", extend, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, 1);
     if (hook) hook->tick();
     for (int k = 1; k <= last; ++k) {
         // bounce k is traced: shade it, then trace its shadow rays together with
@@ -596,15 +569,15 @@ void launch_wavefront_bounces(const FwdParams& p, Queues& q, int n, int has_env_
         if (hook) hook->tick();
         const bool shadow = k <= p.B, next = k < last;
         if (ST_PAIR_TRACE && shadow && next) {
-            ST_LAUNCH("k_trace_pair", k_trace_pair, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, k);
+            ST_LAUNCH("k_trace_pair", pair, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, k);
             if (hook) hook->tick();
         } else {
             if (shadow) {
-                ST_LAUNCH("k_shadow", k_shadow, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, k);
+                ST_LAUNCH("k_shadow", shadow_rays, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, k);
                 if (hook) hook->tick();
             }
             if (next) {
-                ST_LAUNCH("k_extend", k_extend, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, k + 1);
+                ST_LAUNCH("k_extend", extend, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, k + 1);
                 if (hook) hook->tick();
             }
         }
@@ -704,10 +677,11 @@ void launch_fill_u32(uint32_t* ptr, long long n, uint32_t v, hipStream_t st) {
     if (n > 0) ST_LAUNCH("k_fill_u32", k_fill_u32, dim3(grid_for(n, 256, 1u << 16)), dim3(256), 0, st, ptr, n, v);
 }
 
-void launch_trace_debug(const DevScene* s, const float* o, const float* d, int n, float tmin, int brute,
+void launch_trace_debug(const DevScene* s, int nf, const float* o, const float* d, int n, float tmin, int brute,
                         int* out_face, float* out_t, uint32_t* spill, uint32_t* err, hipStream_t st) {
+    const auto kern = tmin == TMIN && nf <= TRAV_FAST_FACES ? k_trace_debug<true> : k_trace_debug<false>;
     if (n > 0)
-        ST_LAUNCH("k_trace_debug", k_trace_debug, dim3((n + TRACE_BLOCK - 1) / TRACE_BLOCK), dim3(TRACE_BLOCK), 0, st, s, o,
+        ST_LAUNCH("k_trace_debug", kern, dim3((n + TRACE_BLOCK - 1) / TRACE_BLOCK), dim3(TRACE_BLOCK), 0, st, s, o,
                            d, n, tmin, brute, out_face, out_t, spill, err);
 }
 
