@@ -346,7 +346,8 @@ int queue_cap(long long cap, int nent) {
 size_t queue_bytes(int cap, int nent) {
     const size_t per = 256;
     const size_t words = 2 * QNCOL + 2 + 3 + 4 + 8 * (size_t)std::max(nent, 1);
-    return (size_t)cap * 4 * words + (size_t)cap * std::max(nent, 1) + (words + 10) * per + 64 * 4;
+    return (size_t)cap * 4 * words + (size_t)cap * std::max(nent, 1) + (words + 10) * per + 64 * 4 +
+           TAKE_INTS * sizeof(int);
 }
 
 constexpr size_t SPILL_BYTES = (size_t)SPILL_STACK * TRACE_GRID * TRACE_BLOCK * sizeof(uint32_t);
@@ -379,6 +380,7 @@ void carve_queues(char* base, int cap, int nent, float* L, uint32_t* spill, Queu
     q.socc = c.take<uint8_t>((size_t)cap * std::max(nent, 1));
     q.slist = c.take<uint32_t>((size_t)cap * std::max(nent, 1));
     q.cnt = c.take<int>(64);
+    q.take = c.take<int>(TAKE_INTS);
     q.spill = spill;
     q.L = L;
     q.cap = cap;
@@ -433,6 +435,7 @@ int render_impl(st_scene* owner, st_scene* const* scenes, int nscenes, const st_
     p.dbg_hash = o.debug_decision_hash;
     p.err = owner->d.err;
     p.work = (o.flags & ST_COUNT_WORK) ? owner->d.work : nullptr;
+    p.nscenes = nscenes;
     p.fast = p.work ? 0 : 1;
     for (int i = 0; i < nscenes; ++i) p.fast &= scenes[i]->d.nf <= TRAV_FAST_FACES ? 1 : 0;
     p.hash_by_q = nullptr;
@@ -1023,6 +1026,7 @@ int st_render_noalloc(st_scene* sc, const st_camera* cams, int32_t ncam, int32_t
     p.dbg_hash = o.debug_decision_hash;
     p.err = sc->d.err;
     p.work = (o.flags & ST_COUNT_WORK) ? sc->d.work : nullptr;
+    p.nscenes = 1;
     p.fast = !p.work && sc->d.nf <= TRAV_FAST_FACES ? 1 : 0;
     p.hash_by_q = nullptr;
     p.rec_face = nullptr;        // no hit records: the scene's record buffer is not touched
@@ -1252,6 +1256,7 @@ int st_render_backward(st_scene* sc, const st_camera* cams, int32_t ncam, int32_
         fp.dbg_hash = nullptr;
         fp.err = sc->d.err;
         fp.work = p.work;
+        fp.nscenes = 1;
         fp.fast = p.fast;
         fp.hash_by_q = hside;
         fp.rec_face = nullptr;

@@ -191,7 +191,7 @@ k_adjoint(BwdParams p, long long total) {
     __shared__ float red_s[TRACE_BLOCK / 64][64 * FACC];
     float* const red = red_s[threadIdx.x >> 6];
     TravStack st = make_trav_stack(lds, p.spill, p.err, p.work ? p.work + 3 * WORK_ADJOINT : nullptr);
-    const TraceGeo G = trace_geo(p.scenes[0]);     // a backward has one scene
+    const TraceGeo G = wave_geo(p.scenes[0]);     // a backward has one scene
     const RecMem rm{p.vrec, (size_t)gridDim.x * blockDim.x, (size_t)blockIdx.x * blockDim.x + threadIdx.x};
     const bool want_interior = !JOBS && (p.flags & 1u), want_secondary = p.flags & 4u;
     const bool sec_interior = p.flags & ST_EDGE_SECONDARY_INTERIOR;   // creases / material edges too
@@ -947,7 +947,7 @@ __device__ void shadow_edge_one(const BwdParams& p, const DevScene& S, const Dev
     const V3 y = va + (vb - va) * t;
     const V3 w = normalize(y - pl);
     float tr;
-    const TraceGeo G = trace_geo(S);
+    const TraceGeo G = wave_geo(S);
     const int fr = trace_closest<FAST>(G, y, w, TMIN, E.z, tr, st);
     h.push(fr < 0 ? 0xFFFFFFFFu : (uint32_t)fr);
     if (fr < 0 || fr == E.w) return;
@@ -1095,6 +1095,7 @@ void launch_primary_edges(const BwdParams& p, const FwdParams& fp, Queues& q, fl
     for (long long e0 = 0; e0 < total_edges; e0 += per) {
         const int n = (int)((total_edges - e0) < per ? (total_edges - e0) : per);
         launch_fill_u32((uint32_t*)q.cnt, 64, 0u, st);
+        launch_fill_u32((uint32_t*)q.take, TAKE_INTS, 0u, st);
         ST_LAUNCH("k_edge_camera", k_edge_camera, dim3(gridb(n, EDGE_CAM_BLOCK, 1 << 20)), dim3(EDGE_CAM_BLOCK), 0, st,
                   p, q, e0, n);
         if (hook) hook->tick();

@@ -214,8 +214,10 @@ __device__ __forceinline__ TravStack make_trav_stack(uint32_t* lds, uint32_t* sp
     return s;
 }
 
-// The geometry one traversal reads.  The pointers are wave-uniform (scalar
-// registers): a node or triangle load is then one base plus a 32-bit lane offset.
+// The geometry one traversal reads.  Where every ray of a launch is of one scene
+// the pointers are wave-uniform (scalar registers): a node or triangle load is then
+// a scalar base plus a 32-bit lane offset.  Rays of several scenes share waves (the
+// compacted queues mix them), so there each lane keeps its own pointers.
 typedef __attribute__((address_space(1))) const char gchar;
 struct TraceGeo {
     const gchar* nodes;
@@ -228,26 +230,12 @@ __device__ __forceinline__ const gchar* uniform_ptr(const void* p) {
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
     return (const gchar*)(((uint64_t)hi << 32) | lo);
 }
-// of a scene that is the same for every active lane
-__device__ __forceinline__ TraceGeo trace_geo(const DevScene& S) {
-    return TraceGeo{uniform_ptr(S.nodes4), uniform_ptr(S.tri), __builtin_amdgcn_readfirstlane(S.nf)};
+__device__ __forceinline__ TraceGeo lane_geo(const DevScene& S) {
+    return TraceGeo{(const gchar*)S.nodes4, (const gchar*)S.tri, S.nf};
 }
-// fn(scene) once per distinct scene among the active lanes, with the lanes of
-// that scene (views of several scenes meet in one wave only at their borders).
-// The loop leaves by a ballot: by a lane's own condition the compiler may move
-// fn behind the loop, where lanes of different scenes run it together.
-template <class Fn>
-__device__ __forceinline__ void for_scene(const DevScene* scenes, int sc, Fn fn) {
-    bool todo = true;
-    for (;;) {
-        const uint64_t m = __ballot(todo);
-        if (!m) break;
-        const int u = __builtin_amdgcn_readlane(sc, __ffsll((long long)m) - 1);
-        if (todo && sc == u) {
-            fn(scenes[u]);
-            todo = false;
-        }
-    }
+// of a scene that is the same for every active lane
+__device__ __forceinline__ TraceGeo wave_geo(const DevScene& S) {
+    return TraceGeo{uniform_ptr(S.nodes4), uniform_ptr(S.tri), __builtin_amdgcn_readfirstlane(S.nf)};
 }
 
 // FAST traversals address nodes and triangles by 32-bit byte offsets, start at

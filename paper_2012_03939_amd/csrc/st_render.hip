@@ -50,6 +50,7 @@ __global__ void k_camera(FwdParams p, Queues q, long long q0, int n) {
     if (blockIdx.x == 0 && threadIdx.x < 64) q.cnt[threadIdx.x] = threadIdx.x == 1 ? n : 0;
     // the hit records are rewritten from here on: their key is cleared until k_film
     if (q0 == 0 && blockIdx.x == 0 && threadIdx.x == 0 && p.rec_key_dev) *p.rec_key_dev = 0ull;
+    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < TAKE_INTS; j += stride) q.take[j] = 0;
     float* const* r = q.ray[1];
     for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < n; s += stride) {
         const long long qq = q0 + s;
@@ -73,53 +74,55 @@ __global__ void k_camera(FwdParams p, Queues q, long long q0, int n) {
     }
 }
 
-// closest hit of queue entry i of bounce k
-template <bool FAST>
+// closest hit of queue entry i of bounce k.  ONE: the launch has one scene, whose
+// geometry is GW; else each ray looks its own up
+template <bool FAST, bool ONE>
 __device__ __forceinline__ void extend_one(const FwdParams& p, const Queues& q, int k, float* const* r, int i,
-                                           TravStack& st) {
-    const DevCam& cam = p.cams[qu_ld(r, QVD, i) & 0xFFFFu];
-    const V3 o = k == 1 ? ld3(cam.eye) : V3{qf(r, QOX, i), qf(r, QOY, i), qf(r, QOZ, i)};
+                                           const TraceGeo& GW, TravStack& st) {
+    const uint32_t view = k == 1 || !ONE ? qu_ld(r, QVD, i) & 0xFFFFu : 0u;
+    const DevScene& S = p.scenes[ONE ? 0 : p.cams[view].scene];
+    const TraceGeo G = ONE ? GW : lane_geo(S);
+    const V3 o = k == 1 ? ld3(p.cams[view].eye) : V3{qf(r, QOX, i), qf(r, QOY, i), qf(r, QOZ, i)};
     const V3 d{qf(r, QDX, i), qf(r, QDY, i), qf(r, QDZ, i)};
-    const uint32_t ex = qu_ld(r, QEXCL, i);
-    float t = __int_as_float(0x7f800000);
-    int f = -1;
-    for_scene(p.scenes, cam.scene, [&](const DevScene& S) {
-        const TraceGeo G = trace_geo(S);
-        float t0 = __int_as_float(0x7f800000);
-        int f0 = -1, excl = (int)ex;
-        if (k == 1 && ex != 0xFFFFFFFFu) {
-            // a primary-edge side ray names its edge: the edge's faces are
-            // tested first, so that the traversal starts with their hit
-            const int4 E = S.edges[ex & 0x7FFFFFFFu];
+    uint32_t ex = qu_ld(r, QEXCL, i);
+    float t0 = __int_as_float(0x7f800000);
+    int f0 = -1;
+    if (k == 1 && ex != 0xFFFFFFFFu) {
+        // a primary-edge side ray names its edge: the edge's faces are
+        // tested first, so that the traversal starts with their hit
+        const int4 E = S.edges[ex & 0x7FFFFFFFu];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int fe = j == 0 ? E.z : E.w;
-                float th; int fh;
-                if (fe >= 0 && tri_test<true>(tri_at(G.tri, (uint32_t)S.fleaf[fe]), o, d, TMIN, __int_as_float(0x7f800000), th,
-                                        fh) &&
-                    (th < t0 || (th == t0 && fh < f0))) {
-                    t0 = th;
-                    f0 = fh;
-                }
+        for (int j = 0; j < 2; ++j) {
+            const int fe = j == 0 ? E.z : E.w;
+            float th; int fh;
+            if (fe >= 0 && tri_test<true>(tri_at(G.tri, (uint32_t)S.fleaf[fe]), o, d, TMIN, __int_as_float(0x7f800000),
+                                          th, fh) &&
+                (th < t0 || (th == t0 && fh < f0))) {
+                t0 = th;
+                f0 = fh;
             }
-            excl = -1;
         }
-        f = trace_closest<FAST>(G, o, d, TMIN, excl, t, st, t0, f0);
-    });
+        ex = 0xFFFFFFFFu;
+    }
+    float t;
+    const int f = trace_closest<FAST>(G, o, d, TMIN, (int)ex, t, st, t0, f0);
     qst(q.ht + i, t);
     qst(q.hf + i, f);
 }
 
 // closest hit for every queued ray of bounce k (queue k & 1): 64 consecutive
 // queue entries per wave, traced in lockstep
-template <bool FAST>
+template <bool FAST, bool ONE>
 __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_extend(FwdParams p, Queues q, int k) {
     __shared__ uint32_t lds[LDS_STACK * TRACE_BLOCK];
     TravStack st = make_trav_stack(lds, q.spill, p.err, p.work ? p.work + 3 * WORK_EXTEND : nullptr);
+    const TraceGeo G = wave_geo(p.scenes[0]);
     const int n = q.cnt[k];
     float* const* r = q.ray[k & 1];
-    const int stride = gridDim.x * blockDim.x;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) extend_one<FAST>(p, q, k, r, i, st);
+    wave_tiles(q.take + TAKE_NC * 32 * k, (uint32_t)n, [&](uint32_t t) {
+        const int i = (int)(t + __lane_id());
+        if (i < n) extend_one<FAST, ONE>(p, q, k, r, i, G, st);
+    });
 }
 
 #ifndef ST_PAIR_TRACE
@@ -313,17 +316,16 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
 
 // shadow ray w of the list of bounce k: occlusion code, or (fused) the
 // unoccluded contribution added and the occlusion recorded
-template <bool FAST>
+template <bool FAST, bool ONE>
 __device__ __forceinline__ void shadow_one(const FwdParams& p, const Queues& q, int k, float* const* r, int w,
-                                           bool fused, TravStack& st) {
+                                           bool fused, const TraceGeo& GW, TravStack& st) {
     const uint32_t e = qld(q.slist + w);
     const int i = (int)(e % (uint32_t)q.cap);
     const int f = qld(q.sface + i);
-    const int sc = p.cams[qu_ld(r, QVD, i) & 0xFFFFu].scene;
+    const TraceGeo G = ONE ? GW : lane_geo(p.scenes[p.cams[qu_ld(r, QVD, i) & 0xFFFFu].scene]);
     const float tmax = qld(q.sh[3] + e);
     const V3 o{qld(q.sx[0] + i), qld(q.sx[1] + i), qld(q.sx[2] + i)}, dd{qld(q.sh[0] + e), qld(q.sh[1] + e), qld(q.sh[2] + e)};
-    bool occluded = false;
-    for_scene(p.scenes, sc, [&](const DevScene& S) { occluded = trace_any<FAST>(trace_geo(S), o, dd, TMIN, tmax, f, st); });
+    const bool occluded = trace_any<FAST>(G, o, dd, TMIN, tmax, f, st);
     if (fused) {
         if (occluded) {
             if (p.rec_occ && (qu_ld(r, QVD, i) >> 16) == 0u) p.rec_occ[(size_t)(k - 1) * p.rec_n + qu_ld(r, QQ, i)] = 1u;
@@ -339,17 +341,19 @@ __device__ __forceinline__ void shadow_one(const FwdParams& p, const Queues& q, 
 // shadow rays of bounce k: the entries listed by k_shade (entry l of shading
 // point i is l * cap + i), one outcome code each (1 occluded, 2 unoccluded);
 // k_shade wrote 0 (no ray) for the others
-template <bool FAST>
+template <bool FAST, bool ONE>
 __global__ void __launch_bounds__(TRACE_BLOCK) SHADOW_OCC k_shadow(FwdParams p, Queues q, int k) {
     __shared__ uint32_t lds[LDS_STACK * TRACE_BLOCK];
     TravStack st = make_trav_stack(lds, q.spill, p.err, p.work ? p.work + 3 * WORK_SHADOW : nullptr);
+    const TraceGeo G = wave_geo(p.scenes[0]);
     const int items = q.cnt[32 + k];
     float* const* r = q.ray[k & 1];
     const bool fused = shadow_fused(p, q);
     // 64 consecutive listed rays per wave, traced in lockstep
-    const int stride = gridDim.x * blockDim.x;
-    for (int w = blockIdx.x * blockDim.x + threadIdx.x; w < items; w += stride)
-        shadow_one<FAST>(p, q, k, r, w, fused, st);
+    wave_tiles(q.take + TAKE_NC * 32 * (16 + k), (uint32_t)items, [&](uint32_t t) {
+        const int w = (int)(t + __lane_id());
+        if (w < items) shadow_one<FAST, ONE>(p, q, k, r, w, fused, G, st);
+    });
 }
 
 // One launch for the extension rays of bounce k + 1 and the shadow rays of
@@ -359,13 +363,14 @@ __global__ void __launch_bounds__(TRACE_BLOCK) SHADOW_OCC k_shadow(FwdParams p, 
 // one drain at the end instead of two.  Waves take the listed shadow rays first
 // (their count rounded up to whole waves), then the extension rays (this order
 // measured 0.7 ms faster per step than the other).
-template <bool FAST>
+template <bool FAST, bool ONE>
 __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_trace_pair(FwdParams p, Queues q, int k) {
     __shared__ uint32_t lds[LDS_STACK * TRACE_BLOCK];
     TravStack st = make_trav_stack(lds, q.spill, p.err, nullptr);
     st.work2 = p.work ? p.work + 3 * WORK_PAIR : nullptr;
     unsigned long long* const wext = p.work ? p.work + 3 * WORK_EXTEND : nullptr;
     unsigned long long* const wsh = p.work ? p.work + 3 * WORK_SHADOW : nullptr;
+    const TraceGeo G = wave_geo(p.scenes[0]);
     const int n = q.cnt[k + 1];
     const int items = q.cnt[32 + k];
     float* const* rn = q.ray[(k + 1) & 1];
@@ -374,18 +379,19 @@ __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_trace_pair(FwdParams
     // unsigned: with many lights the two counts together can pass 2^31 (each is
     // below 2^31, the grid below 2^21, so the sum and the next index fit 32 bits)
     const uint32_t s64 = ((uint32_t)items + 63u) & ~63u;
-    const uint32_t stride = gridDim.x * blockDim.x, all = s64 + (uint32_t)n;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < all; i += stride) {
-        if (i < s64) {
+    const uint32_t all = s64 + (uint32_t)n;
+    wave_tiles(q.take + TAKE_NC * 32 * (16 + k), all, [&](uint32_t t) {
+        const uint32_t i = t + __lane_id();
+        if (t < s64) {
             if (i < (uint32_t)items) {
                 st.work = wsh;
-                shadow_one<FAST>(p, q, k, r, (int)i, fused, st);
+                shadow_one<FAST, ONE>(p, q, k, r, (int)i, fused, G, st);
             }
-        } else {
+        } else if (i < all) {
             st.work = wext;
-            extend_one<FAST>(p, q, k + 1, rn, (int)(i - s64), st);
+            extend_one<FAST, ONE>(p, q, k + 1, rn, (int)(i - s64), G, st);
         }
-    }
+    });
 }
 
 // shadow contributions of bounce k added per shading point in entry order
@@ -444,10 +450,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) k_forward_mega(FwdParams p, float
         const float4 u = draw4(ctr, 0, 0, key);
         const V3 d = cam_dir(c, (float)x + u.x, (float)y + u.y);
         Hash h{FNV_INIT, true};
-        V3 r{0.f, 0.f, 0.f};
-        for_scene(p.scenes, c.scene, [&](const DevScene& SU) {
-            r = trace_estimator(SU, trace_geo(SU), ld3(c.eye), d, -1, p.B, false, ctr, key, h, st);
-        });
+        const V3 r = trace_estimator(S, lane_geo(S), ld3(c.eye), d, -1, p.B, false, ctr, key, h, st);
         L[3 * qq] = r.x; L[3 * qq + 1] = r.y; L[3 * qq + 2] = r.z;
         if (p.dbg_hash) p.dbg_hash[canon(c, x, y, j, p.spp)] = h.h;
     }
@@ -511,7 +514,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) k_trace_debug(const DevScene* sc,
     TravStack st = make_trav_stack(lds, spill, err, nullptr);
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const TraceGeo G = trace_geo(S);
+    const TraceGeo G = wave_geo(S);
     const V3 oo = ld3(o + 3 * i), dd = ld3(d + 3 * i);
     float tb = __int_as_float(0x7f800000);
     int fb = -1;
@@ -554,9 +557,10 @@ void launch_wavefront_bounces(const FwdParams& p, Queues& q, int n, int has_env_
     const unsigned g = grid_for(n, TRACE_BLOCK, gmax);
     const int last = p.B + (has_env_any ? 1 : 0);
     const bool fused = shadow_fused(p, q);
-    const auto extend = p.fast ? k_extend<true> : k_extend<false>;
-    const auto shadow_rays = p.fast ? k_shadow<true> : k_shadow<false>;
-    const auto pair = p.fast ? k_trace_pair<true> : k_trace_pair<false>;
+    const bool one = p.fast && p.nscenes == 1;
+    const auto extend = one ? k_extend<true, true> : p.fast ? k_extend<true, false> : k_extend<false, false>;
+    const auto shadow_rays = one ? k_shadow<true, true> : p.fast ? k_shadow<true, false> : k_shadow<false, false>;
+    const auto pair = one ? k_trace_pair<true, true> : p.fast ? k_trace_pair<true, false> : k_trace_pair<false, false>;
     ST_LAUNCH("k_extend", extend, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, 1);
     if (hook) hook->tick();
     for (int k = 1; k <= last; ++k) {

@@ -78,3 +78,24 @@ def test_fast_and_counting_traversals_agree(B, nf):
     for x, y in zip(ga, gb):
         # float32 sums of the same terms in another order
         assert torch.allclose(x, y, rtol=1e-4, atol=1e-4 * float(x.abs().max()))
+
+
+@pytest.mark.parametrize("size", [(1, 1), (9, 7), (64, 1), (65, 1), (256, 512), (363, 362), (1024, 1024), (1031, 1021)])
+def test_tile_counts(B, size):
+    """Rays in tiles of 64 over the waves of a launch: fewer tiles than waves, as many,
+    one more (2,048 waves in the allocation-free render, 16,384 in the other), and the
+    same paths in small chunks, give the same image bit for bit."""
+    w, h = size
+    _say(f"case tiles: {w}x{h}")
+    rng = np.random.default_rng(11)
+    V, F = S.noise_sphere(6, 0.2, noise_seed=4)
+    g = B.GPUScene(V.astype(np.float32), F, S.random_materials(F.shape[0], rng), S.hemisphere_lights(1, rng),
+                   S.gaussian_lobe_envmap(rng, 32, 16))
+    cams = [S.look_at_origin((0.5, 2.0, 2.0), w, h)]
+    a = g.render(cams, 1, 2, seed=5)
+    b = g.render(cams, 1, 2, seed=5, queue_capacity=100000)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
+    if w * h <= 1 << 20:
+        assert torch.equal(a, g.render_noalloc(cams, 1, 2, seed=5))
+    g.check_errors()
