@@ -186,10 +186,9 @@ __device__ __forceinline__ int kdelta(const uint32_t* m, const uint32_t* fa, int
     return __clzll(a ^ b);
 }
 
-__global__ void k_karras(const uint32_t* __restrict__ m, const uint32_t* __restrict__ fa, int n, int* child,
-                         int* parent) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n - 1) return;
+// children codes of internal node i and the range [first, last] of leaves below it
+__device__ __forceinline__ int2 karras_node(const uint32_t* __restrict__ m, const uint32_t* __restrict__ fa, int n, int i,
+                                            int& left, int& right) {
     const int d = kdelta(m, fa, n, i, i + 1) > kdelta(m, fa, n, i, i - 1) ? 1 : -1;
     const int dmin = kdelta(m, fa, n, i, i - d);
     int lmax = 2;
@@ -205,8 +204,17 @@ __global__ void k_karras(const uint32_t* __restrict__ m, const uint32_t* __restr
         if (kdelta(m, fa, n, i, i + (s + t) * d) > dnode) s += t;
     } while (t > 1);
     const int split = i + s * d + min(d, 0);
-    const int left = (min(i, j) == split) ? (int)(LEAF_BIT | (uint32_t)split) : split;
-    const int right = (max(i, j) == split + 1) ? (int)(LEAF_BIT | (uint32_t)(split + 1)) : split + 1;
+    left = (min(i, j) == split) ? (int)(LEAF_BIT | (uint32_t)split) : split;
+    right = (max(i, j) == split + 1) ? (int)(LEAF_BIT | (uint32_t)(split + 1)) : split + 1;
+    return make_int2(min(i, j), max(i, j));
+}
+
+__global__ void k_karras(const uint32_t* __restrict__ m, const uint32_t* __restrict__ fa, int n, int* child,
+                         int* parent) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n - 1) return;
+    int left, right;
+    karras_node(m, fa, n, i, left, right);
     child[2 * i] = left;
     child[2 * i + 1] = right;
     parent[(left & (int)LEAF_BIT) ? (n - 1) + (left & 0x7FFFFFFF) : left] = i;
@@ -226,92 +234,34 @@ __device__ __forceinline__ void put_tri(const float* __restrict__ V, const int* 
     fleaf[f] = (int)i;
 }
 
-__global__ void k_leaf_init(const uint32_t* __restrict__ sface, const float4* __restrict__ bmin,
-                            const float4* __restrict__ bmax, const float* __restrict__ V, const int* __restrict__ F,
-                            int n, float* aabb, float4* tri, int* fleaf, int* cnt) {
+// The radix tree over the sorted keys as k_treelets walks it: per node (internal
+// nodes, then leaves) its parent and which child it is, (parent << 1) | side, -1 at
+// the root; per internal node the leaves below it.  Also the 64-bit keys and the
+// cleared arrival counters; with one face, its record and box.
+__global__ void k_tree_init(const uint32_t* __restrict__ m, const uint32_t* __restrict__ fa, int n, int* up, int2* range,
+                            uint64_t* keys, int* cnt, const float4* __restrict__ bmin, const float4* __restrict__ bmax,
+                            const float* __restrict__ V, const int* __restrict__ F, float* aabb, float4* tri, int* fleaf) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n - 1) cnt[i] = 0;
     if (i >= n) return;
-    const int f = (int)sface[i];
-    float* b = aabb + 6 * ((size_t)(n - 1) + i);
-    const float4 mn = bmin[f], mx = bmax[f];
-    b[0] = mn.x; b[1] = mn.y; b[2] = mn.z; b[3] = mx.x; b[4] = mx.y; b[5] = mx.z;
-    if (n == 1) put_tri(V, F, f, 0, tri, fleaf);     // otherwise k_pack4 orders them by node
+    keys[i] = ((uint64_t)m[i] << 32) | fa[i];
+    if (n == 1) {
+        put_tri(V, F, 0, 0, tri, fleaf);
+        aabb[0] = bmin[0].x; aabb[1] = bmin[0].y; aabb[2] = bmin[0].z;
+        aabb[3] = bmax[0].x; aabb[4] = bmax[0].y; aabb[5] = bmax[0].z;
+    }
+    if (i >= n - 1) return;
+    cnt[i] = 0;
+    int left, right;
+    range[i] = karras_node(m, fa, n, i, left, right);
+    up[(left & (int)LEAF_BIT) ? (n - 1) + (left & 0x7FFFFFFF) : left] = i << 1;
+    up[(right & (int)LEAF_BIT) ? (n - 1) + (right & 0x7FFFFFFF) : right] = (i << 1) | 1;
+    if (i == 0) up[0] = -1;
 }
 
 __device__ __forceinline__ float aload(const float* p) {
     return __uint_as_float(__hip_atomic_load((const uint32_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
-__global__ void k_refit(const int* __restrict__ parent, const int* __restrict__ child, int n, float* aabb,
-                        int* cnt) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    int node = parent[(n - 1) + i];
-    for (int depth = 0; node >= 0 && depth < 128; ++depth) {
-        __threadfence();
-        if (atomicAdd(&cnt[node], 1) == 0) return;    // the other child is not done yet
-        __threadfence();
-        float box[6];
-        const int c0 = child[2 * node], c1 = child[2 * node + 1];
-        const size_t i0 = (c0 & (int)LEAF_BIT) ? (size_t)(n - 1) + (c0 & 0x7FFFFFFF) : (size_t)c0;
-        const size_t i1 = (c1 & (int)LEAF_BIT) ? (size_t)(n - 1) + (c1 & 0x7FFFFFFF) : (size_t)c1;
-        for (int k = 0; k < 3; ++k) {
-            box[k] = fminf(aload(aabb + 6 * i0 + k), aload(aabb + 6 * i1 + k));
-            box[3 + k] = fmaxf(aload(aabb + 6 * i0 + 3 + k), aload(aabb + 6 * i1 + 3 + k));
-        }
-        for (int k = 0; k < 6; ++k)
-            __hip_atomic_store((uint32_t*)(aabb + 6 * (size_t)node + k), __float_as_uint(box[k]), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        node = parent[node];
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Treelet restructuring of the Karras tree (Karras and Aila, HPG 2013), one
-// bottom-up pass per launch.  Every internal node r with at least TL_LEAVES
-// triangles below it, once both of its subtrees are final (second arrival at
-// r's counter, as in the refit), becomes the root of a treelet of TL_LEAVES
-// entries (smaller nodes only get their triangle count and SAH cost, each by
-// the lane that reached it): starting from r's two children, the
-// internal entry with the largest box area (first in list order on ties) is
-// replaced by its two children, appended at the end of the list.  The entries
-// are re-arranged into the binary tree of least SAH cost (a triangle leaf costs
-// its box area, an internal node C_INNER * area + the costs of its children),
-// found by dynamic programming over the 2^k - 1 subsets of entries; the
-// treelet's internal nodes are reused (r stays the root, the others in
-// ascending id order along the preorder of the new tree).  All comparisons are
-// in float32 with contraction off, in a fixed order, so the tree is a function
-// of the mesh alone, not of the wave schedule.
-//
-// One wave owns a treelet at a time: lane 0 forms it and writes the rebuilt
-// nodes, the 64 lanes share the subset DP (subsets L and L + 64 per lane, one
-// subset size per step).  Every access to tree data that another wave may
-// write during the pass is an agent-scope atomic (coherent across the XCDs'
-// L2s without flushing them), so the hand-off at a node's counter needs only
-// the wave's own outstanding stores drained before the increment
-// (handoff_release), not an L2 write-back and invalidate per level.
-// ---------------------------------------------------------------------------
-constexpr int TL_LEAVES = 7;
-constexpr float TL_C_INNER = 1.2f;
-constexpr int TL_BLOCK = 256;
-constexpr int TL_WAVES = TL_BLOCK / 64;
-constexpr int TL_GUARD = 1 << 16;
-
-__device__ __forceinline__ int ald_i(const int* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void ast_i(int* p, int v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void ast_f(float* p, float v) {
-    __hip_atomic_store((uint32_t*)p, __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float tl_area(const float* b) {
-#pragma clang fp contract(off)
-    const float dx = b[3] - b[0], dy = b[4] - b[1], dz = b[5] - b[2];
-    return 2.0f * ((dx * dy + dy * dz) + dz * dx);
-}
 __device__ __forceinline__ void handoff_release() {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);     // no compiler motion across this point
     __builtin_amdgcn_s_waitcnt(0);               // every store of this wave has completed
@@ -322,213 +272,439 @@ __device__ __forceinline__ void wave_sync_lds() {
     __builtin_amdgcn_wave_barrier();
 }
 
-struct TreeletLds {
-    float opt[128];
-    int part[128];
-    int ent[TL_LEAVES + 1];
-    int ids[TL_LEAVES];
-    float box[TL_LEAVES + 1][6];
-    float cost[TL_LEAVES + 1];
-    int leaves[TL_LEAVES + 1];
-    int k;
+// ---------------------------------------------------------------------------
+// Refit and treelet restructuring of the Karras tree (Karras and Aila, HPG 2013) in
+// one bottom-up pass.  Every internal node r with at least TL_LEAVES triangles below
+// it, once both of its subtrees are final, becomes the root of a treelet of
+// TL_LEAVES entries: starting from r's two children, the internal entry with the
+// largest box area (first in list order on ties) is replaced by its two children,
+// appended at the end of the list.  The entries are re-arranged into the binary tree
+// of least SAH cost (a triangle leaf costs its box area, an internal node C_INNER *
+// area + the costs of its children), found by dynamic programming over the 2^7 - 1
+// subsets of entries; the treelet's internal nodes are reused (r stays the root, the
+// others in ascending id order along the preorder of the new tree).  All comparisons
+// are in float32 with contraction off, in a fixed order, so the tree is a function of
+// the mesh alone, not of the wave schedule.
+//
+// The time is that of the longest chain of hand-offs, root to leaf, so each link is
+// made short.  A node is one 64-byte record, its two children's halves of 8 words:
+// code, box (lower, upper), SAH cost; whoever finishes a subtree writes its half of
+// the parent's record and counts its arrival, the second to arrive goes on with the
+// parent.  A treelet reads one record per entry it opens, 8 lanes to a record.
+// Subtrees that lie inside a block's TL_SPAN leaves (a radix tree's nodes cover
+// ranges of leaves, and node i's range has i at one end) are built in LDS; the nodes
+// above go through global memory with agent-scope accesses (coherent across the XCDs'
+// L2s without flushing them; a hand-off needs only the wave's own stores drained).
+// One wave owns a treelet: its lanes share the list, the subset boxes and the subset
+// programme, whose splits each lane holds in registers.
+// ---------------------------------------------------------------------------
+constexpr int TL_LEAVES = 7;
+constexpr float TL_C_INNER = 1.2f;
+#ifndef ST_TL_SPAN
+#define ST_TL_SPAN 512
+#endif
+#ifndef ST_TL_PER_WAVE
+#define ST_TL_PER_WAVE 32
+#endif
+constexpr int TL_SPAN = ST_TL_SPAN;             // leaves per block
+constexpr int TL_PER_WAVE = ST_TL_PER_WAVE;     // leaves each wave starts from
+constexpr int TL_WAVES = TL_SPAN / TL_PER_WAVE;
+constexpr int TL_BLOCK = 64 * TL_WAVES;
+constexpr int TL_GUARD = 1 << 16;
+static_assert(TL_PER_WAVE <= 64 && TL_BLOCK <= 1024, "leaves per wave");
+
+__device__ __forceinline__ float tl_area(float dx, float dy, float dz) {
+#pragma clang fp contract(off)
+    return 2.0f * ((dx * dy + dy * dz) + dz * dx);
+}
+
+// a subtree as its parent's record holds it
+struct TlHalf {
+    uint32_t w[8];      // code, box lower xyz, box upper xyz, cost
+};
+struct TlLds {
+    uint32_t ent[TL_LEAVES][8];
+    float area[128], opt[128];
+    uint32_t part[128];
+    uint32_t ids[8];
 };
 
-__device__ void treelet_restructure(int r, int lane, TreeletLds& T, int* child, int* parent, float* aabb,
-                                    float* tcost, int* tleaves, int n) {
+// record words [2 j, 2 j + 1] of a node, j < 8
+struct TlLocal {        // the block's records in LDS
+    uint64_t* rec;
+    int lo;
+    __device__ __forceinline__ uint64_t load(int node, int j) const { return rec[8 * (node - lo) + j]; }
+    __device__ __forceinline__ void store(int node, int j, uint64_t v) const { rec[8 * (node - lo) + j] = v; }
+};
+struct TlGlobal {
+    uint64_t* rec;
+    __device__ __forceinline__ uint64_t load(int node, int j) const {
+        return __hip_atomic_load(rec + 8 * (size_t)node + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ void store(int node, int j, uint64_t v) const {
+        __hip_atomic_store(rec + 8 * (size_t)node + j, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
+
+// The splits (P, S ^ P) of the subsets a lane evaluates, as word offsets P | (S ^ P)
+// << 8, and the subset itself; by subset size.  Subset S of size s is split at P =
+// its lowest bit plus the bits of the rest that c selects, c = 2^(s-1) - 2 .. 0 (the
+// order of preference among equal costs).  Sizes 2 to 4: one lane a subset; size 5:
+// two lanes (c even, c odd), size 6: eight (c mod 8), size 7: one lane a split.
+struct TlPlan {
+    uint32_t set[6], s2[1], s3[3], s4[7], s5[8], s6[4], s7[1];     // set[s - 2]: the subset of size s, 0 for none
+};
+constexpr int TL_PLAN_WORDS = sizeof(TlPlan) / sizeof(uint32_t);
+struct TlTable {
+    uint32_t w[TL_PLAN_WORDS][64];      // the plan of every lane, word by word
+};
+constexpr int tl_count(uint32_t v) {
+    int c = 0;
+    for (; v; v &= v - 1) ++c;
+    return c;
+}
+constexpr uint32_t tl_nth_subset(int size, int nth) {
+    for (uint32_t S = 1; S < 128; ++S)
+        if (tl_count(S) == size && nth-- == 0) return S;
+    return 0;
+}
+constexpr uint32_t tl_split(uint32_t S, int c) {
+    const uint32_t lb = S & (0u - S);
+    uint32_t rest = S ^ lb, P = lb;
+    for (int b = 0; rest; ++b) {
+        const uint32_t low = rest & (0u - rest);
+        if (c >> b & 1) P |= low;
+        rest ^= low;
+    }
+    return P | ((S ^ P) << 8);
+}
+constexpr TlTable tl_table() {
+    TlTable t{};
+    for (int lane = 0; lane < 64; ++lane) {
+        const uint32_t set[6] = {tl_nth_subset(2, lane), tl_nth_subset(3, lane), tl_nth_subset(4, lane),
+                                 tl_nth_subset(5, lane >> 1), tl_nth_subset(6, lane >> 3), lane < 63 ? 127u : 0u};
+        int w = 0;
+        for (int q = 0; q < 6; ++q) t.w[w++][lane] = set[q];
+        t.w[w++][lane] = tl_split(set[0], 0);
+        for (int q = 0; q < 3; ++q) t.w[w++][lane] = tl_split(set[1], 2 - q);
+        for (int q = 0; q < 7; ++q) t.w[w++][lane] = tl_split(set[2], 6 - q);
+        for (int q = 0; q < 8; ++q) t.w[w++][lane] = tl_split(set[3], 14 - 2 * q - (lane & 1) < 0 ? 0 : 14 - 2 * q - (lane & 1));
+        for (int q = 0; q < 4; ++q) t.w[w++][lane] = tl_split(set[4], 24 - 8 * q + (lane & 7) > 30 ? 30 : 24 - 8 * q + (lane & 7));
+        t.w[w++][lane] = tl_split(set[5], lane);
+    }
+    return t;
+}
+__constant__ const TlTable TL_TABLE = tl_table();
+__device__ __forceinline__ TlPlan tl_plan(int lane) {
+    uint32_t w[TL_PLAN_WORDS];
+#pragma unroll
+    for (int i = 0; i < TL_PLAN_WORDS; ++i) w[i] = TL_TABLE.w[i][lane];
+    return __builtin_bit_cast(TlPlan, w);
+}
+
+// value of lane + N / lane - N of the same 16 (DPP row shift)
+template <int N> __device__ __forceinline__ uint32_t lane_up(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x100 + N, 0xf, 0xf, true);
+}
+template <int N> __device__ __forceinline__ uint32_t lane_down(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x110 + N, 0xf, 0xf, true);
+}
+// value of the lane at xor 1, xor 2, and mirrored within 8
+__device__ __forceinline__ uint32_t lane_x1(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true); }
+__device__ __forceinline__ uint32_t lane_x2(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true); }
+__device__ __forceinline__ uint32_t lane_m8(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true); }
+__device__ __forceinline__ uint32_t pull(uint32_t v, int lane) { return (uint32_t)__shfl((int)v, lane, 64); }
+
+// (cost, P) of the better split: less cost, on ties the larger P (larger c: P and c
+// order alike within one subset)
+__device__ __forceinline__ void tl_better(float& c, uint32_t& P, float c2, uint32_t P2) {
+    if (c2 < c || (c2 == c && P2 > P)) { c = c2; P = P2; }
+}
+template <int N>
+__device__ __forceinline__ void tl_try(const TlLds& T, const uint32_t (&sp)[N], float& c, uint32_t& P) {
 #pragma clang fp contract(off)
-    auto bidx = [n](int code) -> size_t {
-        return (code & (int)LEAF_BIT) ? (size_t)(n - 1) + (code & 0x7FFFFFFF) : (size_t)code;
-    };
-    wave_sync_lds();
-    if (lane == 0) {
-        int ent[TL_LEAVES + 1], ids[TL_LEAVES];
-        float box[TL_LEAVES + 1][6], area[TL_LEAVES + 1];
-        int k = 2, ni = 1;
-        ids[0] = r;
-        for (int a = 0; a < 2; ++a) {
-            ent[a] = ald_i(child + 2 * r + a);
-            for (int q = 0; q < 6; ++q) box[a][q] = aload(aabb + 6 * bidx(ent[a]) + q);
-            area[a] = tl_area(box[a]);
+    c = T.opt[sp[0] & 255u] + T.opt[sp[0] >> 8];
+    P = sp[0] & 255u;
+#pragma unroll
+    for (int q = 1; q < N; ++q) {
+        const float x = T.opt[sp[q] & 255u] + T.opt[sp[q] >> 8];
+        if (x < c) { c = x; P = sp[q] & 255u; }     // in order of preference
+    }
+}
+
+// Restructures the treelet of root r (its record complete, everything below final);
+// returns the SAH cost of its new subtree.  Called by a whole wave.
+template <class Mem>
+__device__ __forceinline__ float treelet(const Mem& mem, int r, int lane, TlLds& T, const TlPlan& plan) {
+#pragma clang fp contract(off)
+    const int j = lane & 7, g = lane >> 3, base = lane & ~7;
+    // the list: entry g in lanes 8 g .. 8 g + 7, one word of its half each (e), and
+    // two words each of its own record (rx, ry) where it is internal
+    uint32_t e = 0, rx = 0, ry = 0;
+    if (g == 0) {
+        const uint64_t v = mem.load(r, j);
+        rx = (uint32_t)v;
+        ry = (uint32_t)(v >> 32);
+    }
+    int b = 0, id[6];
+    id[0] = r;
+#pragma unroll
+    for (int k = 0; k < TL_LEAVES - 1; ++k) {
+        // entry b of the k (the root at k = 0) leaves the list, the later ones move
+        // down, its children become entries k - 1 and k
+        const int nk = k == 0 ? 2 : k + 2, c0 = nk - 2;
+        const int from = g == c0 ? 8 * b + (j >> 1) : 8 * b + 4 + (j >> 1);
+        const uint32_t cx = pull(rx, from), cy = pull(ry, from);
+        const int mv = g >= b ? min(lane + 8, 63) : lane;
+        const uint32_t me = pull(e, mv), mx = pull(rx, mv), my = pull(ry, mv);
+        const bool fresh = g == c0 || g == c0 + 1;
+        e = fresh ? (j & 1 ? cy : cx) : me;
+        rx = mx;
+        ry = my;
+        if (k == TL_LEAVES - 2) break;
+        const uint32_t code = pull(e, base);
+        if (fresh && !(code & LEAF_BIT)) {
+            const uint64_t v = mem.load((int)code, j);
+            rx = (uint32_t)v;
+            ry = (uint32_t)(v >> 32);
         }
-        while (k < TL_LEAVES) {
-            int bi = -1;
-            float ba = -1.0f;
-            for (int i = 0; i < k; ++i)
-                if (!(ent[i] & (int)LEAF_BIT) && area[i] > ba) { ba = area[i]; bi = i; }
-            if (bi < 0) break;
-            const int c = ent[bi];
-            ids[ni++] = c;
-            for (int i = bi; i + 1 < k; ++i) {
-                ent[i] = ent[i + 1];
-                area[i] = area[i + 1];
-                for (int q = 0; q < 6; ++q) box[i][q] = box[i + 1][q];
-            }
-            k -= 1;
-            for (int a = 0; a < 2; ++a, ++k) {
-                ent[k] = ald_i(child + 2 * c + a);
-                for (int q = 0; q < 6; ++q) box[k][q] = aload(aabb + 6 * bidx(ent[k]) + q);
-                area[k] = tl_area(box[k]);
-            }
+        // the internal entry of largest area, first of the list on ties: box extents
+        // in lanes j = 1..3 of an entry, its area in lane j = 1
+        const float d = __uint_as_float(lane_up<3>(e)) - __uint_as_float(e);
+        const float ar = tl_area(d, __uint_as_float(lane_up<1>(__float_as_uint(d))), __uint_as_float(lane_up<2>(__float_as_uint(d))));
+        const uint32_t key = (lane_down<1>(e) & LEAF_BIT) ? 0u : ar >= 0.0f ? __float_as_uint(ar) + 1u : 1u;
+        uint32_t best = 0;
+#pragma unroll
+        for (int i = 0; i < nk; ++i) {
+            const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)key, 8 * i + 1);
+            if (a > best) { best = a; b = i; }
         }
-        T.k = k;
-        for (int i = 0; i < k; ++i) {
-            T.ent[i] = ent[i];
-            for (int q = 0; q < 6; ++q) T.box[i][q] = box[i][q];
-            T.cost[i] = (ent[i] & (int)LEAF_BIT) ? area[i] : aload(tcost + ent[i]);
-            T.leaves[i] = (ent[i] & (int)LEAF_BIT) ? 1 : ald_i(tleaves + ent[i]);
-        }
-        // the internal nodes other than r in ascending id order (insertion sort)
-        for (int i = 2; i < ni; ++i) {
-            const int v = ids[i];
-            int j = i - 1;
-            while (j >= 1 && ids[j] > v) { ids[j + 1] = ids[j]; --j; }
-            ids[j + 1] = v;
-        }
-        for (int i = 0; i < ni; ++i) T.ids[i] = ids[i];
+        id[k + 1] = __builtin_amdgcn_readlane((int)e, 8 * b);
     }
     wave_sync_lds();
-    const int k = T.k, full = (1 << k) - 1;
-    // union-box areas of this lane's subsets, singletons' costs
-    float sarea[2];
-    int sset[2];
-    for (int h = 0; h < 2; ++h) {
-        const int S = lane + 64 * h;
-        sset[h] = (S >= 1 && S <= full) ? S : 0;
-        float u[6] = {__int_as_float(0x7f800000), __int_as_float(0x7f800000), __int_as_float(0x7f800000),
-                      -__int_as_float(0x7f800000), -__int_as_float(0x7f800000), -__int_as_float(0x7f800000)};
-        for (int j = 0; j < k; ++j)
-            if (sset[h] >> j & 1)
-                for (int q = 0; q < 3; ++q) {
-                    u[q] = fminf(u[q], T.box[j][q]);
-                    u[3 + q] = fmaxf(u[3 + q], T.box[j][3 + q]);
-                }
-        sarea[h] = sset[h] ? tl_area(u) : 0.0f;
-        if (sset[h] && __popc(sset[h]) == 1) T.opt[sset[h]] = T.cost[__ffs(sset[h]) - 1];
-    }
+    if (lane < 8 * TL_LEAVES) T.ent[g][j] = e;
     wave_sync_lds();
-    for (int size = 2; size <= k; ++size) {
-        for (int h = 0; h < 2; ++h) {
-            const int S = sset[h];
-            if (!S || __popc(S) != size) continue;
-            const int lb = S & -S, rest = S ^ lb;
-            float best = __int_as_float(0x7f800000);
-            int bp = 0;
-            int sub = (rest - 1) & rest;
-            for (;;) {
-                const int P = lb | sub;
-                const float c = T.opt[P] + T.opt[S ^ P];
-                if (c < best) { best = c; bp = P; }
-                if (sub == 0) break;
-                sub = (sub - 1) & rest;
+    // the internal nodes other than r in ascending id order
+#pragma unroll
+    for (int i = 2; i < 6; ++i)
+#pragma unroll
+        for (int q = i; q > 1; --q) {
+            const int lo = min(id[q - 1], id[q]), hi = max(id[q - 1], id[q]);
+            id[q - 1] = lo;
+            id[q] = hi;
+        }
+    // boxes of the subsets lane (entries 0..5) and lane + 64 (with entry 6)
+    float lo[3] = {__int_as_float(0x7f800000), __int_as_float(0x7f800000), __int_as_float(0x7f800000)};
+    float hi[3] = {-__int_as_float(0x7f800000), -__int_as_float(0x7f800000), -__int_as_float(0x7f800000)};
+#pragma unroll
+    for (int i = 0; i < TL_LEAVES - 1; ++i)
+        if (lane >> i & 1)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                lo[q] = fminf(lo[q], __uint_as_float(T.ent[i][1 + q]));
+                hi[q] = fmaxf(hi[q], __uint_as_float(T.ent[i][4 + q]));
             }
-            T.opt[S] = TL_C_INNER * sarea[h] + best;
-            T.part[S] = bp;
+    T.area[lane] = tl_area(hi[0] - lo[0], hi[1] - lo[1], hi[2] - lo[2]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        lo[q] = fminf(lo[q], __uint_as_float(T.ent[TL_LEAVES - 1][1 + q]));
+        hi[q] = fmaxf(hi[q], __uint_as_float(T.ent[TL_LEAVES - 1][4 + q]));
+    }
+    T.area[lane + 64] = tl_area(hi[0] - lo[0], hi[1] - lo[1], hi[2] - lo[2]);
+    if (lane < TL_LEAVES) T.opt[1 << lane] = __uint_as_float(T.ent[lane][7]);
+    if (lane < 6) T.ids[lane] = (uint32_t)(lane == 0 ? id[0] : lane == 1 ? id[1] : lane == 2 ? id[2] : lane == 3 ? id[3] : lane == 4 ? id[4] : id[5]);
+    wave_sync_lds();
+    float ar[8];
+#pragma unroll
+    for (int s = 2; s < 8; ++s) ar[s] = T.area[plan.set[s - 2]];
+    float c;
+    uint32_t P;
+    auto settle = [&](int s, bool writes) {
+        if (writes && plan.set[s - 2]) {
+            T.opt[plan.set[s - 2]] = TL_C_INNER * ar[s] + c;
+            T.part[plan.set[s - 2]] = P;
         }
         wave_sync_lds();
+    };
+    tl_try(T, plan.s2, c, P);
+    settle(2, true);
+    tl_try(T, plan.s3, c, P);
+    settle(3, true);
+    tl_try(T, plan.s4, c, P);
+    settle(4, true);
+    tl_try(T, plan.s5, c, P);
+    tl_better(c, P, __uint_as_float(lane_x1(__float_as_uint(c))), lane_x1(P));
+    settle(5, (lane & 1) == 0);
+    tl_try(T, plan.s6, c, P);
+    tl_better(c, P, __uint_as_float(lane_x1(__float_as_uint(c))), lane_x1(P));
+    tl_better(c, P, __uint_as_float(lane_x2(__float_as_uint(c))), lane_x2(P));
+    tl_better(c, P, __uint_as_float(lane_m8(__float_as_uint(c))), lane_m8(P));
+    settle(6, j == 0);
+    tl_try(T, plan.s7, c, P);
+    if (!plan.set[5]) { c = __int_as_float(0x7f800000); P = 0; }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) tl_better(c, P, __uint_as_float(pull(__float_as_uint(c), lane ^ o)), pull(P, lane ^ o));
+    settle(7, lane == 0);
+    const float cost = T.opt[127];
+    // the new tree's internal nodes along its preorder: node i's first child, where
+    // internal, is node i + 1, its second node i + |first|
+    uint64_t pre = 127u;
+#pragma unroll
+    for (int i = 0; i < TL_LEAVES - 1; ++i) {
+        const uint32_t S = (uint32_t)(pre >> (8 * i)) & 255u;
+        const uint32_t A = (uint32_t)__builtin_amdgcn_readfirstlane((int)T.part[S]), Q = S ^ A;
+        if (A & (A - 1)) pre |= (uint64_t)A << (8 * (i + 1));
+        if (Q & (Q - 1)) pre |= (uint64_t)Q << (8 * (i + __popc(A)));
     }
-    if (lane == 0) {
-        // preorder of the optimal tree's internal subsets
-        int pre[TL_LEAVES], st[TL_LEAVES + 1];
-        int np = 0, sp = 0;
-        st[sp++] = full;
-        while (sp > 0) {
-            const int S = st[--sp];
-            pre[np++] = S;
-            const int P = T.part[S], Q = S ^ P;
-            if (__popc(Q) > 1) st[sp++] = Q;
-            if (__popc(P) > 1) st[sp++] = P;
+    // their records: node g, words 2 j and 2 j + 1
+    if (g < TL_LEAVES - 1) {
+        const uint32_t S = (uint32_t)(pre >> (8 * g)) & 255u, A = T.part[S];
+        const uint32_t X = j < 4 ? A : S ^ A;
+        const int w = 2 * (j & 3);
+        uint32_t x, y;
+        if (!(X & (X - 1))) {
+            const int i = __ffs(X) - 1;
+            x = T.ent[i][w];
+            y = T.ent[i][w + 1];
+        } else {
+            float u = w < 4 ? __int_as_float(0x7f800000) : -__int_as_float(0x7f800000), v = w < 3 ? __int_as_float(0x7f800000) : -__int_as_float(0x7f800000);
+#pragma unroll
+            for (int i = 0; i < TL_LEAVES; ++i)
+                if (X >> i & 1) {
+                    const float p = __uint_as_float(T.ent[i][w]), q = __uint_as_float(T.ent[i][w + 1]);
+                    u = w < 4 ? fminf(u, p) : fmaxf(u, p);
+                    v = w < 3 ? fminf(v, q) : fmaxf(v, q);
+                }
+            x = w == 0 ? T.ids[j < 4 ? g + 1 : g + __popc(A)] : __float_as_uint(u);
+            y = w == 6 ? __float_as_uint(T.opt[X]) : __float_as_uint(v);
         }
-        auto code_of = [&](int X) -> int {
-            if (__popc(X) == 1) return T.ent[__ffs(X) - 1];
-            for (int i = 0; i < np; ++i)
-                if (pre[i] == X) return T.ids[i];
-            return -1;
-        };
-        for (int i = 0; i < np; ++i) {
-            const int S = pre[i], id = T.ids[i], P = T.part[S], Q = S ^ P;
-            const int a = code_of(P), c = code_of(Q);
-            ast_i(child + 2 * id, a);
-            ast_i(child + 2 * id + 1, c);
-            ast_i(parent + bidx(a), id);
-            ast_i(parent + bidx(c), id);
-            ast_f(tcost + id, T.opt[S]);
-            int cnt = 0;
-            for (int j = 0; j < k; ++j)
-                if (S >> j & 1) cnt += T.leaves[j];
-            ast_i(tleaves + id, cnt);
-            float u[6] = {__int_as_float(0x7f800000), __int_as_float(0x7f800000), __int_as_float(0x7f800000),
-                          -__int_as_float(0x7f800000), -__int_as_float(0x7f800000), -__int_as_float(0x7f800000)};
-            for (int j = 0; j < k; ++j)
-                if (S >> j & 1)
-                    for (int q = 0; q < 3; ++q) {
-                        u[q] = fminf(u[q], T.box[j][q]);
-                        u[3 + q] = fmaxf(u[3 + q], T.box[j][3 + q]);
-                    }
-            for (int q = 0; q < 6; ++q) ast_f(aabb + 6 * (size_t)id + q, u[q]);
-        }
+        mem.store((int)T.ids[g], j, (uint64_t)x | (uint64_t)y << 32);
     }
+    wave_sync_lds();
+    return cost;
 }
 
-// triangle count and SAH cost of a code (leaf: 1 and its box area)
-__device__ __forceinline__ void code_stats(int code, const float* aabb, const float* tcost, const int* tleaves, int n,
-                                           int& leaves, float& cost) {
-    if (code & (int)LEAF_BIT) {
-        float b[6];
-        for (int q = 0; q < 6; ++q) b[q] = aload(aabb + 6 * ((size_t)(n - 1) + (code & 0x7FFFFFFF)) + q);
-        leaves = 1;
-        cost = tl_area(b);
-    } else {
-        leaves = ald_i(tleaves + code);
-        cost = aload(tcost + code);
-    }
-}
-
-__global__ __launch_bounds__(TL_BLOCK) void k_treelet(int* child, int* parent, float* aabb, float* tcost,
-                                                      int* tleaves, int* cnt, int n, uint32_t* err) {
+// One wave's share of the bottom-up pass in one kind of memory.  h: the finished
+// subtree a lane brings, up: its parent and side; lanes with on false have none.
+// count(node) adds an arrival and returns those before; inside(node): whether this
+// pass builds that node.  A lane whose subtree's parent is not inside keeps it and
+// leaves the pass (on stays true).
+template <class Mem, class Inside, class Count>
+__device__ __forceinline__ void tl_climb(const Mem& mem, TlHalf& h, int& up, bool& on, int lane,
+                                         const int* __restrict__ kup, const int2* __restrict__ range, TlLds& T,
+                                         const TlPlan& plan, uint32_t* err, Inside inside, Count count) {
 #pragma clang fp contract(off)
-    __shared__ TreeletLds lds[TL_WAVES];
-    const int lane = threadIdx.x & 63;
-    TreeletLds& T = lds[threadIdx.x >> 6];
-    const int leaf = blockIdx.x * blockDim.x + threadIdx.x;
-    bool active = leaf < n;
-    int node = active ? parent[(n - 1) + leaf] : -1;
-    if (node < 0) active = false;
-    int guard = 0;
-    for (; guard < TL_GUARD; ++guard) {
-        bool own = false, big = false;
+    bool active = on && up >= 0 && inside(up >> 1);
+    for (int guard = 0; __ballot(active); ++guard) {
+        if (guard == TL_GUARD) { atomicOr(err, ERR_LOOP); return; }
+        const int node = up >> 1;
+        bool own = false;
         if (active) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) mem.store(node, 4 * (up & 1) + q, (uint64_t)h.w[2 * q] | (uint64_t)h.w[2 * q + 1] << 32);
             handoff_release();
-            if (atomicAdd(&cnt[node], 1) == 0) active = false;    // the other subtree is not done yet
-            else own = true;
+            own = count(node) != 0;                     // else the other subtree is not done yet
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            if (!own) active = on = false;
         }
+        bool big = false;
         if (own) {
-            int l0, l1;
-            float k0, k1;
-            code_stats(ald_i(child + 2 * node), aabb, tcost, tleaves, n, l0, k0);
-            code_stats(ald_i(child + 2 * node + 1), aabb, tcost, tleaves, n, l1, k1);
-            big = l0 + l1 >= TL_LEAVES;
-            if (!big) {
-                float b[6];
-                for (int q = 0; q < 6; ++q) b[q] = aload(aabb + 6 * (size_t)node + q);
-                ast_i(tleaves + node, l0 + l1);
-                ast_f(tcost + node, TL_C_INNER * tl_area(b) + (k0 + k1));
+            uint32_t o[8];                              // the other child's half
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint64_t v = mem.load(node, 4 * (~up & 1) + q);
+                o[2 * q] = (uint32_t)v;
+                o[2 * q + 1] = (uint32_t)(v >> 32);
             }
+            const float k0 = __uint_as_float(up & 1 ? o[7] : h.w[7]), k1 = __uint_as_float(up & 1 ? h.w[7] : o[7]);
+            float lo[3], hi[3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                lo[q] = fminf(__uint_as_float(h.w[1 + q]), __uint_as_float(o[1 + q]));
+                hi[q] = fmaxf(__uint_as_float(h.w[4 + q]), __uint_as_float(o[4 + q]));
+                h.w[1 + q] = __float_as_uint(lo[q]);
+                h.w[4 + q] = __float_as_uint(hi[q]);
+            }
+            const int2 rg = range[node];
+            big = rg.y - rg.x + 1 >= TL_LEAVES;
+            h.w[0] = (uint32_t)node;
+            h.w[7] = __float_as_uint(TL_C_INNER * tl_area(hi[0] - lo[0], hi[1] - lo[1], hi[2] - lo[2]) + (k0 + k1));
+            up = kup[node];
+            active = up >= 0 && inside(up >> 1);
         }
-        uint64_t m = __ballot(big);
-        while (m) {
+        for (uint64_t m = __ballot(big); m; m &= m - 1) {
             const int src = __ffsll((unsigned long long)m) - 1;
-            m &= m - 1;
-            treelet_restructure(__builtin_amdgcn_readlane(node, src), lane, T, child, parent, aabb, tcost, tleaves, n);
+            const float c = treelet(mem, __builtin_amdgcn_readlane((int)h.w[0], src), lane, T, plan);
+            if (lane == src) h.w[7] = __float_as_uint(c);
         }
-        if (own) {
-            const int p = ald_i(parent + node);
-            if (p < 0) active = false;
-            else node = p;
-        }
-        if (__ballot(active) == 0) break;
     }
-    if (guard == TL_GUARD && active) atomicOr(err, ERR_LOOP);
+}
+
+__global__ __launch_bounds__(TL_BLOCK) void k_treelets(const int* __restrict__ kup, const int2* __restrict__ range,
+                                                       const uint32_t* __restrict__ sface, const float4* __restrict__ bmin,
+                                                       const float4* __restrict__ bmax, int n, uint32_t* rec, int* cnt,
+                                                       uint32_t* err) {
+    __shared__ uint64_t recs[8 * TL_SPAN];
+    __shared__ int cnts[TL_SPAN];
+    __shared__ TlLds lds[TL_WAVES];
+    const int lane = threadIdx.x & 63, w = (int)(threadIdx.x >> 6);
+    TlLds& T = lds[w];
+    const int lo = blockIdx.x * TL_SPAN, hi = min(n, lo + TL_SPAN) - 1;
+    for (int i = threadIdx.x; i < TL_SPAN; i += TL_BLOCK) cnts[i] = 0;
+    const TlPlan plan = tl_plan(lane);
+    const int leaf = lo + w * TL_PER_WAVE + lane;
+    bool on = lane < TL_PER_WAVE && leaf <= hi;
+    TlHalf h;
+    int up = -1;
+    if (on) {
+        const int f = (int)sface[leaf];
+        const float4 a = bmin[f], b = bmax[f];
+        h.w[0] = LEAF_BIT | (uint32_t)leaf;
+        h.w[1] = __float_as_uint(a.x); h.w[2] = __float_as_uint(a.y); h.w[3] = __float_as_uint(a.z);
+        h.w[4] = __float_as_uint(b.x); h.w[5] = __float_as_uint(b.y); h.w[6] = __float_as_uint(b.z);
+        h.w[7] = __float_as_uint(tl_area(b.x - a.x, b.y - a.y, b.z - a.z));
+        up = kup[(n - 1) + leaf];
+    }
+    __syncthreads();
+    auto local = [&](int node) {
+        const int2 rg = range[node];
+        return rg.x >= lo && rg.y <= hi;
+    };
+    const TlLocal lmem{recs, lo};
+    tl_climb(lmem, h, up, on, lane, kup, range, T, plan, err, local, [&](int node) { return atomicAdd(&cnts[node - lo], 1); });
+    __syncthreads();
+    // the block's records, for the treelets above and the passes after
+    const TlGlobal gmem{(uint64_t*)rec};
+    for (int i = threadIdx.x; i < 8 * (hi - lo + 1); i += TL_BLOCK) {
+        const int node = lo + (i >> 3);
+        if (node < n - 1 && local(node)) gmem.store(node, i & 7, recs[i]);
+    }
+    handoff_release();
+    __syncthreads();
+    tl_climb(gmem, h, up, on, lane, kup, range, T, plan, err, [](int) { return true; }, [&](int node) { return atomicAdd(&cnt[node], 1); });
+}
+
+// the tree of the records as arrays: children, parents, boxes (internal nodes, then
+// leaves); clears the arrival counters for the next pass
+__global__ void k_tree_unpack(const uint32_t* __restrict__ rec, int n, int* child, int* parent, float* aabb, int* cnt) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n - 1) return;
+    const uint32_t* const r = rec + 16 * (size_t)i;
+    cnt[i] = 0;
+    for (int s = 0; s < 2; ++s) {
+        const int c = (int)r[8 * s];
+        const size_t k = (c & (int)LEAF_BIT) ? (size_t)(n - 1) + (c & 0x7FFFFFFF) : (size_t)c;
+        child[2 * i + s] = c;
+        parent[k] = i;
+        for (int q = 0; q < 6; ++q) aabb[6 * k + q] = __uint_as_float(r[8 * s + 1 + q]);
+    }
+    if (i == 0) {
+        parent[0] = -1;
+        for (int q = 0; q < 3; ++q) {
+            aabb[q] = fminf(__uint_as_float(r[1 + q]), __uint_as_float(r[9 + q]));
+            aabb[3 + q] = fmaxf(__uint_as_float(r[4 + q]), __uint_as_float(r[12 + q]));
+        }
+    }
 }
 
 // Collapse of the binary tree into 4-wide nodes with the least summed box area
@@ -555,9 +731,9 @@ __global__ void k_collapse_cost(const int* __restrict__ parent, const int* __res
     if (i >= n) return;
     int node = parent[(n - 1) + i];
     for (int depth = 0; node >= 0 && depth < 128; ++depth) {
-        __threadfence();
+        handoff_release();
         if (atomicAdd(&cnt[node], 1) == 0) return;    // the other child is not done yet
-        __threadfence();
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
         float D[2][5];
         for (int j = 0; j < 2; ++j) {
             const int c = child[2 * node + j];
@@ -971,9 +1147,9 @@ __global__ void k_erefit(const int* __restrict__ parent, const int* __restrict__
     if (i >= n) return;
     int node = parent[(n - 1) + i];
     for (int depth = 0; node >= 0 && depth < 4096; ++depth) {
-        __threadfence();
+        handoff_release();
         if (atomicAdd(&cnt[node], 1) == 0) return;
-        __threadfence();
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
         const int c0 = child[2 * node], c1 = child[2 * node + 1];
         const size_t i0 = (c0 & (int)LEAF_BIT) ? (size_t)(n - 1) + (c0 & 0x7FFFFFFF) : (size_t)c0;
         const size_t i1 = (c1 & (int)LEAF_BIT) ? (size_t)(n - 1) + (c1 & 0x7FFFFFFF) : (size_t)c1;
@@ -1076,20 +1252,13 @@ void launch_scene_geometry(SceneDev& s, hipStream_t st) {
     // after 4 passes the sorted data is back in buffer 0
     const uint32_t* sm = s.mkeys[cur];
     const uint32_t* sf = s.mvals[cur];
-    ST_LAUNCH("k_keys64", k_keys64, dim3(nb(nf, 256)), dim3(256), 0, st, sm, sf, nf, s.keys64);
-    if (nf > 1)
-        ST_LAUNCH("k_karras", k_karras, dim3(nb(nf - 1, 256)), dim3(256), 0, st, sm, sf, nf, s.child, s.parent);
-    ST_LAUNCH("k_leaf_init", k_leaf_init, dim3(nb(nf, 256)), dim3(256), 0, st, sf, s.bmin, s.bmax, s.V, s.F, nf, s.aabb,
-                       s.tri, s.fleaf, s.refit_cnt);
+    ST_LAUNCH("k_tree_init", k_tree_init, dim3(nb(nf, 256)), dim3(256), 0, st, sm, sf, nf, s.kup, s.krange, s.keys64,
+              s.refit_cnt, s.bmin, s.bmax, s.V, s.F, s.aabb, s.tri, s.fleaf);
     if (nf > 1) {
-        ST_LAUNCH("k_refit", k_refit, dim3(nb(nf, 256)), dim3(256), 0, st, s.parent, s.child, nf, s.aabb,
-                           s.refit_cnt);
-        for (int rd = 0; rd < TREELET_ROUNDS; ++rd) {
-            launch_fill_u32((uint32_t*)s.refit_cnt, nf - 1, 0u, st);
-            ST_LAUNCH("k_treelet", k_treelet, dim3(nb(nf, TL_BLOCK)), dim3(TL_BLOCK), 0, st, s.child, s.parent, s.aabb,
-                      s.tcost, s.tleaves, s.refit_cnt, nf, s.err);
-        }
-        launch_fill_u32((uint32_t*)s.refit_cnt, nf - 1, 0u, st);
+        ST_LAUNCH("k_treelets", k_treelets, dim3(nb(nf, TL_SPAN)), dim3(TL_BLOCK), 0, st, s.kup, s.krange, sf, s.bmin,
+                  s.bmax, nf, s.trec, s.refit_cnt, s.err);
+        ST_LAUNCH("k_tree_unpack", k_tree_unpack, dim3(nb(nf - 1, 256)), dim3(256), 0, st, s.trec, nf, s.child, s.parent,
+                  s.aabb, s.refit_cnt);
         ST_LAUNCH("k_collapse_cost", k_collapse_cost, dim3(nb(nf, 256)), dim3(256), 0, st, s.parent, s.child, s.aabb,
                   nf, s.refit_cnt, (float*)s.ccost, s.cdec);
         ST_LAUNCH("k_collapse_flag", k_collapse_flag, dim3(nb(nf - 1, 256)), dim3(256), 0, st, s.parent, s.child,

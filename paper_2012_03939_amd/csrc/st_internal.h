@@ -22,8 +22,6 @@ extern bool g_prof_on;
 
 // every device allocation of one scene (library-owned)
 constexpr int PACK_TILE = 1024;     // binary nodes per block of the 4-wide packing's scan
-constexpr int TREELET_ROUNDS = 1;   // bottom-up treelet-restructuring passes over the Karras tree (a second one
-                                    // bought no measurable traversal time for its 1.9 ms)
 constexpr int FACC = 16;   // gradient slots of one vertex: 3 corners x xyz, then the 7 material parameters
 // Gradient accumulators are face-major, so that the slots one shading point adds
 // to share a cache line: face f owns facc[16 f .. 16 f + 15] (corners in 0..8;
@@ -58,7 +56,9 @@ struct SceneDev {
     int* parent = nullptr;                   // [2*nf-1]
     float* aabb = nullptr;                   // [(2*nf-1)*6]
     int* refit_cnt = nullptr;
-    float* tcost = nullptr;                  // [nf-1] SAH cost of every internal node's subtree
+    int* kup = nullptr;                      // [2*nf-1] radix tree: (parent << 1) | side, -1 at the root
+    int2* krange = nullptr;                  // [nf-1] radix tree: first and last leaf below a node
+    uint32_t* trec = nullptr;                // [16 (nf-1)] node records of the treelet pass
     // secondary-edge importance tree (built on demand): radix tree over the edge
     // boxes with per-node length sums; sorted leaf -> edge in evals_sorted
     float4 *ebmin = nullptr, *ebmax = nullptr, *ecen = nullptr;
@@ -71,7 +71,6 @@ struct SceneDev {
     float *eaabb = nullptr, *elen = nullptr, *enbox = nullptr;
     float4* enode = nullptr;                 // packed internal nodes of the edge tree (8 float4 each)
     const uint32_t* eleaf_edge = nullptr;    // points into emkeys/emvals after the sort
-    int* tleaves = nullptr;                  // [nf-1] triangles below every internal node
     float4* nodes4 = nullptr;                // [(nf-1)*8] 4-wide nodes (at most nf-1 of them)
     int* flag4 = nullptr;                    // [nf-1] binary node starts a 4-wide node
     uint2* slots4 = nullptr;                 // [nf-1] internal and leaf slots of each such node, then what precedes it
