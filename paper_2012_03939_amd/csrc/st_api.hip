@@ -638,7 +638,7 @@ int st_scene_create(const float* V, int32_t nv, const int32_t* F, int32_t nf, co
     A(dalloc(&d.V, 3 * (size_t)nv)); A(dalloc(&d.F, 3 * (size_t)nf)); A(dalloc(&d.mat, 7 * (size_t)nf));
     A(dalloc(&d.lights, 6 * (size_t)std::max(nl, 1)));
     A(dalloc(&d.fnorm, nf)); A(dalloc(&d.bmin, nf)); A(dalloc(&d.bmax, nf)); A(dalloc(&d.cen, nf));
-    A(dalloc(&d.bounds, 16));
+    A(dalloc(&d.bounds, 6 * (size_t)((nf + 1023) / 1024)));
     for (int b = 0; b < 2; ++b) { A(dalloc(&d.mkeys[b], nf)); A(dalloc(&d.mvals[b], nf)); }
     A(dalloc(&d.rs_hist, 256 * (size_t)((nf + 1023) / 1024)));
     A(dalloc(&d.keys64, nf));
@@ -664,6 +664,7 @@ int st_scene_create(const float* V, int32_t nv, const int32_t* F, int32_t nf, co
     A(dalloc(&d.macc, MACC_STRIDE));     // per-texel material slots exist only with mesh colours
     A(dalloc(&d.edges, edges.size()));
     A(dalloc(&d.edge_w, edges.size()));
+    A(dalloc(&d.edge_tiles, (size_t)cdf_tiles((int)edges.size())));
     A(dalloc(&d.eguide, (size_t)1 << guide_log2((int)edges.size())));
     A(dalloc(&d.ecdf, edges.size() + 1));
     A(dalloc(&d.etotal_d, 1));
@@ -879,7 +880,7 @@ static int ensure_edge_tree(st_scene* sc, hipStream_t s) {
         const size_t n = (size_t)d.ne;
         int rc = 0;
         auto A = [&](int r) { if (r && !rc) rc = r; };
-        A(dalloc(&d.ebmin, n)); A(dalloc(&d.ebmax, n)); A(dalloc(&d.ecen, n)); A(dalloc(&d.ebounds, 16));
+        A(dalloc(&d.ebmin, n)); A(dalloc(&d.ebmax, n)); A(dalloc(&d.ecen, n)); A(dalloc(&d.ebounds, 6 * ((n + 1023) / 1024)));
         for (int b = 0; b < 2; ++b) { A(dalloc(&d.emkeys[b], n)); A(dalloc(&d.emvals[b], n)); }
         A(dalloc(&d.ers_hist, 256 * ((n + 1023) / 1024)));
         A(dalloc(&d.ekeys64, n));
@@ -1082,7 +1083,8 @@ int st_render_backward(st_scene* sc, const st_camera* cams, int32_t ncam, int32_
     const size_t pbytes = sizeof(double) * ((size_t)ncam * ne + (size_t)ncam * (ne + 1) + ncam) +
                           sizeof(int) * ((size_t)ncam << pglog) + sizeof(double) * 2 * (size_t)ncam * ne +
                           sizeof(double) * ((size_t)nls * ne + (size_t)nls * (ne + 1) + nls) +
-                          sizeof(int) * ((size_t)nls << pglog) + 9 * 256;
+                          sizeof(int) * ((size_t)nls << pglog) +
+                          sizeof(double) * (size_t)(ncam + nls) * cdf_tiles(ne) + 11 * 256;
     // workspace of the call, checked against the caller's cap before any kernel:
     // spill stack, edge tables, deferred secondary-edge jobs and, for the primary
     // edges, the side paths' radiance (and hashes) and their wavefront queues
@@ -1140,12 +1142,14 @@ int st_render_backward(st_scene* sc, const st_camera* cams, int32_t ncam, int32_
     p.fast = !p.work && sc->d.nf <= TRAV_FAST_FACES ? 1 : 0;
     p.spill = (uint32_t*)sc->spillbuf.p;
     p.pw = c.take<double>((size_t)ncam * ne);
+    p.ptiles = c.take<double>((size_t)ncam * cdf_tiles(ne));
     p.pcdf = c.take<double>((size_t)ncam * (ne + 1));
     p.ptotal = c.take<double>(ncam);
     p.pguide = c.take<int>((size_t)ncam << pglog);
     p.pglog = pglog;
     p.pacc = c.take<double>(2 * (size_t)ncam * ne);
     p.lw = c.take<double>((size_t)nls * ne);
+    p.ltiles = c.take<double>((size_t)nls * cdf_tiles(ne));
     p.lcdf = c.take<double>((size_t)nls * (ne + 1));
     p.ltotal = c.take<double>(nls);
     p.lguide = c.take<int>((size_t)nls << pglog);
@@ -1460,7 +1464,7 @@ void st_scene_destroy(st_scene* sc) {
     void* ptrs[] = {d.V, d.F, d.mat, d.lights, d.env, d.fnorm, d.bmin, d.bmax, d.cen, d.bounds, d.mkeys[0], d.mkeys[1],
                     d.mvals[0], d.mvals[1], d.rs_hist, d.keys64, d.child, d.parent, d.aabb, d.refit_cnt, d.kup, d.krange, d.trec, d.ebmin, d.ebmax, d.ecen, d.ebounds, d.emkeys[0], d.emkeys[1],
                     d.emvals[0], d.emvals[1], d.ers_hist, d.ekeys64, d.echild, d.eparent, d.ecnt, d.eaabb, d.elen, d.enbox, d.enode, d.nodes4, d.flag4, d.slots4, d.tiles4, d.ccost, d.cdec,
-                    d.tri, d.fleaf, d.edges, d.edge_w, d.eguide, d.mguide, d.cguide, d.ecdf, d.etotal_d, d.etotal_f, d.row_dom, d.rowcos, d.cond, d.marg,
+                    d.tri, d.fleaf, d.edges, d.edge_w, d.edge_tiles, d.eguide, d.mguide, d.cguide, d.ecdf, d.etotal_d, d.etotal_f, d.row_dom, d.rowcos, d.cond, d.marg,
                     d.env_rows, d.env_total, d.texpdf, d.err, d.work, d.dscene, d.vf_off, d.vf_idx, d.facc, d.macc, d.fe,
                     d.ealias, d.rec_key};
     for (void* p : ptrs)

@@ -603,13 +603,16 @@ __device__ __forceinline__ bool screen_edge(const DevCam& c, const DevScene& S, 
     return true;
 }
 
-__global__ void k_prim_weights(BwdParams p) {
+__global__ void __launch_bounds__(CDF_BLOCK) k_prim_weights(BwdParams p) {
 #pragma clang fp contract(off)
     const int v = blockIdx.y;
     const DevCam& c = p.cams[v];
     const DevScene& S = p.scenes[c.scene];
     const int ne = S.ne;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < ne; e += gridDim.x * blockDim.x) {
+    double sum = 0.0;
+    for (int q = 0; q < CDF_PER; ++q) {
+        const int e = blockIdx.x * CDF_TILE + threadIdx.x * CDF_PER + q;
+        if (e >= ne) break;
         const int4 E = S.edges[e];
         double lenv = 0.0;
         const bool cand = E.w < 0 || front_facing_d(S, E.z, c) || front_facing_d(S, E.w, c);
@@ -619,13 +622,15 @@ __global__ void k_prim_weights(BwdParams p) {
             lenv = (se.t1 - se.t0) * sqrt(dx * dx + dy * dy);
         }
         p.pw[(size_t)v * p.ne + e] = lenv;
+        sum += lenv;
     }
+    cdf_tile_sum(sum, p.ptiles + (size_t)v * cdf_tiles(p.ne));
 }
 
-__global__ void k_prim_cdf(BwdParams p) {
-    const int v = blockIdx.x;
-    const DevScene& S = p.scenes[p.cams[v].scene];
-    block_scan_normalise(p.pw + (size_t)v * p.ne, S.ne, p.pcdf + (size_t)v * (p.ne + 1), p.ptotal + v);
+__global__ void __launch_bounds__(CDF_BLOCK) k_prim_cdf(BwdParams p) {
+    const int v = blockIdx.y;
+    cdf_tile_write(p.pw + (size_t)v * p.ne, p.ne, p.ptiles + (size_t)v * cdf_tiles(p.ne), p.pcdf + (size_t)v * (p.ne + 1),
+                   p.ptotal + v);
 }
 
 // ---------------------------------------------------------------------------
@@ -888,12 +893,15 @@ __global__ void k_face_gather(BwdParams p) {
 // d_image(s) . (V- - V+) L_l(z) (n . ds/dtheta) |tau| W_l / (|vb - va| N_s)
 // for theta = the edge's endpoints and the receiver face's vertices.
 // ---------------------------------------------------------------------------
-__global__ void k_light_weights(BwdParams p) {
+__global__ void __launch_bounds__(CDF_BLOCK) k_light_weights(BwdParams p) {
 #pragma clang fp contract(off)
     const int l = blockIdx.y;
     const DevScene& S = p.scenes[0];
     const V3 pl = ld3(S.lights + 6 * l);
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < S.ne; e += gridDim.x * blockDim.x) {
+    double sum = 0.0;
+    for (int q = 0; q < CDF_PER; ++q) {
+        const int e = blockIdx.x * CDF_TILE + threadIdx.x * CDF_PER + q;
+        if (e >= S.ne) break;
         const int4 E = S.edges[e];
         double w = 0.0;
         if (silhouette(S, E, pl)) {
@@ -903,12 +911,15 @@ __global__ void k_light_weights(BwdParams p) {
             w = sqrt(dx * dx + dy * dy + dz * dz);
         }
         p.lw[(size_t)l * p.ne + e] = w;
+        sum += w;
     }
+    cdf_tile_sum(sum, p.ltiles + (size_t)l * cdf_tiles(p.ne));
 }
 
-__global__ void k_light_cdf(BwdParams p) {
-    const int l = blockIdx.x;
-    block_scan_normalise(p.lw + (size_t)l * p.ne, p.ne, p.lcdf + (size_t)l * (p.ne + 1), p.ltotal + l);
+__global__ void __launch_bounds__(CDF_BLOCK) k_light_cdf(BwdParams p) {
+    const int l = blockIdx.y;
+    cdf_tile_write(p.lw + (size_t)l * p.ne, p.ne, p.ltiles + (size_t)l * cdf_tiles(p.ne), p.lcdf + (size_t)l * (p.ne + 1),
+                   p.ltotal + l);
 }
 
 // screen point of z and its Jacobian rows (d sx/dz, d sy/dz) for camera c
@@ -1088,8 +1099,9 @@ static inline unsigned gridb(long long n, int bs, int cap) {
 void launch_primary_edges(const BwdParams& p, const FwdParams& fp, Queues& q, float* Lside, uint32_t* hside,
                           long long total_edges, int has_env_any, hipStream_t st, LaunchHook* hook) {
     if (total_edges <= 0 || p.ne <= 0) return;
-    ST_LAUNCH("k_prim_weights", k_prim_weights, dim3(gridb(p.ne, 256, 1024), p.ncam), dim3(256), 0, st, p);
-    ST_LAUNCH("k_prim_cdf", k_prim_cdf, dim3(p.ncam), dim3(1024), 0, st, p);
+    const dim3 tiles((unsigned)cdf_tiles(p.ne), p.ncam);
+    ST_LAUNCH("k_prim_weights", k_prim_weights, tiles, dim3(CDF_BLOCK), 0, st, p);
+    ST_LAUNCH("k_prim_cdf", k_prim_cdf, tiles, dim3(CDF_BLOCK), 0, st, p);
     launch_guide(p.pcdf, p.ne, (size_t)(p.ne + 1), p.ncam, p.pguide, p.pglog, st);
     const long long per = q.cap / 2;
     for (long long e0 = 0; e0 < total_edges; e0 += per) {
@@ -1253,8 +1265,9 @@ void launch_face_gather(const BwdParams& p, int nv, hipStream_t st) {
 
 void launch_shadow_edges(const BwdParams& p, long long total_edges, int nl, hipStream_t st) {
     if (total_edges <= 0 || p.ne <= 0 || nl <= 0) return;
-    ST_LAUNCH("k_light_weights", k_light_weights, dim3(gridb(p.ne, 256, 1024), nl), dim3(256), 0, st, p);
-    ST_LAUNCH("k_light_cdf", k_light_cdf, dim3(nl), dim3(1024), 0, st, p);
+    const dim3 tiles((unsigned)cdf_tiles(p.ne), nl);
+    ST_LAUNCH("k_light_weights", k_light_weights, tiles, dim3(CDF_BLOCK), 0, st, p);
+    ST_LAUNCH("k_light_cdf", k_light_cdf, tiles, dim3(CDF_BLOCK), 0, st, p);
     launch_guide(p.lcdf, p.ne, (size_t)(p.ne + 1), nl, p.lguide, p.pglog, st);
     const long long nsh = total_edges * nl;
     const auto edges = p.fast ? k_shadow_edges<true> : k_shadow_edges<false>;

@@ -14,55 +14,63 @@
 namespace st {
 
 // ---------------------------------------------------------------------------
-__global__ void k_face_prep(const float* __restrict__ V, const int* __restrict__ F, int nf, float4* fnorm,
-                            float4* bmin, float4* bmax, float4* cen) {
-#pragma clang fp contract(off)
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= nf) return;
-    const V3 a = ld3(V + 3 * F[3 * f]), b = ld3(V + 3 * F[3 * f + 1]), c = ld3(V + 3 * F[3 * f + 2]);
-    const V3 N = cross(b - a, c - a);
-    const float l = len(N);
-    const V3 n = l > 0.0f ? N * (1.0f / l) : V3{0.f, 0.f, 0.f};
-    fnorm[f] = make_float4(n.x, n.y, n.z, 0.5f * l);
-    const V3 mn{fminf(a.x, fminf(b.x, c.x)), fminf(a.y, fminf(b.y, c.y)), fminf(a.z, fminf(b.z, c.z))};
-    const V3 mx{fmaxf(a.x, fmaxf(b.x, c.x)), fmaxf(a.y, fmaxf(b.y, c.y)), fmaxf(a.z, fmaxf(b.z, c.z))};
-    bmin[f] = make_float4(mn.x, mn.y, mn.z, 0.f);
-    bmax[f] = make_float4(mx.x, mx.y, mx.z, 0.f);
-    const float cx = mn.x + mx.x, cy = mn.y + mx.y, cz = mn.z + mx.z;
-    cen[f] = make_float4(cx * 0.5f, cy * 0.5f, cz * 0.5f, 0.f);
+// Centroid bounds in two steps: each block of BND_TILE centroids leaves its own, and
+// the blocks of k_morton reduce those of all blocks again (one block over all the
+// centroids took 16 us at 40,000).
+constexpr int BND_TILE = 1024, BND_BLOCK = 256;
+struct Bounds {
+    float lo[3], hi[3];
+};
+__device__ __forceinline__ Bounds bounds_none() {
+    const float INF = __int_as_float(0x7f800000);
+    return Bounds{{INF, INF, INF}, {-INF, -INF, -INF}};
+}
+// of the block's threads, in every thread
+__device__ __forceinline__ Bounds block_bounds(Bounds b) {
+    __shared__ Bounds lds[BND_BLOCK / 64];
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1)
+        for (int k = 0; k < 3; ++k) {
+            b.lo[k] = fminf(b.lo[k], __shfl_xor(b.lo[k], o, 64));
+            b.hi[k] = fmaxf(b.hi[k], __shfl_xor(b.hi[k], o, 64));
+        }
+    if (__lane_id() == 0) lds[threadIdx.x >> 6] = b;
+    __syncthreads();
+    for (int w = 0; w < BND_BLOCK / 64; ++w)
+        for (int k = 0; k < 3; ++k) {
+            b.lo[k] = fminf(b.lo[k], lds[w].lo[k]);
+            b.hi[k] = fmaxf(b.hi[k], lds[w].hi[k]);
+        }
+    return b;
+}
+__device__ __forceinline__ void bounds_add(Bounds& b, float x, float y, float z) {
+    b.lo[0] = fminf(b.lo[0], x); b.lo[1] = fminf(b.lo[1], y); b.lo[2] = fminf(b.lo[2], z);
+    b.hi[0] = fmaxf(b.hi[0], x); b.hi[1] = fmaxf(b.hi[1], y); b.hi[2] = fmaxf(b.hi[2], z);
 }
 
-// single block: centroid bounds and the per-axis Morton scale
-__global__ void k_bounds(const float4* __restrict__ cen, int nf, float* out /* lo[3], hi[3], s[3] */) {
-    __shared__ float smin[3][1024], smax[3][1024];
-    const int t = threadIdx.x;
-    float lo[3] = {__int_as_float(0x7f800000), __int_as_float(0x7f800000), __int_as_float(0x7f800000)};
-    float hi[3] = {-__int_as_float(0x7f800000), -__int_as_float(0x7f800000), -__int_as_float(0x7f800000)};
-    for (int i = t; i < nf; i += blockDim.x) {
-        const float4 c = cen[i];
-        lo[0] = fminf(lo[0], c.x); lo[1] = fminf(lo[1], c.y); lo[2] = fminf(lo[2], c.z);
-        hi[0] = fmaxf(hi[0], c.x); hi[1] = fmaxf(hi[1], c.y); hi[2] = fmaxf(hi[2], c.z);
+__global__ void __launch_bounds__(BND_BLOCK) k_face_prep(const float* __restrict__ V, const int* __restrict__ F, int nf,
+                                                         float4* fnorm, float4* bmin, float4* bmax, float4* cen,
+                                                         Bounds* bounds) {
+#pragma clang fp contract(off)
+    Bounds bb = bounds_none();
+    for (int q = 0; q < BND_TILE / BND_BLOCK; ++q) {
+        const int f = blockIdx.x * BND_TILE + q * BND_BLOCK + threadIdx.x;
+        if (f >= nf) break;
+        const V3 a = ld3(V + 3 * F[3 * f]), b = ld3(V + 3 * F[3 * f + 1]), c = ld3(V + 3 * F[3 * f + 2]);
+        const V3 N = cross(b - a, c - a);
+        const float l = len(N);
+        const V3 n = l > 0.0f ? N * (1.0f / l) : V3{0.f, 0.f, 0.f};
+        fnorm[f] = make_float4(n.x, n.y, n.z, 0.5f * l);
+        const V3 mn{fminf(a.x, fminf(b.x, c.x)), fminf(a.y, fminf(b.y, c.y)), fminf(a.z, fminf(b.z, c.z))};
+        const V3 mx{fmaxf(a.x, fmaxf(b.x, c.x)), fmaxf(a.y, fmaxf(b.y, c.y)), fmaxf(a.z, fmaxf(b.z, c.z))};
+        bmin[f] = make_float4(mn.x, mn.y, mn.z, 0.f);
+        bmax[f] = make_float4(mx.x, mx.y, mx.z, 0.f);
+        const float cx = mn.x + mx.x, cy = mn.y + mx.y, cz = mn.z + mx.z;
+        cen[f] = make_float4(cx * 0.5f, cy * 0.5f, cz * 0.5f, 0.f);
+        bounds_add(bb, cx * 0.5f, cy * 0.5f, cz * 0.5f);
     }
-    for (int k = 0; k < 3; ++k) { smin[k][t] = lo[k]; smax[k][t] = hi[k]; }
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (t < s)
-            for (int k = 0; k < 3; ++k) {
-                smin[k][t] = fminf(smin[k][t], smin[k][t + s]);
-                smax[k][t] = fmaxf(smax[k][t], smax[k][t + s]);
-            }
-        __syncthreads();
-    }
-    if (t == 0) {
-        // one scale for all axes (cubic cells): 1024 cells along the longest extent
-        double ext = 0.0;
-        for (int k = 0; k < 3; ++k) ext = fmax(ext, (double)smax[k][0] - (double)smin[k][0]);
-        for (int k = 0; k < 3; ++k) {
-            out[k] = smin[k][0];
-            out[3 + k] = smax[k][0];
-            out[6 + k] = ext > 0.0 ? (float)(1024.0 / ext) : 0.0f;
-        }
-    }
+    bb = block_bounds(bb);
+    if (threadIdx.x == 0) bounds[blockIdx.x] = bb;
 }
 
 __device__ __forceinline__ uint32_t spread10(uint32_t v) {
@@ -74,24 +82,6 @@ __device__ __forceinline__ uint32_t spread10(uint32_t v) {
     return v;
 }
 
-__global__ void k_morton(const float4* __restrict__ cen, int nf, const float* __restrict__ bnd, uint32_t* keys,
-                         uint32_t* vals) {
-#pragma clang fp contract(off)
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= nf) return;
-    const float4 c = cen[f];
-    const float cc[3] = {c.x, c.y, c.z};
-    uint32_t q[3];
-    for (int k = 0; k < 3; ++k) {
-        const float d = cc[k] - bnd[k];
-        const float p = d * bnd[6 + k];
-        const int qi = (int)floorf(p);
-        q[k] = (uint32_t)min(1023, max(0, qi));
-    }
-    keys[f] = (spread10(q[0]) << 2) | (spread10(q[1]) << 1) | spread10(q[2]);
-    vals[f] = (uint32_t)f;
-}
-
 // ---------------------------------------------------------------------------
 // stable LSD radix sort of (u32 key, u32 value), 8-bit digits, tiles of 1024
 // ---------------------------------------------------------------------------
@@ -99,7 +89,8 @@ constexpr int RS_THREADS = 256;
 constexpr int RS_ITEMS = 4;
 constexpr int RS_TILE = RS_THREADS * RS_ITEMS;
 
-__global__ void k_rs_hist(const uint32_t* __restrict__ keys, int n, int shift, uint32_t* hist, int nblocks) {
+// digit counts of a block's tile: hist[256 block + digit]
+__global__ void k_rs_hist(const uint32_t* __restrict__ keys, int n, int shift, uint32_t* hist) {
     __shared__ uint32_t h[256];
     h[threadIdx.x] = 0;
     __syncthreads();
@@ -109,26 +100,94 @@ __global__ void k_rs_hist(const uint32_t* __restrict__ keys, int n, int shift, u
         if (i < n) atomicAdd(&h[(keys[i] >> shift) & 0xFFu], 1u);
     }
     __syncthreads();
-    hist[threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
+    hist[256 * (size_t)blockIdx.x + threadIdx.x] = h[threadIdx.x];
 }
 
-// exclusive scan of hist[256 * nblocks] (digit-major) in one block
-__global__ void k_rs_scan(uint32_t* hist, int total) {
-    __shared__ uint32_t part[1024];
-    const int t = threadIdx.x;
-    const int per = (total + 1023) / 1024;
-    const int b = t * per, e = min(total, b + per);
-    uint32_t s = 0;
-    for (int i = b; i < e; ++i) s += hist[i];
-    part[t] = s;
-    __syncthreads();
-    if (t == 0) {
-        uint32_t acc = 0;
-        for (int i = 0; i < 1024; ++i) { const uint32_t v = part[i]; part[i] = acc; acc += v; }
+// Morton keys and the digit counts of the first sorting pass (of the same tiles)
+__global__ void __launch_bounds__(BND_BLOCK) k_morton(const float4* __restrict__ cen, int nf, const Bounds* __restrict__ bounds,
+                                                      int nbounds, uint32_t* keys, uint32_t* vals, uint32_t* hist) {
+#pragma clang fp contract(off)
+    static_assert(RS_TILE == BND_TILE && RS_THREADS == BND_BLOCK, "one tile for bounds, keys and counts");
+    __shared__ uint32_t h[256];
+    h[threadIdx.x] = 0;
+    Bounds bb = bounds_none();
+    for (int i = threadIdx.x; i < nbounds; i += BND_BLOCK) {
+        const Bounds o = bounds[i];
+        bounds_add(bb, o.lo[0], o.lo[1], o.lo[2]);
+        bounds_add(bb, o.hi[0], o.hi[1], o.hi[2]);
+    }
+    bb = block_bounds(bb);     // (synchronises the block)
+    // one scale for all axes (cubic cells): 1024 cells along the longest extent
+    double ext = 0.0;
+    for (int k = 0; k < 3; ++k) ext = fmax(ext, (double)bb.hi[k] - (double)bb.lo[k]);
+    const float scale = ext > 0.0 ? (float)(1024.0 / ext) : 0.0f;
+    for (int r = 0; r < RS_ITEMS; ++r) {
+        const int f = blockIdx.x * RS_TILE + r * RS_THREADS + threadIdx.x;
+        if (f >= nf) break;
+        const float4 c = cen[f];
+        const float cc[3] = {c.x, c.y, c.z};
+        uint32_t q[3];
+        for (int k = 0; k < 3; ++k) {
+            const float d = cc[k] - bb.lo[k];
+            const float p = d * scale;
+            const int qi = (int)floorf(p);
+            q[k] = (uint32_t)min(1023, max(0, qi));
+        }
+        const uint32_t key = (spread10(q[0]) << 2) | (spread10(q[1]) << 1) | spread10(q[2]);
+        keys[f] = key;
+        vals[f] = (uint32_t)f;
+        atomicAdd(&h[key & 0xFFu], 1u);
     }
     __syncthreads();
-    uint32_t acc = part[t];
-    for (int i = b; i < e; ++i) { const uint32_t v = hist[i]; hist[i] = acc; acc += v; }
+    hist[256 * (size_t)blockIdx.x + threadIdx.x] = h[threadIdx.x];
+}
+
+// Where a tile's entries of each digit go: the entries of lower digits, then those
+// of the same digit in the tiles before.  Up to RS_SUM_TILES tiles every tile adds
+// the counts of all tiles itself (a coalesced row of 256 a tile: 40 rows take 2 us at
+// 40,000 keys, where one block scanning them took 16); beyond, k_rs_scan prepares them.
+constexpr int RS_SUM_TILES = 512;
+// exclusive sum of v over the first 256 threads of the block (those with in)
+__device__ __forceinline__ uint32_t block_excl_256(uint32_t v, uint32_t* lds /* 4 */, bool in = true) {
+    uint32_t inc = v;
+    const int lane = (int)__lane_id(), w = (int)(threadIdx.x >> 6);
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t x = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += x;
+    }
+    if (lane == 63 && in) lds[w] = inc;
+    __syncthreads();
+    uint32_t before = 0;
+    for (int k = 0; in && k < w; ++k) before += lds[k];
+    return before + inc - v;
+}
+// hist to these starts, in place; one block, a thread per digit and quarter of the tiles
+constexpr int RS_SCAN_THREADS = 1024;
+__global__ void __launch_bounds__(RS_SCAN_THREADS) k_rs_scan(uint32_t* hist, int nblocks) {
+    __shared__ uint32_t lds[4];
+    __shared__ uint32_t part[4][256], start[256];
+    const int d = threadIdx.x & 255, q = threadIdx.x >> 8;
+    const int b0 = (int)((long long)nblocks * q / 4), b1 = (int)((long long)nblocks * (q + 1) / 4);
+    uint32_t tot = 0;
+#pragma unroll 8
+    for (int b = b0; b < b1; ++b) tot += hist[256 * (size_t)b + d];
+    part[q][d] = tot;
+    __syncthreads();
+    // the first 256 threads (four waves) scan; all synchronise
+    uint32_t all = 0;
+    for (int k = 0; k < 4; ++k) all += part[k][d];
+    const uint32_t at0 = block_excl_256(q == 0 ? all : 0u, lds, q == 0);
+    if (q == 0) start[d] = at0;
+    __syncthreads();
+    uint32_t at = start[d];
+    for (int k = 0; k < q; ++k) at += part[k][d];
+#pragma unroll 8
+    for (int b = b0; b < b1; ++b) {
+        const uint32_t c = hist[256 * (size_t)b + d];
+        hist[256 * (size_t)b + d] = at;
+        at += c;
+    }
 }
 
 __global__ void k_rs_scatter(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint32_t* kout,
@@ -137,9 +196,21 @@ __global__ void k_rs_scatter(const uint32_t* __restrict__ kin, const uint32_t* _
     __shared__ uint32_t wcount[NW][256];
     __shared__ uint32_t running[256];
     __shared__ uint32_t gbase[256];
+    __shared__ uint32_t scan[4];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     running[t] = 0;
-    gbase[t] = hist[t * nblocks + blockIdx.x];
+    if (nblocks > RS_SUM_TILES) {
+        gbase[t] = hist[256 * (size_t)blockIdx.x + t];
+    } else {
+        uint32_t tot = 0, before = 0;
+#pragma unroll 8
+        for (int b = 0; b < nblocks; ++b) {
+            const uint32_t c = hist[256 * b + t];
+            tot += c;
+            before += b < (int)blockIdx.x ? c : 0u;
+        }
+        gbase[t] = before + block_excl_256(tot, scan);
+    }
     for (int k = 0; k < NW; ++k) wcount[k][t] = 0;
     __syncthreads();
     const int base = blockIdx.x * RS_TILE;
@@ -951,19 +1022,26 @@ __global__ void k_keys64(const uint32_t* __restrict__ m, const uint32_t* __restr
     if (i < n) out[i] = ((uint64_t)m[i] << 32) | fa[i];
 }
 
-__global__ void k_edge_len(const int4* __restrict__ edges, int ne, const float* __restrict__ V, double* w) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= ne) return;
-    const int4 E = edges[e];
-    const double dx = (double)V[3 * E.y] - (double)V[3 * E.x];
-    const double dy = (double)V[3 * E.y + 1] - (double)V[3 * E.x + 1];
-    const double dz = (double)V[3 * E.y + 2] - (double)V[3 * E.x + 2];
-    w[e] = sqrt(dx * dx + dy * dy + dz * dz);
+__global__ void __launch_bounds__(CDF_BLOCK) k_edge_len(const int4* __restrict__ edges, int ne, const float* __restrict__ V,
+                                                        double* w, double* tiles) {
+    double s = 0.0;
+    for (int q = 0; q < CDF_PER; ++q) {
+        const int e = blockIdx.x * CDF_TILE + threadIdx.x * CDF_PER + q;
+        if (e >= ne) break;
+        const int4 E = edges[e];
+        const double dx = (double)V[3 * E.y] - (double)V[3 * E.x];
+        const double dy = (double)V[3 * E.y + 1] - (double)V[3 * E.x + 1];
+        const double dz = (double)V[3 * E.y + 2] - (double)V[3 * E.x + 2];
+        w[e] = sqrt(dx * dx + dy * dy + dz * dz);
+        s += w[e];
+    }
+    cdf_tile_sum(s, tiles);
 }
 
-__global__ void k_edge_cdf(const double* w, int ne, double* cdf, double* total, float* ftotal) {
-    block_scan_normalise(w, ne, cdf, total);
-    if (threadIdx.x == 0) *ftotal = (float)*total;
+__global__ void __launch_bounds__(CDF_BLOCK) k_edge_cdf(const double* w, const double* tiles, int ne, double* cdf,
+                                                        double* total, float* ftotal) {
+    const double t = cdf_tile_write(w, ne, tiles, cdf, total);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *ftotal = (float)t;
 }
 
 // environment map: per-row texel weights (mean rgb times row solid angle) and
@@ -1073,19 +1151,25 @@ void launch_subdivide(const SceneDev& s, float* out_V, int32_t* out_F, hipStream
 // secondary-edge importance tree: the same radix tree over the edges' boxes,
 // each node also carrying the float sum of the edge lengths below it
 // ---------------------------------------------------------------------------
-__global__ void k_edge_prep(const float* __restrict__ V, const int4* __restrict__ edges, int ne, float4* bmin,
-                            float4* bmax, float4* cen) {
+__global__ void __launch_bounds__(BND_BLOCK) k_edge_prep(const float* __restrict__ V, const int4* __restrict__ edges, int ne,
+                                                         float4* bmin, float4* bmax, float4* cen, Bounds* bounds) {
 #pragma clang fp contract(off)
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= ne) return;
-    const int4 E = edges[e];
-    const V3 a = ld3(V + 3 * E.x), c = ld3(V + 3 * E.y);
-    const V3 mn{fminf(a.x, c.x), fminf(a.y, c.y), fminf(a.z, c.z)};
-    const V3 mx{fmaxf(a.x, c.x), fmaxf(a.y, c.y), fmaxf(a.z, c.z)};
-    bmin[e] = make_float4(mn.x, mn.y, mn.z, 0.f);
-    bmax[e] = make_float4(mx.x, mx.y, mx.z, 0.f);
-    const float cx = mn.x + mx.x, cy = mn.y + mx.y, cz = mn.z + mx.z;
-    cen[e] = make_float4(cx * 0.5f, cy * 0.5f, cz * 0.5f, 0.f);
+    Bounds bb = bounds_none();
+    for (int q = 0; q < BND_TILE / BND_BLOCK; ++q) {
+        const int e = blockIdx.x * BND_TILE + q * BND_BLOCK + threadIdx.x;
+        if (e >= ne) break;
+        const int4 E = edges[e];
+        const V3 a = ld3(V + 3 * E.x), c = ld3(V + 3 * E.y);
+        const V3 mn{fminf(a.x, c.x), fminf(a.y, c.y), fminf(a.z, c.z)};
+        const V3 mx{fmaxf(a.x, c.x), fmaxf(a.y, c.y), fmaxf(a.z, c.z)};
+        bmin[e] = make_float4(mn.x, mn.y, mn.z, 0.f);
+        bmax[e] = make_float4(mx.x, mx.y, mx.z, 0.f);
+        const float cx = mn.x + mx.x, cy = mn.y + mx.y, cz = mn.z + mx.z;
+        cen[e] = make_float4(cx * 0.5f, cy * 0.5f, cz * 0.5f, 0.f);
+        bounds_add(bb, cx * 0.5f, cy * 0.5f, cz * 0.5f);
+    }
+    bb = block_bounds(bb);
+    if (threadIdx.x == 0) bounds[blockIdx.x] = bb;
 }
 
 // unit normal of face f: the double cross product of the float edge vectors over
@@ -1193,17 +1277,16 @@ __global__ void k_epack(const int* __restrict__ child, const float* __restrict__
     }
 }
 
-// Morton keys of n centres, stably sorted (4 LSD passes); returns the buffer
-// index that holds the sorted (key, value) pairs
-static int radix_sort_keys(const float4* cen, int n, float* bounds, uint32_t* const mk[2], uint32_t* const mv[2],
+// Morton keys of n centres with these block bounds, stably sorted (4 LSD passes);
+// returns the buffer index that holds the sorted (key, value) pairs
+static int radix_sort_keys(const float4* cen, int n, const Bounds* bounds, uint32_t* const mk[2], uint32_t* const mv[2],
                            uint32_t* hist, hipStream_t st) {
-    ST_LAUNCH("k_bounds", k_bounds, dim3(1), dim3(1024), 0, st, cen, n, bounds);
-    ST_LAUNCH("k_morton", k_morton, dim3(nb(n, 256)), dim3(256), 0, st, cen, n, bounds, mk[0], mv[0]);
     const int nblocks = (n + RS_TILE - 1) / RS_TILE;
+    ST_LAUNCH("k_morton", k_morton, dim3(nblocks), dim3(RS_THREADS), 0, st, cen, n, bounds, nblocks, mk[0], mv[0], hist);
     int cur = 0;
     for (int shift = 0; shift < 32; shift += 8) {
-        ST_LAUNCH("k_rs_hist", k_rs_hist, dim3(nblocks), dim3(RS_THREADS), 0, st, mk[cur], n, shift, hist, nblocks);
-        ST_LAUNCH("k_rs_scan", k_rs_scan, dim3(1), dim3(1024), 0, st, hist, 256 * nblocks);
+        if (shift > 0) ST_LAUNCH("k_rs_hist", k_rs_hist, dim3(nblocks), dim3(RS_THREADS), 0, st, mk[cur], n, shift, hist);
+        if (nblocks > RS_SUM_TILES) ST_LAUNCH("k_rs_scan", k_rs_scan, dim3(1), dim3(RS_SCAN_THREADS), 0, st, hist, nblocks);
         ST_LAUNCH("k_rs_scatter", k_rs_scatter, dim3(nblocks), dim3(RS_THREADS), 0, st, mk[cur], mv[cur], mk[cur ^ 1],
                   mv[cur ^ 1], n, shift, hist, nblocks);
         cur ^= 1;
@@ -1214,9 +1297,9 @@ static int radix_sort_keys(const float4* cen, int n, float* bounds, uint32_t* co
 void launch_edge_tree(SceneDev& s, hipStream_t st) {
     const int n = s.ne;
     if (n <= 0) return;
-    ST_LAUNCH("k_edge_prep", k_edge_prep, dim3(nb(n, 256)), dim3(256), 0, st, s.V, s.edges, n, s.ebmin, s.ebmax,
-              s.ecen);
-    const int cur = radix_sort_keys(s.ecen, n, s.ebounds, s.emkeys, s.emvals, s.ers_hist, st);
+    ST_LAUNCH("k_edge_prep", k_edge_prep, dim3(nb(n, BND_TILE)), dim3(BND_BLOCK), 0, st, s.V, s.edges, n, s.ebmin, s.ebmax,
+              s.ecen, (Bounds*)s.ebounds);
+    const int cur = radix_sort_keys(s.ecen, n, (const Bounds*)s.ebounds, s.emkeys, s.emvals, s.ers_hist, st);
     const uint32_t* sm = s.emkeys[cur];
     const uint32_t* se = s.emvals[cur];
     s.eleaf_edge = se;
@@ -1235,20 +1318,9 @@ void launch_edge_tree(SceneDev& s, hipStream_t st) {
 void launch_scene_geometry(SceneDev& s, hipStream_t st) {
     const int nf = s.nf;
     if (nf <= 0) return;
-    ST_LAUNCH("k_face_prep", k_face_prep, dim3(nb(nf, 256)), dim3(256), 0, st, s.V, s.F, nf, s.fnorm, s.bmin, s.bmax,
-                       s.cen);
-    ST_LAUNCH("k_bounds", k_bounds, dim3(1), dim3(1024), 0, st, s.cen, nf, s.bounds);
-    ST_LAUNCH("k_morton", k_morton, dim3(nb(nf, 256)), dim3(256), 0, st, s.cen, nf, s.bounds, s.mkeys[0], s.mvals[0]);
-    const int nblocks = (nf + RS_TILE - 1) / RS_TILE;
-    int cur = 0;
-    for (int shift = 0; shift < 32; shift += 8) {
-        ST_LAUNCH("k_rs_hist", k_rs_hist, dim3(nblocks), dim3(RS_THREADS), 0, st, s.mkeys[cur], nf, shift, s.rs_hist,
-                           nblocks);
-        ST_LAUNCH("k_rs_scan", k_rs_scan, dim3(1), dim3(1024), 0, st, s.rs_hist, 256 * nblocks);
-        ST_LAUNCH("k_rs_scatter", k_rs_scatter, dim3(nblocks), dim3(RS_THREADS), 0, st, s.mkeys[cur], s.mvals[cur],
-                           s.mkeys[cur ^ 1], s.mvals[cur ^ 1], nf, shift, s.rs_hist, nblocks);
-        cur ^= 1;
-    }
+    ST_LAUNCH("k_face_prep", k_face_prep, dim3(nb(nf, BND_TILE)), dim3(BND_BLOCK), 0, st, s.V, s.F, nf, s.fnorm, s.bmin,
+              s.bmax, s.cen, (Bounds*)s.bounds);
+    const int cur = radix_sort_keys(s.cen, nf, (const Bounds*)s.bounds, s.mkeys, s.mvals, s.rs_hist, st);
     // after 4 passes the sorted data is back in buffer 0
     const uint32_t* sm = s.mkeys[cur];
     const uint32_t* sf = s.mvals[cur];
@@ -1271,9 +1343,10 @@ void launch_scene_geometry(SceneDev& s, hipStream_t st) {
                   s.slots4, sf, s.V, s.F, nf, s.nodes4, s.tri, s.fleaf, s.err);
     }
     if (s.ne > 0) {
-        ST_LAUNCH("k_edge_len", k_edge_len, dim3(nb(s.ne, 256)), dim3(256), 0, st, s.edges, s.ne, s.V, s.edge_w);
-        ST_LAUNCH("k_edge_cdf", k_edge_cdf, dim3(1), dim3(1024), 0, st, s.edge_w, s.ne, s.ecdf, s.etotal_d,
-                           s.etotal_f);
+        const dim3 tiles((unsigned)cdf_tiles(s.ne));
+        ST_LAUNCH("k_edge_len", k_edge_len, tiles, dim3(CDF_BLOCK), 0, st, s.edges, s.ne, s.V, s.edge_w, s.edge_tiles);
+        ST_LAUNCH("k_edge_cdf", k_edge_cdf, tiles, dim3(CDF_BLOCK), 0, st, s.edge_w, s.edge_tiles, s.ne, s.ecdf,
+                  s.etotal_d, s.etotal_f);
         launch_guide(s.ecdf, s.ne, 0, 1, s.eguide, guide_log2(s.ne), st);
     }
 }

@@ -47,7 +47,7 @@ struct SceneDev {
     float* env = nullptr;
     // geometry build
     float4 *fnorm = nullptr, *bmin = nullptr, *bmax = nullptr, *cen = nullptr;
-    float* bounds = nullptr;                 // lo[3], hi[3], scale[3]
+    float* bounds = nullptr;                 // centroid bounds of each tile of 1024: lo[3], hi[3]
     uint32_t* mkeys[2] = {nullptr, nullptr};
     uint32_t* mvals[2] = {nullptr, nullptr};
     uint32_t* rs_hist = nullptr;
@@ -82,6 +82,7 @@ struct SceneDev {
     // edges (topology fixed at creation)
     int4* edges = nullptr;
     double* edge_w = nullptr;
+    double* edge_tiles = nullptr;            // sums of edge_w over tiles of CDF_TILE
     int* eguide = nullptr;                   // guide table of ecdf
     int* mguide = nullptr;                   // guide table of the env marginal CDF
     int* cguide = nullptr;                   // guide tables of the env conditional CDFs
@@ -276,12 +277,14 @@ struct BwdParams {
     uint32_t* spill;
     double* pcdf;            // per-view primary edge CDF [ncam, ne+1]
     double* pw;              // per-view primary edge weights [ncam, ne]
+    double* ptiles;          // their sums over tiles of CDF_TILE [ncam, cdf_tiles(ne)]
     double* ptotal;          // [ncam]
     int* pguide;             // per-view guide tables of pcdf [ncam, 2^pglog]
     int pglog;
     double* pacc;            // per (view, edge): sums of c (1-t) and c t over its primary edge samples [ncam, ne, 2]
     int ne;
     double* lw;              // per-light shadow-edge weights [nl, ne]
+    double* ltiles;          // their tile sums [nl, cdf_tiles(ne)]
     double* lcdf;            // per-light shadow-edge CDF [nl, ne+1]
     double* ltotal;          // [nl]
     int* lguide;             // per-light guide tables [nl, 2^pglog]
