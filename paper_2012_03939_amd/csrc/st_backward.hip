@@ -82,9 +82,9 @@ __device__ __forceinline__ void atomic_add3(float* p, V3 g) {
 // unnormalised face normal in double, fixed operation order
 __device__ __forceinline__ void face_N_d(const DevScene& S, int f, double N[3], double v0[3]) {
 #pragma clang fp contract(off)
-    const float* a = S.V + 3 * S.F[3 * f];
-    const float* b = S.V + 3 * S.F[3 * f + 1];
-    const float* c = S.V + 3 * S.F[3 * f + 2];
+    const auto a = S.V + 3 * S.F[3 * f];
+    const auto b = S.V + 3 * S.F[3 * f + 1];
+    const auto c = S.V + 3 * S.F[3 * f + 2];
     const double e1x = (double)b[0] - (double)a[0], e1y = (double)b[1] - (double)a[1], e1z = (double)b[2] - (double)a[2];
     const double e2x = (double)c[0] - (double)a[0], e2y = (double)c[1] - (double)a[1], e2z = (double)c[2] - (double)a[2];
     N[0] = e1y * e2z - e1z * e2y;
@@ -283,7 +283,7 @@ k_adjoint(BwdParams p, long long total) {
                 const Mat m = load_mat(S.mat + 7 * (size_t)tx);
                 const uint32_t rocc = (REC || rec_occ) ? qld(rec_occ + ri) : 0u;
                 for (int l = 0; l < S.nl; ++l) {
-                    const float* lt = S.lights + 6 * l;
+                    const auto lt = S.lights + 6 * l;
                     const V3 dl = ld3(lt) - xh;
                     const float r2 = dot(dl, dl);
                     uint32_t code = 0;
@@ -449,7 +449,7 @@ k_adjoint(BwdParams p, long long total) {
                     float gm[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
                     for (int l = 0; l < S.nl; ++l) {
                         if (!((fl >> (8 + l)) & 1u)) continue;
-                        const float* lt = S.lights + 6 * l;
+                        const auto lt = S.lights + 6 * l;
                         const V3 I = ld3(lt + 3);
                         const V3 dl = ld3(lt) - xh;
                         const float r2 = dot(dl, dl);
@@ -565,8 +565,8 @@ struct ScreenEdge {
 
 __device__ __forceinline__ bool screen_edge(const DevCam& c, const DevScene& S, int4 E, ScreenEdge& r) {
 #pragma clang fp contract(off)
-    const float* A = S.V + 3 * E.x;
-    const float* B = S.V + 3 * E.y;
+    const auto A = S.V + 3 * E.x;
+    const auto B = S.V + 3 * E.y;
     const double a0 = A[0], a1 = A[1], a2 = A[2], b0 = B[0], b1 = B[1], b2 = B[2];
     double ax, ay, az, bx, by, bz;
     project_d(c, a0, a1, a2, ax, ay, az);
@@ -953,7 +953,7 @@ __device__ void shadow_edge_one(const BwdParams& p, const DevScene& S, const Dev
     const float t = u.y;
     h.push((uint32_t)e);
     const int4 E = S.edges[e];
-    const float* lt = S.lights + 6 * l;
+    const auto lt = S.lights + 6 * l;
     const V3 pl = ld3(lt), va = ld3(S.V + 3 * E.x), vb = ld3(S.V + 3 * E.y);
     const V3 y = va + (vb - va) * t;
     const V3 w = normalize(y - pl);

@@ -65,7 +65,7 @@ __device__ __forceinline__ V3 cross(V3 a, V3 b) {
 __device__ __forceinline__ float len(V3 a) { return sqrtf(dot(a, a)); }
 __device__ __forceinline__ V3 normalize(V3 a) { return a * (1.0f / len(a)); }
 __device__ __forceinline__ float hsum(V3 a) { return a.x + a.y + a.z; }
-__device__ __forceinline__ V3 ld3(const float* p) { return V3{p[0], p[1], p[2]}; }
+template <class P> __device__ __forceinline__ V3 ld3(P p) { return V3{p[0], p[1], p[2]}; }
 __device__ __forceinline__ V3 xyz(float4 a) { return V3{a.x, a.y, a.z}; }
 
 // ---------------------------------------------------------------------------
@@ -116,34 +116,48 @@ struct __align__(16) EnvAlias {
     int pad;
 };
 
+// A pointer kept in a struct in memory, of which device code knows that it points to
+// global memory: its loads are global, not flat (a flat load also occupies the LDS
+// path, and its waits cannot be told from those of LDS accesses).
+#if defined(__HIP_DEVICE_COMPILE__)
+#define ST_GLOBAL __attribute__((address_space(1)))
+#else
+#define ST_GLOBAL
+#endif
+template <class T> struct GPtr {
+    T* p;
+    __host__ __device__ __forceinline__ GPtr& operator=(T* q) { p = q; return *this; }
+    __host__ __device__ __forceinline__ operator T ST_GLOBAL*() const { return (T ST_GLOBAL*)p; }
+};
+
 struct DevScene {
-    const float* V;       // [nv,3]
-    const int* F;         // [nf,3]
-    const float* mat;     // [nf,7]
-    const float* lights;  // [nl,6]
-    const float4* fnorm;  // [nf] unit geometric normal
-    const float4* tri;    // [nf*3] node-ordered (v0, face bits) (e1) (e2)
-    const int* fleaf;     // [nf] record of each face in tri
-    const float4* nodes4; // 4-wide nodes, 8 float4 each: SoA child boxes + where the children start
-    const float* env;     // [he,we,3]
-    const double* marg;   // [he+1]
-    const double* cond;   // [he,we+1]
-    const float* texpdf;  // [he*we] solid-angle pdf of each texel
-    const float* rowcos;  // [2*(he+1)]: 1 - cos(pi r / he), then 1 + cos(pi r / he)
-    const int4* edges;    // [ne] (va, vb, f1, f2)
-    const double* ecdf;   // [ne+1] cumulative 3-D length / total
-    const float* etotal;  // total 3-D edge length
-    const int* eguide;    // guide table of ecdf, 2^eglog entries
-    const int* mguide;    // guide table of the env marginal CDF, 2^mglog entries
-    const int* cguide;    // guide tables of the env conditional CDFs, 2^cglog entries per row
-    const int* etchild;   // secondary-edge importance tree: children [ne-1, 2]
-    const float* etbox;   // node boxes [2ne-1, 6] (internal nodes, then leaves)
-    const float* etlen;   // node length sums [2ne-1]
-    const float* etnbox;  // node boxes of the adjacent faces' unit normals [2ne-1, 6]
-    const float4* etnode; // per internal node, both children's box, length, normal box and code
+    GPtr<const float> V;       // [nv,3]
+    GPtr<const int> F;         // [nf,3]
+    GPtr<const float> mat;     // [nf,7]
+    GPtr<const float> lights;  // [nl,6]
+    GPtr<const float4> fnorm;  // [nf] unit geometric normal
+    GPtr<const float4> tri;    // [nf*3] node-ordered (v0, face bits) (e1) (e2)
+    GPtr<const int> fleaf;     // [nf] record of each face in tri
+    GPtr<const float4> nodes4; // 4-wide nodes, 8 float4 each: SoA child boxes + where the children start
+    GPtr<const float> env;     // [he,we,3]
+    GPtr<const double> marg;   // [he+1]
+    GPtr<const double> cond;   // [he,we+1]
+    GPtr<const float> texpdf;  // [he*we] solid-angle pdf of each texel
+    GPtr<const float> rowcos;  // [2*(he+1)]: 1 - cos(pi r / he), then 1 + cos(pi r / he)
+    GPtr<const int4> edges;    // [ne] (va, vb, f1, f2)
+    GPtr<const double> ecdf;   // [ne+1] cumulative 3-D length / total
+    GPtr<const float> etotal;  // total 3-D edge length
+    GPtr<const int> eguide;    // guide table of ecdf, 2^eglog entries
+    GPtr<const int> mguide;    // guide table of the env marginal CDF, 2^mglog entries
+    GPtr<const int> cguide;    // guide tables of the env conditional CDFs, 2^cglog entries per row
+    GPtr<const int> etchild;   // secondary-edge importance tree: children [ne-1, 2]
+    GPtr<const float> etbox;   // node boxes [2ne-1, 6] (internal nodes, then leaves)
+    GPtr<const float> etlen;   // node length sums [2ne-1]
+    GPtr<const float> etnbox;  // node boxes of the adjacent faces' unit normals [2ne-1, 6]
+    GPtr<const float4> etnode; // per internal node, both children's box, length, normal box and code
                           // in one 128-B record (8 float4, layout of k_epack) [ne-1]
-    const uint32_t* etedge; // sorted leaf -> edge
-    const EnvAlias* ealias; // [he*we] alias table of the texel probabilities, used when env_alias
+    GPtr<const uint32_t> etedge; // sorted leaf -> edge
+    GPtr<const EnvAlias> ealias; // [he*we] alias table of the texel probabilities, used when env_alias
     int env_alias;
     int vndf;             // specular lobe sampled from the visible normals
     int eglog, mglog, cglog;
@@ -231,11 +245,11 @@ __device__ __forceinline__ const gchar* uniform_ptr(const void* p) {
     return (const gchar*)(((uint64_t)hi << 32) | lo);
 }
 __device__ __forceinline__ TraceGeo lane_geo(const DevScene& S) {
-    return TraceGeo{(const gchar*)S.nodes4, (const gchar*)S.tri, S.nf};
+    return TraceGeo{(const gchar*)S.nodes4.p, (const gchar*)S.tri.p, S.nf};
 }
 // of a scene that is the same for every active lane
 __device__ __forceinline__ TraceGeo wave_geo(const DevScene& S) {
-    return TraceGeo{uniform_ptr(S.nodes4), uniform_ptr(S.tri), __builtin_amdgcn_readfirstlane(S.nf)};
+    return TraceGeo{uniform_ptr(S.nodes4.p), uniform_ptr(S.tri.p), __builtin_amdgcn_readfirstlane(S.nf)};
 }
 
 // FAST traversals address nodes and triangles by 32-bit byte offsets, start at
@@ -553,7 +567,7 @@ __device__ __forceinline__ bool trace_any(const TraceGeo& G, V3 o, V3 d, float t
 // height-correlated Smith G of the Beckmann surface.
 // ---------------------------------------------------------------------------
 struct Mat { V3 kd, ks; float a; };
-__device__ __forceinline__ Mat load_mat(const float* m) {
+template <class P> __device__ __forceinline__ Mat load_mat(P m) {
     Mat r;
     r.kd = V3{m[0], m[1], m[2]};
     r.ks = V3{m[3], m[4], m[5]};
@@ -725,8 +739,8 @@ __device__ __forceinline__ int bsdf_sample(float4 u, V3 wo, V3 n, float alpha, b
 // takes each child with probability proportional to its weight, by a fresh
 // uniform per level (level l: component l % 4 of the draw of block 4 + l / 4 at
 // vertex k); returns the edge and its probability pe, or -1 when all weights vanish.
-__device__ __forceinline__ float edge_node_weight(const float* bx, float len, const float* nb, V3 p, V3 nrm,
-                                                  bool sil) {
+template <class P>
+__device__ __forceinline__ float edge_node_weight(P bx, float len, P nb, V3 p, V3 nrm, bool sil) {
 #pragma clang fp contract(off)
     const float dx = (bx[0] + bx[3]) * 0.5f - p.x, dy = (bx[1] + bx[4]) * 0.5f - p.y, dz = (bx[2] + bx[5]) * 0.5f - p.z;
     const float ex = bx[3] - bx[0], ey = bx[4] - bx[1], ez = bx[5] - bx[2];
@@ -750,12 +764,13 @@ __device__ __forceinline__ float edge_node_weight(const float* bx, float len, co
 }
 
 // child j (0, 1) of a packed record: box (6), length, normal box (6), code
-__device__ __forceinline__ float edge_child_weight(const float4* rec, int j, V3 p, V3 nrm, bool sil, int& code) {
-    const float4 a = rec[4 * j], b = rec[4 * j + 1], c = rec[4 * j + 2], d = rec[4 * j + 3];
+template <class P> __device__ __forceinline__ float edge_child_weight(P rec, int j, V3 p, V3 nrm, bool sil, int& code) {
+    const vf4 a = *(const gfloat4*)(rec + 4 * j), b = *(const gfloat4*)(rec + 4 * j + 1), c = *(const gfloat4*)(rec + 4 * j + 2),
+              d = *(const gfloat4*)(rec + 4 * j + 3);
     const float bx[6] = {a.x, a.y, a.z, a.w, b.x, b.y};
     const float nb[6] = {b.w, c.x, c.y, c.z, c.w, d.x};
     code = __float_as_int(d.y);
-    return edge_node_weight(bx, b.z, nb, p, nrm, sil);
+    return edge_node_weight<const float*>(bx, b.z, nb, p, nrm, sil);
 }
 
 __device__ __forceinline__ int edge_tree_sample(const DevScene& S, V3 p, V3 nrm, const Ctr& ctr, int k,
@@ -768,7 +783,7 @@ __device__ __forceinline__ int edge_tree_sample(const DevScene& S, V3 p, V3 nrm,
     for (int level = 0; !(code & (int)LEAF_BIT); ++level) {
         if (level >= 128) return -1;
         if ((level & 3) == 0) u = draw4(ctr, k, 4 + (level >> 2), key);
-        const float4* rec = S.etnode + 8 * (size_t)code;
+        const auto rec = S.etnode + 8 * (size_t)code;
         int c0, c1;
         const float w0 = edge_child_weight(rec, 0, p, nrm, sil, c0), w1 = edge_child_weight(rec, 1, p, nrm, sil, c1);
         const float tot = w0 + w1;
@@ -837,7 +852,8 @@ __device__ __forceinline__ void brdf_backward(V3 wi, V3 wo, V3 n, const Mat& m, 
 // C[i] <= g / G, G = 2^glog.  With g = floor(u G) the answer of cdf_find lies in
 // [guide[g], guide[g + 1]], so a search of that (usually one- or two-entry)
 // range returns exactly the index of the plain search.
-__device__ __forceinline__ int cdf_guided(const double* C, int n, const int* guide, int glog, double u) {
+template <class PC, class PG>
+__device__ __forceinline__ int cdf_guided(PC C, int n, PG guide, int glog, double u) {
     const int G = 1 << glog;
     int g = (int)(u * (double)G);
     g = g < G - 1 ? g : G - 1;
@@ -967,7 +983,7 @@ __device__ V3 trace_estimator(const DevScene& S, const TraceGeo& G, V3 o, V3 d, 
         if (S.tex_res) hash.push((uint32_t)tx);
         const Mat m = load_mat(S.mat + 7 * (size_t)tx);
         for (int l = 0; l < S.nl; ++l) {
-            const float* lt = S.lights + 6 * l;
+            const auto lt = S.lights + 6 * l;
             const V3 dl = ld3(lt) - x;
             const float r2 = dot(dl, dl);
             uint32_t code = 0;

@@ -206,7 +206,7 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                 if (S.tex_res) h.push((uint32_t)tx);
                 const Mat m = load_mat(S.mat + 7 * (size_t)tx);
                 for (int l = 0; l < S.nl; ++l) {
-                    const float* lt = S.lights + 6 * l;
+                    const auto lt = S.lights + 6 * l;
                     const V3 dl = ld3(lt) - x;
                     const float r2 = dot(dl, dl);
                     float tmax = -1.0f;
