@@ -436,6 +436,7 @@ int render_impl(st_scene* owner, st_scene* const* scenes, int nscenes, const st_
     p.err = owner->d.err;
     p.work = (o.flags & ST_COUNT_WORK) ? owner->d.work : nullptr;
     p.nscenes = nscenes;
+    p.scene = scenes[0]->d.hscene;
     p.fast = p.work ? 0 : 1;
     for (int i = 0; i < nscenes; ++i) p.fast &= scenes[i]->d.nf <= TRAV_FAST_FACES ? 1 : 0;
     p.hash_by_q = nullptr;
@@ -1029,6 +1030,7 @@ int st_render_noalloc(st_scene* sc, const st_camera* cams, int32_t ncam, int32_t
     p.err = sc->d.err;
     p.work = (o.flags & ST_COUNT_WORK) ? sc->d.work : nullptr;
     p.nscenes = 1;
+    p.scene = sc->d.hscene;
     p.fast = !p.work && sc->d.nf <= TRAV_FAST_FACES ? 1 : 0;
     p.hash_by_q = nullptr;
     p.rec_face = nullptr;        // no hit records: the scene's record buffer is not touched
@@ -1121,7 +1123,7 @@ int st_render_backward(st_scene* sc, const st_camera* cams, int32_t ncam, int32_
     if (rc) return rc;
     Carver c{(char*)sc->primbuf.p};
     BwdParams p;
-    p.scenes = cs.scenes;
+    p.scene = sc->d.hscene;
     p.cams = cs.cams;
     p.qoff = cs.qoff;
     p.eoff = cs.eoff;
@@ -1262,6 +1264,7 @@ int st_render_backward(st_scene* sc, const st_camera* cams, int32_t ncam, int32_
         fp.err = sc->d.err;
         fp.work = p.work;
         fp.nscenes = 1;
+        fp.scene = p.scene;
         fp.fast = p.fast;
         fp.hash_by_q = hside;
         fp.rec_face = nullptr;

@@ -191,7 +191,7 @@ k_adjoint(BwdParams p, long long total) {
     __shared__ float red_s[TRACE_BLOCK / 64][64 * FACC];
     float* const red = red_s[threadIdx.x >> 6];
     TravStack st = make_trav_stack(lds, p.spill, p.err, p.work ? p.work + 3 * WORK_ADJOINT : nullptr);
-    const TraceGeo G = wave_geo(p.scenes[0]);     // a backward has one scene
+    const TraceGeo G = wave_geo(p.scene);     // a backward has one scene
     const RecMem rm{p.vrec, (size_t)gridDim.x * blockDim.x, (size_t)blockIdx.x * blockDim.x + threadIdx.x};
     const bool want_interior = !JOBS && (p.flags & 1u), want_secondary = p.flags & 4u;
     const bool sec_interior = p.flags & ST_EDGE_SECONDARY_INTERIOR;   // creases / material edges too
@@ -222,7 +222,7 @@ k_adjoint(BwdParams p, long long total) {
         }
         const int vw = find_view(p.qoff, p.ncam, qq);
         const DevCam& c = p.cams[vw];
-        const DevScene& S = p.scenes[c.scene];
+        const DevScene& S = p.scene;
         int x, y, j;
         decode_path(c, qq - c.qoff, p.spp, x, y, j);
         const long long g = (c.pixoff + (long long)y * c.W + x) * p.spp + j;
@@ -607,7 +607,7 @@ __global__ void __launch_bounds__(CDF_BLOCK) k_prim_weights(BwdParams p) {
 #pragma clang fp contract(off)
     const int v = blockIdx.y;
     const DevCam& c = p.cams[v];
-    const DevScene& S = p.scenes[c.scene];
+    const DevScene& S = p.scene;
     const int ne = S.ne;
     double sum = 0.0;
     for (int q = 0; q < CDF_PER; ++q) {
@@ -649,7 +649,7 @@ __device__ __forceinline__ bool edge_setup(const BwdParams& p, long long ge, Edg
     if (p.edge_mask && !p.edge_mask[ge]) return false;
     es.v = find_view(p.eoff, p.ncam, ge);
     const DevCam& c = p.cams[es.v];
-    const DevScene& S = p.scenes[c.scene];
+    const DevScene& S = p.scene;
     if (!(p.ptotal[es.v] > 0.0)) return false;
     es.si = ge - c.eoff;
     const Ctr ctr{(uint32_t)es.si, (uint32_t)c.rngview << 16, 0u, 1u};
@@ -813,7 +813,7 @@ __global__ void k_edge_finish(BwdParams p) {
 #pragma clang fp contract(off)
     const int v = blockIdx.y;
     const DevCam& c = p.cams[v];
-    const DevScene& S = p.scenes[c.scene];
+    const DevScene& S = p.scene;
     for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < S.ne; e += gridDim.x * blockDim.x) {
         const double* acc = p.pacc + 2 * ((size_t)v * p.ne + e);
         const double w0 = acc[0], w1 = acc[1];
@@ -860,7 +860,7 @@ __global__ void k_edge_finish(BwdParams p) {
 // (vertex gather over the incidence CSR, fixed order); material accumulators
 // (per face, or per texel with mesh colours) to dmat [ntex, 7]
 __global__ void k_face_gather(BwdParams p) {
-    const DevScene& S = p.scenes[0];
+    const DevScene& S = p.scene;
     const int stride = gridDim.x * blockDim.x;
     for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < S.nv; v += stride) {
         float sx = 0.f, sy = 0.f, sz = 0.f;
@@ -896,7 +896,7 @@ __global__ void k_face_gather(BwdParams p) {
 __global__ void __launch_bounds__(CDF_BLOCK) k_light_weights(BwdParams p) {
 #pragma clang fp contract(off)
     const int l = blockIdx.y;
-    const DevScene& S = p.scenes[0];
+    const DevScene& S = p.scene;
     const V3 pl = ld3(S.lights + 6 * l);
     double sum = 0.0;
     for (int q = 0; q < CDF_PER; ++q) {
@@ -1067,7 +1067,7 @@ template <bool FAST>
 __global__ void __launch_bounds__(TRACE_BLOCK) k_shadow_edges(BwdParams p, long long total_edges, long long nsh) {
     __shared__ uint32_t lds[LDS_STACK * TRACE_BLOCK];
     TravStack st = make_trav_stack(lds, p.spill, p.err, nullptr);
-    const DevScene& S = p.scenes[0];
+    const DevScene& S = p.scene;
     const long long nl = S.nl;
     const long long stride = (long long)gridDim.x * blockDim.x;
     for (long long gs = blockIdx.x * (long long)blockDim.x + threadIdx.x; gs < nsh; gs += stride) {

@@ -223,6 +223,7 @@ struct FwdParams {
     long long rec_n;
     int fast;                // every scene within the FAST traversals' reach, no work counters
     int nscenes;
+    DevScene scene;          // the scene of a launch that has one: read from the kernel arguments
     unsigned long long* rec_key_dev;  // with rec_face: the records' key word, cleared by the first camera kernel
 };
 
@@ -255,10 +256,10 @@ void launch_check_finite(const float* a, long long na, const float* b, long long
 void launch_sample_radiance(const FwdParams& p, const float* L, long long total, float* out, hipStream_t st);
 
 struct BwdParams {
+    DevScene scene;          // a backward has one scene: read from the kernel arguments
     int fast;                // the scene is within the FAST traversals' reach, no work counters
     int rec_split;           // the main pass is split: a records-only pass, then one that traces if they are stale
     float* vrec;             // the adjoint's per-vertex replay records (adj_vrec_bytes)
-    const DevScene* scenes;
     const DevCam* cams;
     const long long* qoff;   // [ncam+1] path offsets (processing order)
     const long long* eoff;   // [ncam+1] primary edge sample offsets

@@ -80,7 +80,7 @@ template <bool FAST, bool ONE>
 __device__ __forceinline__ void extend_one(const FwdParams& p, const Queues& q, int k, float* const* r, int i,
                                            const TraceGeo& GW, TravStack& st) {
     const uint32_t view = k == 1 || !ONE ? qu_ld(r, QVD, i) & 0xFFFFu : 0u;
-    const DevScene& S = p.scenes[ONE ? 0 : p.cams[view].scene];
+    const DevScene& S = ONE ? p.scene : p.scenes[p.cams[view].scene];
     const TraceGeo G = ONE ? GW : lane_geo(S);
     const V3 o = k == 1 ? ld3(p.cams[view].eye) : V3{qf(r, QOX, i), qf(r, QOY, i), qf(r, QOZ, i)};
     const V3 d{qf(r, QDX, i), qf(r, QDY, i), qf(r, QDZ, i)};
@@ -116,7 +116,7 @@ template <bool FAST, bool ONE>
 __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_extend(FwdParams p, Queues q, int k) {
     __shared__ uint32_t lds[LDS_STACK * TRACE_BLOCK];
     TravStack st = make_trav_stack(lds, q.spill, p.err, p.work ? p.work + 3 * WORK_EXTEND : nullptr);
-    const TraceGeo G = wave_geo(p.scenes[0]);
+    const TraceGeo G = wave_geo(p.scene);
     const int n = q.cnt[k];
     float* const* r = q.ray[k & 1];
     wave_tiles(q.take + TAKE_NC * 32 * k, (uint32_t)n, [&](uint32_t t) {
@@ -138,7 +138,8 @@ __host__ __device__ __forceinline__ bool shadow_fused(const FwdParams& p, const 
 // shading of bounce k: escapes, next-event set-up and BRDF continuation.
 // HASH: decision hashes are asked for (p.dbg_hash or p.hash_by_q); compiled
 // apart, because the hash state alone made the compiler spill 11 more dwords.
-template <bool HASH>
+// ONE: the launch has one scene.
+template <bool HASH, bool ONE>
 __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Queues q, int k) {
     __shared__ int resv[2 * (SHADE_BLOCK / 64 + 1)];
     const int n = q.cnt[k];
@@ -167,7 +168,7 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
             c0 = qu_ld(r, QC0, i);
             c1 = qu_ld(r, QC1, i);
             vd = qu_ld(r, QVD, i);
-            const DevScene& S = p.scenes[p.cams[vd & 0xFFFFu].scene];
+            const DevScene& S = ONE ? p.scene : p.scenes[p.cams[vd & 0xFFFFu].scene];
             const Key key{p.seed, S.scene_id};
             const Ctr ctr{c0, c1, 0u, vd >> 16};
             Hash h{hashing ? (k == 1 ? FNV_INIT : qu_ld(r, QHASH, i)) : 0u, hashing};
@@ -345,7 +346,7 @@ template <bool FAST, bool ONE>
 __global__ void __launch_bounds__(TRACE_BLOCK) SHADOW_OCC k_shadow(FwdParams p, Queues q, int k) {
     __shared__ uint32_t lds[LDS_STACK * TRACE_BLOCK];
     TravStack st = make_trav_stack(lds, q.spill, p.err, p.work ? p.work + 3 * WORK_SHADOW : nullptr);
-    const TraceGeo G = wave_geo(p.scenes[0]);
+    const TraceGeo G = wave_geo(p.scene);
     const int items = q.cnt[32 + k];
     float* const* r = q.ray[k & 1];
     const bool fused = shadow_fused(p, q);
@@ -370,7 +371,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_trace_pair(FwdParams
     st.work2 = p.work ? p.work + 3 * WORK_PAIR : nullptr;
     unsigned long long* const wext = p.work ? p.work + 3 * WORK_EXTEND : nullptr;
     unsigned long long* const wsh = p.work ? p.work + 3 * WORK_SHADOW : nullptr;
-    const TraceGeo G = wave_geo(p.scenes[0]);
+    const TraceGeo G = wave_geo(p.scene);
     const int n = q.cnt[k + 1];
     const int items = q.cnt[32 + k];
     float* const* rn = q.ray[(k + 1) & 1];
@@ -557,7 +558,9 @@ void launch_wavefront_bounces(const FwdParams& p, Queues& q, int n, int has_env_
     const unsigned g = grid_for(n, TRACE_BLOCK, gmax);
     const int last = p.B + (has_env_any ? 1 : 0);
     const bool fused = shadow_fused(p, q);
-    const bool one = p.fast && p.nscenes == 1;
+    const bool one = p.fast && p.nscenes == 1, hashing = p.dbg_hash || p.hash_by_q;
+    const auto shade = p.nscenes == 1 ? (hashing ? k_shade<true, true> : k_shade<false, true>)
+                                      : (hashing ? k_shade<true, false> : k_shade<false, false>);
     const auto extend = one ? k_extend<true, true> : p.fast ? k_extend<true, false> : k_extend<false, false>;
     const auto shadow_rays = one ? k_shadow<true, true> : p.fast ? k_shadow<true, false> : k_shadow<false, false>;
     const auto pair = one ? k_trace_pair<true, true> : p.fast ? k_trace_pair<true, false> : k_trace_pair<false, false>;
@@ -566,10 +569,7 @@ void launch_wavefront_bounces(const FwdParams& p, Queues& q, int n, int has_env_
     for (int k = 1; k <= last; ++k) {
         // bounce k is traced: shade it, then trace its shadow rays together with
         // the extension rays of bounce k + 1
-        if (p.dbg_hash || p.hash_by_q)
-            ST_LAUNCH("k_shade", k_shade<true>, dim3(grid_for(n, SHADE_BLOCK, gmax)), dim3(SHADE_BLOCK), 0, st, p, q, k);
-        else
-            ST_LAUNCH("k_shade", k_shade<false>, dim3(grid_for(n, SHADE_BLOCK, gmax)), dim3(SHADE_BLOCK), 0, st, p, q, k);
+        ST_LAUNCH("k_shade", shade, dim3(grid_for(n, SHADE_BLOCK, gmax)), dim3(SHADE_BLOCK), 0, st, p, q, k);
         if (hook) hook->tick();
         const bool shadow = k <= p.B, next = k < last;
         if (ST_PAIR_TRACE && shadow && next) {
