@@ -1111,7 +1111,7 @@ void launch_primary_edges(const BwdParams& p, const FwdParams& fp, Queues& q, fl
         ST_LAUNCH("k_edge_camera", k_edge_camera, dim3(gridb(n, EDGE_CAM_BLOCK, 1 << 20)), dim3(EDGE_CAM_BLOCK), 0, st,
                   p, q, e0, n);
         if (hook) hook->tick();
-        launch_wavefront_bounces(fp, q, 2 * n, has_env_any, st, hook);
+        launch_wavefront_bounces(fp, q, 2 * n, -1, has_env_any, st, hook);
     }
     launch_fill_u32((uint32_t*)p.pacc, 4ll * p.ncam * p.ne, 0u, st);      // +0.0 doubles
     ST_LAUNCH("k_edge_grad", k_edge_grad, dim3(gridb(total_edges, 256, 1 << 16)), dim3(256), 0, st, p, Lside, hside,

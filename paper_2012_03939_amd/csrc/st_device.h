@@ -76,10 +76,10 @@ __device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint32_t c2, u
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
         if (r > 0) { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
-        const uint32_t hi0 = __umulhi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
-        const uint32_t hi1 = __umulhi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
-        const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
-        c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
+        // one 64-bit product each: high and low word from a single quarter-rate multiply
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
+        const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0, n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+        c0 = n0; c1 = (uint32_t)p1; c2 = n2; c3 = (uint32_t)p0;
     }
     return make_uint4(c0, c1, c2, c3);
 }
@@ -613,7 +613,14 @@ __device__ __forceinline__ float smith_lambda(float c, float a) {
     return (expf(-x * x) * INV_SQRT_PI_F / x - erfcf(x)) * 0.5f;
 }
 
-__device__ __forceinline__ V3 brdf_eval(V3 wi, V3 wo, V3 n, const Mat& m) {
+// Lambda(wo) of a shading point, for every evaluation there: an exponential and an
+// erfc less in each (only read where n.wo > 0)
+__device__ __forceinline__ float out_lambda(V3 wo, V3 n, const Mat& m) {
+    const float co = dot(n, wo);
+    return co > 0.0f ? smith_lambda(co, alpha_eff(m.a)) : 0.0f;
+}
+
+__device__ __forceinline__ V3 brdf_eval(V3 wi, V3 wo, V3 n, const Mat& m, float lambda_o) {
     const float ci = dot(n, wi), co = dot(n, wo);
     if (!(ci > 0.0f) || !(co > 0.0f)) return V3{0.f, 0.f, 0.f};
     const float a = alpha_eff(m.a);
@@ -622,10 +629,13 @@ __device__ __forceinline__ V3 brdf_eval(V3 wi, V3 wo, V3 n, const Mat& m) {
     float spec = 0.0f;
     if (ch > 0.0f) {
         const float D = beckmann_D(n, h, ch, a);
-        const float G = 1.0f / (1.0f + smith_lambda(ci, a) + smith_lambda(co, a));
+        const float G = 1.0f / (1.0f + smith_lambda(ci, a) + lambda_o);
         spec = D * G / (4.0f * ci * co);
     }
     return m.kd * INV_PI_F + m.ks * spec;
+}
+__device__ __forceinline__ V3 brdf_eval(V3 wi, V3 wo, V3 n, const Mat& m) {
+    return brdf_eval(wi, wo, n, m, out_lambda(wo, n, m));
 }
 
 // pdf of the one-sample mixture: 1/2 cosine-weighted + 1/2 specular, whose
@@ -1040,17 +1050,18 @@ __device__ __forceinline__ uint64_t lanemask_lt64() {
 
 // processing order of path samples inside one view: sample-major, then 8x8
 // pixel tiles (when the view is a multiple of 8 in both axes), then row-major
+// (a call has fewer than 2^31 path samples: 32-bit divisions)
 __device__ __forceinline__ void decode_path(const DevCam& c, long long local, int spp, int& x, int& y, int& j) {
-    const long long hw = (long long)c.W * c.H;
-    j = (int)(local / hw);
-    const int p = (int)(local - (long long)j * hw);
+    const uint32_t hw = (uint32_t)c.W * (uint32_t)c.H, l = (uint32_t)local;
+    j = (int)(l / hw);
+    const uint32_t p = l - (uint32_t)j * hw;
     if ((c.W & 7) == 0 && (c.H & 7) == 0) {
-        const int tile = p >> 6, within = p & 63, tw = c.W >> 3;
-        x = (tile % tw) * 8 + (within & 7);
-        y = (tile / tw) * 8 + (within >> 3);
+        const uint32_t tile = p >> 6, within = p & 63u, tw = (uint32_t)c.W >> 3, ty = tile / tw;
+        x = (int)((tile - ty * tw) * 8 + (within & 7u));
+        y = (int)(ty * 8 + (within >> 3));
     } else {
-        x = p % c.W;
-        y = p / c.W;
+        y = (int)(p / (uint32_t)c.W);
+        x = (int)(p - (uint32_t)y * (uint32_t)c.W);
     }
     (void)spp;
 }
@@ -1063,6 +1074,12 @@ __device__ __forceinline__ int find_view(const long long* off, int ncam, long lo
         if (off[mid] <= q) lo = mid; else hi = mid - 1;
     }
     return lo;
+}
+
+// the view of entry q when entry base (uniform, base <= q) is of view vb: the same
+// but for entries past that view's end
+__device__ __forceinline__ int find_view_from(const long long* off, int ncam, int vb, long long q) {
+    return q < off[vb + 1] ? vb : find_view(off, ncam, q);
 }
 
 // ---------------------------------------------------------------------------

@@ -208,6 +208,8 @@ __device__ __forceinline__ uint32_t qu_ld(float* const* cols, int c, int i) { re
 __device__ __forceinline__ void qf_st(float* const* cols, int c, int i, float v) { qst(cols[c] + i, v); }
 __device__ __forceinline__ void qu_st(float* const* cols, int c, int i, uint32_t v) { qst((uint32_t*)cols[c] + i, v); }
 
+// A wavefront pass starts from camera rays, made where they are traced, or from side
+// rays of primary edge samples, queued by k_edge_camera.
 struct FwdParams {
     const DevScene* scenes;
     const DevCam* cams;
@@ -244,7 +246,7 @@ struct LaunchHook {
         if (++count == at && fn) fn();
     }
 };
-void launch_wavefront_bounces(const FwdParams& p, Queues& q, int n, int has_env_any, hipStream_t st,
+void launch_wavefront_bounces(const FwdParams& p, Queues& q, int n, long long q0, int has_env_any, hipStream_t st,
                               LaunchHook* hook = nullptr);
 void launch_forward_mega(const FwdParams& p, float* L, long long total, uint32_t* spill, int grid, hipStream_t st);
 // key_dev (optional): receives key before the film is written (the forward is complete)

@@ -44,90 +44,103 @@ __device__ __forceinline__ void final_hash(const FwdParams& p, float* const* r, 
     }
 }
 
-// ---------------------------------------------------------------------------
-__global__ void k_camera(FwdParams p, Queues q, long long q0, int n) {
-    const int stride = gridDim.x * blockDim.x;
-    if (blockIdx.x == 0 && threadIdx.x < 64) q.cnt[threadIdx.x] = threadIdx.x == 1 ? n : 0;
-    // the hit records are rewritten from here on: their key is cleared until k_film
-    if (q0 == 0 && blockIdx.x == 0 && threadIdx.x == 0 && p.rec_key_dev) *p.rec_key_dev = 0ull;
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < TAKE_INTS; j += stride) q.take[j] = 0;
-    float* const* r = q.ray[1];
-    for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < n; s += stride) {
-        const long long qq = q0 + s;
-        const int v = find_view(p.qoff, p.ncam, qq);
-        const DevCam& c = p.cams[v];
-        const DevScene& S = p.scenes[c.scene];
-        int x, y, j;
-        decode_path(c, qq - c.qoff, p.spp, x, y, j);
-        const Ctr ctr{(uint32_t)(y * c.W + x), ((uint32_t)c.rngview << 16) | (uint32_t)j, 0u, 0u};
-        const float4 u = draw4(ctr, 0, 0, Key{p.seed, S.scene_id});
-        const V3 d = cam_dir(c, (float)x + u.x, (float)y + u.y);
-        // origin (the eye), previous pdf, throughput and hash of a camera ray are
-        // constants that the bounce-1 kernels take from the camera themselves
-        qf_st(r, QDX, s, d.x); qf_st(r, QDY, s, d.y); qf_st(r, QDZ, s, d.z);
-        qu_st(r, QEXCL, s, 0xFFFFFFFFu);
-        qu_st(r, QQ, s, (uint32_t)qq);
-        qu_st(r, QC0, s, ctr.c0);
-        qu_st(r, QC1, s, ctr.c1);
-        qu_st(r, QVD, s, (uint32_t)v);
-        q.L[3 * (size_t)qq] = 0.0f; q.L[3 * (size_t)qq + 1] = 0.0f; q.L[3 * (size_t)qq + 2] = 0.0f;
-    }
+// Clears what the kernels of a pass count in; n: rays of the first bounce.
+__device__ __forceinline__ void clear_counters(const Queues& q, int n, int skip_set) {
+    const int stride = gridDim.x * blockDim.x, g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (g < 64) q.cnt[g] = g == 1 ? n : 0;
+    for (int j = g; j < TAKE_INTS; j += stride)
+        if (j / (TAKE_NC * 32) != skip_set) q.take[j] = 0;
+}
+__global__ void k_pass_begin(Queues q, int n) { clear_counters(q, n, -1); }
+
+// random counters, and with them camera direction, of path sample qq (processing
+// order) of view c
+__device__ __forceinline__ Ctr path_ctr(const FwdParams& p, const DevCam& c, long long qq) {
+    int x, y, j;
+    decode_path(c, qq - c.qoff, p.spp, x, y, j);
+    return Ctr{(uint32_t)(y * c.W + x), ((uint32_t)c.rngview << 16) | (uint32_t)j, 0u, 0u};
+}
+__device__ __forceinline__ V3 path_dir(const FwdParams& p, const DevCam& c, const Ctr& ctr, uint32_t scene_id) {
+    const float4 u = draw4(ctr, 0, 0, Key{p.seed, scene_id});
+    const uint32_t y = ctr.c0 / (uint32_t)c.W, x = ctr.c0 - y * (uint32_t)c.W;
+    return cam_dir(c, (float)(int)x + u.x, (float)(int)y + u.y);
 }
 
-// closest hit of queue entry i of bounce k.  ONE: the launch has one scene, whose
-// geometry is GW; else each ray looks its own up
+// closest hit of queue entry i of bounce k >= 2.  ONE: the launch has one scene,
+// whose geometry is GW; else each ray looks its own up
 template <bool FAST, bool ONE>
-__device__ __forceinline__ void extend_one(const FwdParams& p, const Queues& q, int k, float* const* r, int i,
-                                           const TraceGeo& GW, TravStack& st) {
-    const uint32_t view = k == 1 || !ONE ? qu_ld(r, QVD, i) & 0xFFFFu : 0u;
-    const DevScene& S = ONE ? p.scene : p.scenes[p.cams[view].scene];
-    const TraceGeo G = ONE ? GW : lane_geo(S);
-    const V3 o = k == 1 ? ld3(p.cams[view].eye) : V3{qf(r, QOX, i), qf(r, QOY, i), qf(r, QOZ, i)};
-    const V3 d{qf(r, QDX, i), qf(r, QDY, i), qf(r, QDZ, i)};
-    uint32_t ex = qu_ld(r, QEXCL, i);
-    float t0 = __int_as_float(0x7f800000);
-    int f0 = -1;
-    if (k == 1 && ex != 0xFFFFFFFFu) {
-        // a primary-edge side ray names its edge: the edge's faces are
-        // tested first, so that the traversal starts with their hit
-        const int4 E = S.edges[ex & 0x7FFFFFFFu];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int fe = j == 0 ? E.z : E.w;
-            float th; int fh;
-            if (fe >= 0 && tri_test<true>(tri_at(G.tri, (uint32_t)S.fleaf[fe]), o, d, TMIN, __int_as_float(0x7f800000),
-                                          th, fh) &&
-                (th < t0 || (th == t0 && fh < f0))) {
-                t0 = th;
-                f0 = fh;
-            }
-        }
-        ex = 0xFFFFFFFFu;
-    }
+__device__ __forceinline__ void extend_one(const FwdParams& p, const Queues& q, float* const* r, int i, const TraceGeo& GW,
+                                           TravStack& st) {
+    const TraceGeo G = ONE ? GW : lane_geo(p.scenes[p.cams[qu_ld(r, QVD, i) & 0xFFFFu].scene]);
+    const V3 o{qf(r, QOX, i), qf(r, QOY, i), qf(r, QOZ, i)}, d{qf(r, QDX, i), qf(r, QDY, i), qf(r, QDZ, i)};
     float t;
-    const int f = trace_closest<FAST>(G, o, d, TMIN, (int)ex, t, st, t0, f0);
+    const int f = trace_closest<FAST>(G, o, d, TMIN, (int)qu_ld(r, QEXCL, i), t, st);
     qst(q.ht + i, t);
     qst(q.hf + i, f);
 }
 
-// closest hit for every queued ray of bounce k (queue k & 1): 64 consecutive
-// queue entries per wave, traced in lockstep
-template <bool FAST, bool ONE>
-__global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_extend(FwdParams p, Queues q, int k) {
+// Closest hits of the first bounce, 64 consecutive rays per wave, traced in lockstep.
+// Camera rays (SIDE false; path samples q0 .. q0 + n - 1) are made here from their
+// index: a ray that misses, as most do around a small object, is never written; one
+// that hits leaves its direction for k_shade.  Before, a kernel of its own wrote 40
+// bytes a ray (0.22 of 5.1 ms for a 1024^2 view at 32 spp) that two kernels read back.
+// Side rays come from the queue; each names its edge, whose faces are tested first,
+// so that the traversal starts with their hit.
+template <bool FAST, bool ONE, bool SIDE>
+__global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_extend(FwdParams p, Queues q, long long q0, int n_cam) {
     __shared__ uint32_t lds[LDS_STACK * TRACE_BLOCK];
     TravStack st = make_trav_stack(lds, q.spill, p.err, p.work ? p.work + 3 * WORK_EXTEND : nullptr);
-    const TraceGeo G = wave_geo(p.scene);
-    const int n = q.cnt[k];
-    float* const* r = q.ray[k & 1];
-    wave_tiles(q.take + TAKE_NC * 32 * k, (uint32_t)n, [&](uint32_t t) {
-        const int i = (int)(t + __lane_id());
-        if (i < n) extend_one<FAST, ONE>(p, q, k, r, i, G, st);
+    const TraceGeo GW = wave_geo(p.scene);
+    float* const* r = q.ray[1];
+    const int n = SIDE ? q.cnt[1] : n_cam;
+    if (!SIDE) {
+        // counters of the launches after this one (its own were cleared before it
+        // when it needs them)
+        clear_counters(q, n, 1);
+        // the hit records are rewritten from here on: their key is cleared until k_film
+        if (q0 == 0 && blockIdx.x == 0 && threadIdx.x == 0 && p.rec_key_dev) *p.rec_key_dev = 0ull;
+    }
+    wave_tiles(q.take + TAKE_NC * 32, (uint32_t)n, [&](uint32_t tile) {
+        const int i = (int)(tile + __lane_id());
+        if (i >= n) return;
+        float t0 = __int_as_float(0x7f800000);
+        int f0 = -1;
+        V3 o, d;
+        TraceGeo G = GW;
+        if (SIDE) {
+            const DevScene& S = p.scene;                // a backward has one scene
+            o = ld3(p.cams[qu_ld(r, QVD, i) & 0xFFFFu].eye);
+            d = V3{qf(r, QDX, i), qf(r, QDY, i), qf(r, QDZ, i)};
+            const int4 E = S.edges[qu_ld(r, QEXCL, i) & 0x7FFFFFFFu];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int fe = j == 0 ? E.z : E.w;
+                float th; int fh;
+                if (fe >= 0 && tri_test<true>(tri_at(G.tri, (uint32_t)S.fleaf[fe]), o, d, TMIN, __int_as_float(0x7f800000),
+                                              th, fh) &&
+                    (th < t0 || (th == t0 && fh < f0))) {
+                    t0 = th;
+                    f0 = fh;
+                }
+            }
+        } else {
+            const int v = find_view_from(p.qoff, p.ncam, find_view(p.qoff, p.ncam, q0 + tile), q0 + i);
+            const DevCam& c = p.cams[v];
+            const DevScene& S = ONE ? p.scene : p.scenes[c.scene];
+            if (!ONE) G = lane_geo(S);
+            o = ld3(c.eye);
+            d = path_dir(p, c, path_ctr(p, c, q0 + i), S.scene_id);
+        }
+        float t;
+        const int f = trace_closest<FAST>(G, o, d, TMIN, -1, t, st, t0, f0);
+        qst(q.ht + i, t);
+        qst(q.hf + i, f);
+        if (!SIDE && f >= 0) {
+            qf_st(r, QDX, i, d.x); qf_st(r, QDY, i, d.y); qf_st(r, QDZ, i, d.z);
+        }
     });
 }
 
-#ifndef ST_PAIR_TRACE
-#define ST_PAIR_TRACE 1
-#endif
 // With one shadow entry per shading point and no decision hashes, k_shadow adds
 // each unoccluded contribution itself and records occlusion in the hit records,
 // and k_shadow_sum is not launched (the sum over one entry is that entry).
@@ -138,9 +151,11 @@ __host__ __device__ __forceinline__ bool shadow_fused(const FwdParams& p, const 
 // shading of bounce k: escapes, next-event set-up and BRDF continuation.
 // HASH: decision hashes are asked for (p.dbg_hash or p.hash_by_q); compiled
 // apart, because the hash state alone made the compiler spill 11 more dwords.
-// ONE: the launch has one scene.
-template <bool HASH, bool ONE>
-__global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Queues q, int k) {
+// ONE: the launch has one scene.  FROM: where the entries come from: later bounces
+// (k >= 2), camera rays or side rays (k == 1).
+enum { FROM_LATER, FROM_CAMERA, FROM_SIDE };
+template <bool HASH, bool ONE, int FROM>
+__global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Queues q, int k, long long q0) {
     __shared__ int resv[2 * (SHADE_BLOCK / 64 + 1)];
     const int n = q.cnt[k];
     float* const* r = q.ray[k & 1];
@@ -164,22 +179,59 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
         // path identity (slot, counters, camera | domain), carried to the continuation
         uint32_t pq = 0, c0 = 0, c1 = 0, vd = 0;
         if (active) {
-            pq = qu_ld(r, QQ, i);
-            c0 = qu_ld(r, QC0, i);
-            c1 = qu_ld(r, QC1, i);
-            vd = qu_ld(r, QVD, i);
+            // an entry's words are asked for together, one trip to memory before the
+            // gathers; of a first-bounce entry, the hit alone: most of them are misses
+            f = qld(q.hf + i);
+            float ht = 0.0f;
+            V3 o{0.f, 0.f, 0.f}, d{0.f, 0.f, 0.f};
+            beta = V3{1.f, 1.f, 1.f};
+            if (FROM == FROM_LATER) {
+                pq = qu_ld(r, QQ, i);
+                c0 = qu_ld(r, QC0, i);
+                c1 = qu_ld(r, QC1, i);
+                vd = qu_ld(r, QVD, i);
+                ht = qld(q.ht + i);
+                d = V3{qf(r, QDX, i), qf(r, QDY, i), qf(r, QDZ, i)};
+                beta = V3{qf(r, QBR, i), qf(r, QBG, i), qf(r, QBB, i)};
+            }
+            if (FROM == FROM_CAMERA) {
+                pq = (uint32_t)(q0 + i);
+                float* L = q.L + 3 * (size_t)pq;
+                L[0] = 0.0f; L[1] = 0.0f; L[2] = 0.0f;
+            }
+            if (FROM == FROM_LATER ? true : f >= 0 || hashing) {
+                if (FROM == FROM_CAMERA) {
+                    const int v = find_view_from(p.qoff, p.ncam, find_view(p.qoff, p.ncam, q0 + b0), q0 + i);
+                    const Ctr cc = path_ctr(p, p.cams[v], q0 + i);
+                    c0 = cc.c0;
+                    c1 = cc.c1;
+                    vd = (uint32_t)v;
+                    // for the shadow kernels and the hashes of this bounce
+                    qu_st(r, QQ, i, pq);
+                    qu_st(r, QVD, i, vd);
+                    if (hashing) { qu_st(r, QC0, i, c0); qu_st(r, QC1, i, c1); }
+                }
+                if (FROM == FROM_SIDE) {
+                    pq = qu_ld(r, QQ, i);
+                    c0 = qu_ld(r, QC0, i);
+                    c1 = qu_ld(r, QC1, i);
+                    vd = qu_ld(r, QVD, i);
+                }
+                if (FROM != FROM_LATER && f >= 0) {
+                    ht = qld(q.ht + i);
+                    d = V3{qf(r, QDX, i), qf(r, QDY, i), qf(r, QDZ, i)};
+                }
+            }
             const DevScene& S = ONE ? p.scene : p.scenes[p.cams[vd & 0xFFFFu].scene];
             const Key key{p.seed, S.scene_id};
             const Ctr ctr{c0, c1, 0u, vd >> 16};
-            Hash h{hashing ? (k == 1 ? FNV_INIT : qu_ld(r, QHASH, i)) : 0u, hashing};
-            beta = k == 1 ? V3{1.f, 1.f, 1.f} : V3{qf(r, QBR, i), qf(r, QBG, i), qf(r, QBB, i)};
-            f = qld(q.hf + i);
+            Hash h{hashing ? (FROM != FROM_LATER ? FNV_INIT : qu_ld(r, QHASH, i)) : 0u, hashing};
             push_face(h, f);
-            if (p.rec_face && (vd >> 16) == 0u) qst(p.rec_face + (size_t)(k - 1) * p.rec_n + pq, f);
+            // (the records belong to main paths: side paths come without them)
+            if (FROM != FROM_SIDE && p.rec_face) qst(p.rec_face + (size_t)(k - 1) * p.rec_n + pq, f);
             if (!fused) q.sface[i] = -1;
-            const V3 d{qf(r, QDX, i), qf(r, QDY, i), qf(r, QDZ, i)};
             if (f < 0) {
-                if (S.has_env && k > 1) {
+                if (S.has_env && FROM == FROM_LATER) {
                     const int tex = env_texel_of(S, d);
                     h.push((uint32_t)tex);
                     const float pp = qf(r, QPPREV, i);
@@ -191,21 +243,22 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                 if (hashing) final_hash(p, r, i, h.h);
             } else if (k > p.B) {
                 if (hashing) final_hash(p, r, i, h.h);
-            } else if (k == 1 && (vd >> 16) == 1u && qld(q.hf + (i ^ 1)) == f) {
+            } else if (FROM == FROM_SIDE && qld(q.hf + (i ^ 1)) == f) {
                 // the two side rays of a primary edge sample (queue slots 2j and
                 // 2j + 1 at bounce 1) met the same face first: the edge point is
                 // hidden behind it, there is no jump to measure, and both side
                 // paths end here with zero radiance
                 if (hashing) final_hash(p, r, i, h.h);
             } else {
-                const V3 o = k == 1 ? ld3(p.cams[vd & 0xFFFFu].eye) : V3{qf(r, QOX, i), qf(r, QOY, i), qf(r, QOZ, i)};
-                x = o + d * qld(q.ht + i);
+                o = FROM != FROM_LATER ? ld3(p.cams[vd & 0xFFFFu].eye) : V3{qf(r, QOX, i), qf(r, QOY, i), qf(r, QOZ, i)};
+                x = o + d * ht;
                 V3 n = xyz(S.fnorm[f]);
                 const V3 wo = -d;
                 if (dot(n, wo) < 0.0f) n = -n;
                 const int tx = texel_of(S, f, x);
                 if (S.tex_res) h.push((uint32_t)tx);
                 const Mat m = load_mat(S.mat + 7 * (size_t)tx);
+                const float lo = out_lambda(wo, n, m);
                 for (int l = 0; l < S.nl; ++l) {
                     const auto lt = S.lights + 6 * l;
                     const V3 dl = ld3(lt) - x;
@@ -218,7 +271,7 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                         const float c = dot(n, wl);
                         if (c > 0.0f) {
                             tmax = rr * (1.0f - SHADOW_SHRINK);
-                            ct = mul(beta, mul(ld3(lt + 3), brdf_eval(wl, wo, n, m))) * (c / r2);
+                            ct = mul(beta, mul(ld3(lt + 3), brdf_eval(wl, wo, n, m, lo))) * (c / r2);
                         }
                     }
                     // an entry is read only when it carries a ray (listed for k_shadow;
@@ -243,7 +296,7 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                     if (c > 0.0f && pe > 0.0f) {
                         tmax = __int_as_float(0x7f800000);
                         const float den = pe + bsdf_pdf(we, wo, n, m.a, S.vndf);
-                        ct = mul(beta, mul(env_rgb(S, tex), brdf_eval(we, wo, n, m))) * (c / den);
+                        ct = mul(beta, mul(env_rgb(S, tex), brdf_eval(we, wo, n, m, lo))) * (c / den);
                     }
                     const size_t e = (size_t)S.nl * q.cap + i;
                     if (tmax >= 0.0f) {
@@ -264,7 +317,7 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                     if (ci > 0.0f && pb > 0.0f) {
                         info |= 4u;
                         emit = true;
-                        beta = mul(beta, brdf_eval(wi, wo, n, m)) * (ci / pb);
+                        beta = mul(beta, brdf_eval(wi, wo, n, m, lo)) * (ci / pb);
                     }
                 }
                 // the shading record: the shadow rays' origin and excluded face (fused:
@@ -274,7 +327,7 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                     qst(q.sx[0] + i, x.x); qst(q.sx[1] + i, x.y); qst(q.sx[2] + i, x.z);
                 }
                 if (!fused) q.sinfo[i] = info;
-                if (shadow_fused(p, q) && p.rec_occ && (vd >> 16) == 0u)
+                if (fused && FROM != FROM_SIDE && p.rec_occ)
                     p.rec_occ[(size_t)(k - 1) * p.rec_n + pq] = 0u;
                 if (!fused) q.stex[i] = tex;
                 if (!fused) q.snext[i] = -1;
@@ -321,7 +374,7 @@ template <bool FAST, bool ONE>
 __device__ __forceinline__ void shadow_one(const FwdParams& p, const Queues& q, int k, float* const* r, int w,
                                            bool fused, const TraceGeo& GW, TravStack& st) {
     const uint32_t e = qld(q.slist + w);
-    const int i = (int)(e % (uint32_t)q.cap);
+    const int i = (int)(fused ? e : e % (uint32_t)q.cap);      // (fused: one entry per shading point)
     const int f = qld(q.sface + i);
     const TraceGeo G = ONE ? GW : lane_geo(p.scenes[p.cams[qu_ld(r, QVD, i) & 0xFFFFu].scene]);
     const float tmax = qld(q.sh[3] + e);
@@ -329,7 +382,7 @@ __device__ __forceinline__ void shadow_one(const FwdParams& p, const Queues& q, 
     const bool occluded = trace_any<FAST>(G, o, dd, TMIN, tmax, f, st);
     if (fused) {
         if (occluded) {
-            if (p.rec_occ && (qu_ld(r, QVD, i) >> 16) == 0u) p.rec_occ[(size_t)(k - 1) * p.rec_n + qu_ld(r, QQ, i)] = 1u;
+            if (p.rec_occ) p.rec_occ[(size_t)(k - 1) * p.rec_n + qu_ld(r, QQ, i)] = 1u;
         } else {
             float* L = q.L + 3 * (size_t)qu_ld(r, QQ, i);
             L[0] += qld(q.sh[4] + e); L[1] += qld(q.sh[5] + e); L[2] += qld(q.sh[6] + e);
@@ -390,7 +443,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_trace_pair(FwdParams
             }
         } else if (i < all) {
             st.work = wext;
-            extend_one<FAST, ONE>(p, q, k + 1, rn, (int)(i - s64), G, st);
+            extend_one<FAST, ONE>(p, q, rn, (int)(i - s64), G, st);
         }
     });
 }
@@ -418,7 +471,7 @@ __global__ void k_shadow_sum(FwdParams p, Queues q, int k) {
             if (code == 1u) occ |= 1u << l;
             h.push(code);
         }
-        if (p.rec_occ && (qu(r, QVD, i) >> 16) == 0u) p.rec_occ[(size_t)(k - 1) * p.rec_n + qu(r, QQ, i)] = occ;
+        if (p.rec_occ) p.rec_occ[(size_t)(k - 1) * p.rec_n + qu(r, QQ, i)] = occ;
         const uint32_t info = q.sinfo[i];
         if (info & 1u) {
             h.push((info >> 1) & 1u);
@@ -545,47 +598,50 @@ void launch_forward_wavefront(const FwdParams& p, Queues& q, long long total, in
     q.nent = nent;
     for (long long q0 = 0; q0 < total; q0 += q.cap) {
         const int n = (int)((total - q0) < q.cap ? (total - q0) : q.cap);
-        ST_LAUNCH("k_camera", k_camera, dim3(grid_for(n, 256, 1u << 20)), dim3(256), 0, st, p, q, q0, n);
-        launch_wavefront_bounces(p, q, n, has_env_any, st);
+        launch_wavefront_bounces(p, q, n, q0, has_env_any, st);
     }
 }
 
-// extension / shading / shadow kernels of every bounce for a chunk whose first
-// ray queue (queue 1) and count cnt[1] have been filled; n bounds the count
-void launch_wavefront_bounces(const FwdParams& p, Queues& q, int n, int has_env_any, hipStream_t st,
+// Extension / shading / shadow kernels of every bounce for a chunk of n camera rays,
+// path samples q0 .. q0 + n - 1, or (q0 < 0) of the side rays that fill queue 1 and
+// whose count in cnt[1] n bounds (the counters cleared before).
+void launch_wavefront_bounces(const FwdParams& p, Queues& q, int n, long long q0, int has_env_any, hipStream_t st,
                               LaunchHook* hook) {
     const unsigned gmax = (q.grid > 0 && (unsigned)q.grid < TRACE_GRID) ? (unsigned)q.grid : TRACE_GRID;
     const unsigned g = grid_for(n, TRACE_BLOCK, gmax);
     const int last = p.B + (has_env_any ? 1 : 0);
-    const bool fused = shadow_fused(p, q);
+    const bool fused = shadow_fused(p, q), side = q0 < 0;
     const bool one = p.fast && p.nscenes == 1, hashing = p.dbg_hash || p.hash_by_q;
-    const auto shade = p.nscenes == 1 ? (hashing ? k_shade<true, true> : k_shade<false, true>)
-                                      : (hashing ? k_shade<true, false> : k_shade<false, false>);
-    const auto extend = one ? k_extend<true, true> : p.fast ? k_extend<true, false> : k_extend<false, false>;
+    using Shade = void (*)(FwdParams, Queues, int, long long);
+    constexpr Shade shades[2][2][3] = {      // [hashing][one scene][from]
+        {{k_shade<false, false, FROM_LATER>, k_shade<false, false, FROM_CAMERA>, nullptr},
+         {k_shade<false, true, FROM_LATER>, k_shade<false, true, FROM_CAMERA>, k_shade<false, true, FROM_SIDE>}},
+        {{k_shade<true, false, FROM_LATER>, k_shade<true, false, FROM_CAMERA>, nullptr},
+         {k_shade<true, true, FROM_LATER>, k_shade<true, true, FROM_CAMERA>, k_shade<true, true, FROM_SIDE>}}};
+    const auto extend = side ? (p.fast ? k_extend<true, true, true> : k_extend<false, true, true>)
+                        : one ? k_extend<true, true, false>
+                        : p.fast ? k_extend<true, false, false> : k_extend<false, false, false>;
     const auto shadow_rays = one ? k_shadow<true, true> : p.fast ? k_shadow<true, false> : k_shadow<false, false>;
     const auto pair = one ? k_trace_pair<true, true> : p.fast ? k_trace_pair<true, false> : k_trace_pair<false, false>;
-    ST_LAUNCH("k_extend", extend, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, 1);
+    // (only a launch with more tiles than waves takes from its counters)
+    if (!side && (unsigned)((n + 63) / 64) > g * (TRACE_BLOCK / 64))
+        ST_LAUNCH("k_pass_begin", k_pass_begin, dim3(TAKE_INTS / 256), dim3(256), 0, st, q, n);
+    ST_LAUNCH("k_extend", extend, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, q0, n);
     if (hook) hook->tick();
     for (int k = 1; k <= last; ++k) {
         // bounce k is traced: shade it, then trace its shadow rays together with
         // the extension rays of bounce k + 1
-        ST_LAUNCH("k_shade", shade, dim3(grid_for(n, SHADE_BLOCK, gmax)), dim3(SHADE_BLOCK), 0, st, p, q, k);
+        ST_LAUNCH("k_shade", shades[hashing][p.nscenes == 1][k > 1 ? FROM_LATER : side ? FROM_SIDE : FROM_CAMERA],
+                  dim3(grid_for(n, SHADE_BLOCK, gmax)), dim3(SHADE_BLOCK), 0, st, p, q, k, q0);
         if (hook) hook->tick();
-        const bool shadow = k <= p.B, next = k < last;
-        if (ST_PAIR_TRACE && shadow && next) {
+        if (k <= p.B && k < last) {
             ST_LAUNCH("k_trace_pair", pair, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, k);
             if (hook) hook->tick();
-        } else {
-            if (shadow) {
-                ST_LAUNCH("k_shadow", shadow_rays, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, k);
-                if (hook) hook->tick();
-            }
-            if (next) {
-                ST_LAUNCH("k_extend", extend, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, k + 1);
-                if (hook) hook->tick();
-            }
+        } else if (k <= p.B) {
+            ST_LAUNCH("k_shadow", shadow_rays, dim3(g), dim3(TRACE_BLOCK), 0, st, p, q, k);
+            if (hook) hook->tick();
         }
-        if (shadow && !fused)
+        if (k <= p.B && !fused)
             ST_LAUNCH("k_shadow_sum", k_shadow_sum, dim3(grid_for(n, 256, gmax)), dim3(256), 0, st, p, q, k);
     }
 }
