@@ -729,12 +729,44 @@ __global__ void __launch_bounds__(EDGE_CAM_BLOCK) k_edge_camera(BwdParams p, Que
     }
 }
 
-// sum of v over the lanes of the wave whose flag is set (every lane takes part)
-__device__ __forceinline__ double wave_sum_masked(bool in, double v) {
-    double s = in ? v : 0.0;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+// v of another lane by a DPP move (0 where the pattern has no lane, or ROWS leaves a row out)
+template <int CTRL, int ROWS> __device__ __forceinline__ float dpp_or_zero(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, false));
+}
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_or_zero(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false));
+}
+
+// Sum of v over the lanes of the wave whose flag is set, in lane 63 (every lane takes
+// part): row shifts by 1, 2, 4, 8 sum each row of 16, two row broadcasts sum the rows.
+// Moves within the vector ALU: the butterfly over ds_bpermute that it replaces waits
+// for an LDS round trip at each of its six steps.
+template <class T> __device__ __forceinline__ T wave_sum_masked(bool in, T v) {
+    T s = in ? v : T(0);
+    s += dpp_or_zero<0x111, 0xf>(s);      // row_shr:1
+    s += dpp_or_zero<0x112, 0xf>(s);      // row_shr:2
+    s += dpp_or_zero<0x114, 0xf>(s);      // row_shr:4
+    s += dpp_or_zero<0x118, 0xf>(s);      // row_shr:8
+    s += dpp_or_zero<0x142, 0xa>(s);      // row_bcast:15 into rows 1 and 3
+    s += dpp_or_zero<0x143, 0xc>(s);      // row_bcast:31 into rows 2 and 3
     return s;
+}
+
+// Calls fn(key, in) once for each different key of the lanes that have one, with the
+// whole wave converged; `in` marks the lanes of that key.
+template <class Fn> __device__ __forceinline__ void for_keys(bool has, long long key, Fn fn) {
+    bool pending = has;
+    for (;;) {
+        const uint64_t m = __ballot(pending);
+        if (!m) break;
+        const int leader = __ffsll((long long)m) - 1;
+        const long long k = ((long long)__builtin_amdgcn_readlane((int)(key >> 32), leader) << 32) |
+                            (unsigned int)__builtin_amdgcn_readlane((int)(key & 0xFFFFFFFFll), leader);
+        const bool mine = pending && key == k;
+        fn(k, mine);
+        pending = pending && !mine;
+    }
 }
 
 __global__ void k_edge_grad(BwdParams p, const float* __restrict__ Ls, const uint32_t* __restrict__ hs,
@@ -783,22 +815,14 @@ __global__ void k_edge_grad(BwdParams p, const float* __restrict__ Ls, const uin
         // the two endpoint weights are summed per (view, edge) here and applied once in
         // k_edge_finish; lanes of a wave that share a (view, edge) (consecutive
         // stratified samples mostly do) are summed first, one atomic pair per group
-        bool pending = has;
-        for (;;) {
-            const uint64_t m = __ballot(pending);
-            if (!m) break;
-            const int leader = __ffsll((long long)m) - 1;
-            const long long lk = ((long long)__builtin_amdgcn_readlane((int)(key >> 32), leader) << 32) |
-                                 (unsigned int)__builtin_amdgcn_readlane((int)(key & 0xFFFFFFFFll), leader);
-            const bool mine = pending && key == lk;
+        for_keys(has, key, [&](long long k, bool mine) {
             const double s0 = wave_sum_masked(mine, a0), s1 = wave_sum_masked(mine, a1);
-            if (lane == leader) {
-                double* acc = p.pacc + 2 * (size_t)lk;
+            if (lane == 63) {
+                double* acc = p.pacc + 2 * (size_t)k;
                 atomicAdd(acc, s0);
                 atomicAdd(acc + 1, s1);
             }
-            pending = pending && !mine;
-        }
+        });
     }
 }
 
@@ -940,11 +964,18 @@ __device__ __forceinline__ void project_jac(const DevCam& c, const double z[3], 
     }
 }
 
+// what one sample adds to dV: to the edge's ends and to the receiver face's vertices
+struct ShadowGrad {
+    int e, f;
+    float gv[5][3];
+};
+
+// false: the sample adds nothing
 template <bool FAST>
-__device__ void shadow_edge_one(const BwdParams& p, const DevScene& S, const DevCam& c, int v, int l, long long si,
-                                long long nsv, Hash& h, TravStack& st) {
+__device__ bool shadow_edge_one(const BwdParams& p, const DevScene& S, const DevCam& c, int v, int l, long long si,
+                                long long nsv, Hash& h, TravStack& st, ShadowGrad& out) {
 #pragma clang fp contract(off)
-    if (!(p.ltotal[l] > 0.0)) return;
+    if (!(p.ltotal[l] > 0.0)) return false;
     const Ctr ctr{(uint32_t)si, ((uint32_t)c.rngview << 16) | (uint32_t)l, 0u, 3u};
     const float4 u = draw4(ctr, 0, 3, Key{p.seed, S.scene_id});
     // stratified over the nsv samples of the (view, light) pair
@@ -961,14 +992,14 @@ __device__ void shadow_edge_one(const BwdParams& p, const DevScene& S, const Dev
     const TraceGeo G = wave_geo(S);
     const int fr = trace_closest<FAST>(G, y, w, TMIN, E.z, tr, st);
     h.push(fr < 0 ? 0xFFFFFFFFu : (uint32_t)fr);
-    if (fr < 0 || fr == E.w) return;
+    if (fr < 0 || fr == E.w) return false;
     const V3 zt = y + w * tr;
     const V3 eye = ld3(c.eye);
     float tc;
     const int fc = trace_closest<FAST>(G, eye, normalize(zt - eye), TMIN, -1, tc, st);
     const bool vis = fc == fr;
     h.push(vis ? 2u : 1u);
-    if (!vis) return;
+    if (!vis) return false;
     // receiver point on the plane of fr along the light ray through y (fp64)
     double Nr[3], r0[3];
     face_N_d(S, fr, Nr, r0);
@@ -983,9 +1014,9 @@ __device__ void shadow_edge_one(const BwdParams& p, const DevScene& S, const Dev
     const int px = (int)floor(xs), py = (int)floor(ys);
     const bool inside = depth > ZNEAR && xs >= 0.0 && ys >= 0.0 && px < c.W && py < c.H;
     h.push(inside ? 1u : 0u);
-    if (!inside) return;
+    if (!inside) return false;
     const float* di = p.d_image + 3 * (c.pixoff + (long long)py * c.W + px);
-    if (di[0] == 0.0f && di[1] == 0.0f && di[2] == 0.0f) return;
+    if (di[0] == 0.0f && di[1] == 0.0f && di[2] == 0.0f) return false;
     // tau = ds/dt = J (dz/dy)(vb - va), dz/dy d = lam (d - D (Nr . d) / Bd)
     const double ed[3] = {(double)vb.x - (double)va.x, (double)vb.y - (double)va.y, (double)vb.z - (double)va.z};
     const double ne_ = (Nr[0] * ed[0] + Nr[1] * ed[1] + Nr[2] * ed[2]) / Bd;
@@ -994,7 +1025,7 @@ __device__ void shadow_edge_one(const BwdParams& p, const DevScene& S, const Dev
     const double tx = jx[0] * dz[0] + jx[1] * dz[1] + jx[2] * dz[2];
     const double ty = jy[0] * dz[0] + jy[1] * dz[1] + jy[2] * dz[2];
     const double tl = sqrt(tx * tx + ty * ty);
-    if (!(tl > 0.0)) return;
+    if (!(tl > 0.0)) return false;
     const double nx = -ty / tl, ny = tx / tl;
     // light visibility on both sides, at the receiver plane under the side points
     int vsd[2];
@@ -1017,7 +1048,7 @@ __device__ void shadow_edge_one(const BwdParams& p, const DevScene& S, const Dev
         vsd[side] = trace_any<FAST>(G, zf, wf, TMIN, (float)(r * (1.0 - (double)SHADOW_SHRINK)), fr, st) ? 0 : 1;
         h.push((uint32_t)vsd[side]);
     }
-    if (vsd[0] == vsd[1]) return;
+    if (vsd[0] == vsd[1]) return false;
     // unshadowed radiance of the light at z toward the camera
     const V3 zf{(float)z[0], (float)z[1], (float)z[2]};
     const V3 wo = normalize(eye - zt);
@@ -1027,7 +1058,7 @@ __device__ void shadow_edge_one(const BwdParams& p, const DevScene& S, const Dev
     const float r2 = dot(dl, dl);
     const V3 wl = dl * (1.0f / sqrtf(r2));
     const float cl = dot(n, wl);
-    if (!(cl > 0.0f)) return;
+    if (!(cl > 0.0f)) return false;
     const Mat m = load_mat(S.mat + 7 * (size_t)texel_of(S, fr, zf));
     const V3 fv = brdf_eval(wl, wo, n, m);
     const V3 I = ld3(lt + 3);
@@ -1052,39 +1083,82 @@ __device__ void shadow_edge_one(const BwdParams& p, const DevScene& S, const Dev
     const double ge1[3] = {e2[1] * gN[2] - e2[2] * gN[1], e2[2] * gN[0] - e2[0] * gN[2], e2[0] * gN[1] - e2[1] * gN[0]};
     const double ge2[3] = {gN[1] * e1[2] - gN[2] * e1[1], gN[2] * e1[0] - gN[0] * e1[2], gN[0] * e1[1] - gN[1] * e1[0]};
     const float tt = t;
-    atomic_add3(p.dV + 3 * (size_t)E.x, V3{(float)(gy[0] * (1.0 - tt)), (float)(gy[1] * (1.0 - tt)),
-                                           (float)(gy[2] * (1.0 - tt))});
-    atomic_add3(p.dV + 3 * (size_t)E.y, V3{(float)(gy[0] * tt), (float)(gy[1] * tt), (float)(gy[2] * tt)});
-    atomic_add3(p.dV + 3 * (size_t)i0, V3{(float)(gr0[0] - ge1[0] - ge2[0]), (float)(gr0[1] - ge1[1] - ge2[1]),
-                                          (float)(gr0[2] - ge1[2] - ge2[2])});
-    atomic_add3(p.dV + 3 * (size_t)i1, V3{(float)ge1[0], (float)ge1[1], (float)ge1[2]});
-    atomic_add3(p.dV + 3 * (size_t)i2, V3{(float)ge2[0], (float)ge2[1], (float)ge2[2]});
+    out.e = e;
+    out.f = fr;
+    for (int k = 0; k < 3; ++k) {
+        out.gv[0][k] = (float)(gy[k] * (1.0 - tt));
+        out.gv[1][k] = (float)(gy[k] * tt);
+        out.gv[2][k] = (float)(gr0[k] - ge1[k] - ge2[k]);
+        out.gv[3][k] = (float)ge1[k];
+        out.gv[4][k] = (float)ge2[k];
+    }
+    return true;
 }
 
-// one thread per shadow-edge sample; sample gs of (view v, light l, index i) is
-// nl eoff[v] + l N_e(v) + i, and its hash / mask slot follows the primary edge samples
+// sum over the marked lanes of a vertex's gradient, added by one lane
+__device__ __forceinline__ void add_sum3(float* dV, int vert, bool mine, const float* g, int lane) {
+    const V3 s{wave_sum_masked(mine, g[0]), wave_sum_masked(mine, g[1]), wave_sum_masked(mine, g[2])};
+    if (lane == 63) atomic_add3(dV + 3 * (size_t)vert, s);
+}
+
+// sample gs of (view v, light l, index i) is nl eoff[v] + l N_e(v) + i
 template <bool FAST>
-__global__ void __launch_bounds__(TRACE_BLOCK) k_shadow_edges(BwdParams p, long long total_edges, long long nsh) {
+__device__ __forceinline__ bool shadow_edge_sample(const BwdParams& p, const DevScene& S, long long total_edges,
+                                                   long long gs, TravStack& st, ShadowGrad& g) {
+    const long long nl = S.nl;
+    int lo = 0, hi = p.ncam - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (nl * p.eoff[mid] <= gs) lo = mid; else hi = mid - 1;
+    }
+    const DevCam& c = p.cams[lo];
+    const long long nsv = p.eoff[lo + 1] - p.eoff[lo];
+    const long long rem = gs - nl * p.eoff[lo];
+    const int l = (int)(rem / nsv);
+    const long long si = rem - (long long)l * nsv;
+    Hash h{FNV_INIT, p.dbg_edge_hash != nullptr};
+    const bool has = shadow_edge_one<FAST>(p, S, c, lo, l, si, nsv, h, st, g);
+    if (p.dbg_edge_hash) p.dbg_edge_hash[total_edges + gs] = h.h;
+    return has;
+}
+
+// One thread per shadow-edge sample; its hash / mask slot follows the primary edge
+// samples.  Bound by the light rays' traversal (half of the time).  Four waves per SIMD:
+// the fp64 tail alone would take 174 registers and leave room for two, and few lanes
+// reach it (3.5M samples over 9,680 faces: 1,473 us at two waves, 1,235 at four, 1,298
+// at six).  The tail's 15 atomics per sample, mostly of a whole wave on the same
+// vertices, took 350 us of that; summed in the wave first the kernel takes 948 us.
+#ifndef ST_SE_WAVES
+#define ST_SE_WAVES 4
+#endif
+template <bool FAST>
+__global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(ST_SE_WAVES)))
+k_shadow_edges(BwdParams p, long long total_edges, long long nsh) {
     __shared__ uint32_t lds[LDS_STACK * TRACE_BLOCK];
     TravStack st = make_trav_stack(lds, p.spill, p.err, nullptr);
     const DevScene& S = p.scene;
-    const long long nl = S.nl;
     const long long stride = (long long)gridDim.x * blockDim.x;
-    for (long long gs = blockIdx.x * (long long)blockDim.x + threadIdx.x; gs < nsh; gs += stride) {
-        int lo = 0, hi = p.ncam - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (nl * p.eoff[mid] <= gs) lo = mid; else hi = mid - 1;
-        }
-        const DevCam& c = p.cams[lo];
-        const long long nsv = p.eoff[lo + 1] - p.eoff[lo];
-        const long long rem = gs - nl * p.eoff[lo];
-        const int l = (int)(rem / nsv);
-        const long long si = rem - (long long)l * nsv;
-        if (p.edge_mask && !p.edge_mask[total_edges + gs]) continue;
-        Hash h{FNV_INIT, p.dbg_edge_hash != nullptr};
-        shadow_edge_one<FAST>(p, S, c, lo, l, si, nsv, h, st);
-        if (p.dbg_edge_hash) p.dbg_edge_hash[total_edges + gs] = h.h;
+    const int lane = (int)(threadIdx.x & 63u);
+    // whole waves iterate together: the sums below need every lane
+    for (long long w0 = blockIdx.x * (long long)blockDim.x + (threadIdx.x & ~63u); w0 < nsh; w0 += stride) {
+        const long long gs = w0 + lane;
+        bool has = false;
+        ShadowGrad g{};
+        if (gs < nsh && !(p.edge_mask && !p.edge_mask[total_edges + gs]))
+            has = shadow_edge_sample<FAST>(p, S, total_edges, gs, st, g);
+        // consecutive samples of a (view, light) are stratified over the edges, so most
+        // lanes of a wave share the edge and a few receiver faces: their terms are summed
+        // first, and each distinct edge and face takes one set of atomics
+        for_keys(has, g.e, [&](long long e, bool mine) {
+            const int4 E = S.edges[e];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) add_sum3(p.dV, i == 0 ? E.x : E.y, mine, g.gv[i], lane);
+        });
+        for_keys(has, g.f, [&](long long f, bool mine) {
+            const int* F = S.F + 3 * f;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) add_sum3(p.dV, F[i], mine, g.gv[2 + i], lane);
+        });
     }
 }
 
