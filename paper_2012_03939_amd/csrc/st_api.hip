@@ -345,7 +345,7 @@ int queue_cap(long long cap, int nent) {
 // bytes of the queue workspace of a chunk of cap paths with nent shadow entries each
 size_t queue_bytes(int cap, int nent) {
     const size_t per = 256;
-    const size_t words = 2 * QNCOL + 2 + 3 + 4 + 8 * (size_t)std::max(nent, 1);
+    const size_t words = 2 * QNCOL + RNCOL + 8 * (size_t)std::max(nent, 1);
     return (size_t)cap * 4 * words + (size_t)cap * std::max(nent, 1) + (words + 10) * per + 64 * 4 +
            TAKE_INTS * sizeof(int);
 }
@@ -367,16 +367,11 @@ int ensure_spill(st_scene* sc) {
 // which holds queue_bytes(cap, nent) bytes
 void carve_queues(char* base, int cap, int nent, float* L, uint32_t* spill, Queues& q) {
     Carver c{base};
-    for (int b = 0; b < 2; ++b)
-        for (int i = 0; i < QNCOL; ++i) q.ray[b][i] = c.take<float>(cap);
-    q.ht = c.take<float>(cap);
-    q.hf = c.take<int>(cap);
-    for (int i = 0; i < 3; ++i) q.sx[i] = c.take<float>(cap);
-    q.sface = c.take<int>(cap);
-    q.sinfo = c.take<uint32_t>(cap);
-    q.stex = c.take<int>(cap);
-    q.snext = c.take<int>(cap);
-    for (int i = 0; i < 7; ++i) q.sh[i] = c.take<float>((size_t)cap * std::max(nent, 1));
+    // (queue_bytes counts whole columns, each with the slack that the last block of 64 needs)
+    auto blocks = [](size_t n) { return (n + 63) & ~(size_t)63; };
+    for (int b = 0; b < 2; ++b) q.ray[b] = c.take<uint32_t>(QNCOL * blocks(cap));
+    q.rec = c.take<uint32_t>(RNCOL * blocks(cap));
+    q.sh = c.take<uint32_t>(SNCOL * blocks((size_t)cap * std::max(nent, 1)));
     q.socc = c.take<uint8_t>((size_t)cap * std::max(nent, 1));
     q.slist = c.take<uint32_t>((size_t)cap * std::max(nent, 1));
     q.cnt = c.take<int>(64);
@@ -1002,7 +997,7 @@ int st_render_noalloc(st_scene* sc, const st_camera* cams, int32_t ncam, int32_t
     int cap = 0;
     if (!mega) {
         // the largest chunk whose queues fit the rest of the scratch
-        const size_t words = 2 * QNCOL + 2 + 3 + 4 + 8 * (size_t)std::max(nent, 1);
+        const size_t words = 2 * QNCOL + RNCOL + 8 * (size_t)std::max(nent, 1);
         const size_t per = 4 * words + (size_t)std::max(nent, 1), fixed = queue_bytes(0, nent);
         long long c = qroom > fixed ? (long long)((qroom - fixed) / per) : 0;
         c = std::min<long long>(c, std::max<long long>(ch.total_paths, 1));

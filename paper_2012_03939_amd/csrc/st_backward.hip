@@ -692,7 +692,6 @@ constexpr int EDGE_CAM_BLOCK = 1024;   // threads of a k_edge_camera block (one 
 __global__ void __launch_bounds__(EDGE_CAM_BLOCK) k_edge_camera(BwdParams p, Queues q, long long e0, int n) {
     __shared__ int resv[EDGE_CAM_BLOCK / 64 + 1];
     const int stride = gridDim.x * blockDim.x;
-    float* const* r = q.ray[1];
     for (int b0 = blockIdx.x * blockDim.x; b0 < n; b0 += stride) {
         const int i = b0 + (int)threadIdx.x;
         const long long ge = e0 + i;
@@ -715,15 +714,18 @@ __global__ void __launch_bounds__(EDGE_CAM_BLOCK) k_edge_camera(BwdParams p, Que
             const V3 d = side_dir(c, es, side);
             // (origin, previous pdf, throughput and hash of a camera ray are
             // taken from the camera by the bounce-1 kernels)
-            r[QDX][s] = d.x; r[QDY][s] = d.y; r[QDZ][s] = d.z;
+            const RayRow r(q.ray[1], s);
+            r.put(QDX, __float_as_uint(d.x));
+            r.put(QDY, __float_as_uint(d.y));
+            r.put(QDZ, __float_as_uint(d.z));
             // a camera ray excludes no face: the slot carries the sampled edge
             // (top bit set), whose faces the extension tests before traversing
-            qu(r, QEXCL, s) = 0x80000000u | (uint32_t)es.e;
+            r.put(QEXCL, 0x80000000u | (uint32_t)es.e);
             const uint32_t lq = (uint32_t)(2 * ge + side);
-            qu(r, QQ, s) = lq;
-            qu(r, QC0, s) = (uint32_t)es.si;
-            qu(r, QC1, s) = (uint32_t)c.rngview << 16;
-            qu(r, QVD, s) = (uint32_t)es.v | (1u << 16);
+            r.put(QQ, lq);
+            r.put(QC0, (uint32_t)es.si);
+            r.put(QC1, (uint32_t)c.rngview << 16);
+            r.put(QVD, (uint32_t)es.v | (1u << 16));
             q.L[3 * (size_t)lq] = 0.0f; q.L[3 * (size_t)lq + 1] = 0.0f; q.L[3 * (size_t)lq + 2] = 0.0f;
         }
     }

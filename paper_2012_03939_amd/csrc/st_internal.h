@@ -111,9 +111,17 @@ struct Workspace {
     void* base = nullptr;
 };
 
-// columns of a ray queue (SoA, one float-sized word each): the ray and the state
-// of the path it continues, copied along on compaction so that every kernel
-// reads its queue entries coalesced
+// Queues hold one 4-byte word per column and entry, in blocks of 64 entries: word
+// (entry i, column c) of a queue of N columns lies at ((i / 64) N + c) 64 + i % 64.
+// A wave's 64 entries of a column are 256 consecutive bytes, as in whole columns, but
+// a queue is one pointer and a column an immediate offset of the access (a row's
+// columns span at most 4 KB).  With a pointer for each of its 55 columns k_shade kept
+// more scalar registers than there are and moved them to vector lanes and back: 420 of
+// its 3,380 vector instructions, and a wait before each use (now 160 of 3,110; k_shade
+// 1.71 -> 1.61 ms for a 1024^2 view at 32 spp, 21.9 -> 20.8 ms in a 40k-face step).
+//
+// columns of a ray queue: the ray and the state of the path it continues, copied along
+// on compaction so that every kernel reads its queue entries coalesced
 enum QCol {
     QOX, QOY, QOZ, QDX, QDY, QDZ,   // ray origin, direction
     QEXCL,                          // face the ray leaves (int), -1 for camera rays
@@ -125,6 +133,21 @@ enum QCol {
     QHASH,                          // decision hash (debug outputs only)
     QNCOL
 };
+static_assert(QNCOL <= 16, "a row's columns must be within the immediate offsets");
+
+// columns of the records of a bounce's rays: the hit and the shading point
+enum RCol {
+    RT, RF,                         // hit distance, face (-1: none)
+    RX0, RX1, RX2,                  // shading point
+    RFACE,                          // its face, -1: no shadow rays
+    RINFO,                          // bit 0: continued, bit 1: lobe, bit 2: emitted
+    RTEX,                           // environment texel of its shadow ray
+    RNEXT,                          // index in the next queue, -1: none
+    RNCOL
+};
+
+// columns of a shadow entry (l * cap + i): direction, length, contribution
+enum SCol { SWX, SWY, SWZ, STMAX, SCR, SCG, SCB, SNCOL };
 
 // Counters from which the waves of a traversal kernel take their work (wave_tiles),
 // each on its own 128-byte line.
@@ -159,16 +182,10 @@ template <class Fn> __device__ __forceinline__ void wave_tiles(int* counters, ui
 
 // queue and path-state arrays of one wavefront chunk (SoA)
 struct Queues {
-    float* ray[2][QNCOL];    // queue of bounce k is ray[k & 1]
-    float* ht;               // hit t
-    int* hf;                 // hit face
-    float* sx[3];            // shade record: hit point
-    int* sface;              // shade record: face, -1 when no vertex
-    uint32_t* sinfo;         // shade record: bit0 sampled, bit1 lobe, bit2 continued
-    int* stex;               // shade record: env texel sampled
-    int* snext;              // shade record: index of the continuation in the next queue, -1 if none
-    float* sh[7];            // shadow entries [entry][i]: dir xyz, tmax, contrib rgb
-    uint8_t* socc;           // shadow entry outcome [entry][i]: 0 no ray, 1 occluded, 2 unoccluded
+    uint32_t* ray[2];        // QNCOL columns; queue of bounce k is ray[k & 1]
+    uint32_t* rec;           // RNCOL columns; hits and shading points of the current bounce
+    uint32_t* sh;            // SNCOL columns; shadow entries
+    uint8_t* socc;           // outcome code of a shadow entry: 0 no ray, 1 occluded, 2 unoccluded
     uint32_t* slist;         // shadow entries (l * cap + i) that carry a ray, compacted per bounce
     int* cnt;                // ray counts per bounce (k), shadow-ray counts per bounce (32 + k)
     int* take;               // wave_tiles counters: set k (extension rays of bounce k), 16 + k (shadow rays of bounce k)
@@ -178,8 +195,6 @@ struct Queues {
     int grid;                // blocks of the traversal kernels (<= TRACE_GRID)
     int nent;                // shadow entries per shading point (nl + env)
 };
-
-__device__ __forceinline__ uint32_t& qu(float* const* cols, int c, int i) { return ((uint32_t*)cols[c])[i]; }
 
 // Queue streams (rays, hits, shading records, shadow entries) are written once
 // and read once or twice per bounce, gigabytes per pass: with ST_QUEUE_NT they
@@ -203,10 +218,26 @@ template <class T> __device__ __forceinline__ void qst(T* p, T v) {
     *p = v;
 #endif
 }
-__device__ __forceinline__ float qf(float* const* cols, int c, int i) { return qld(cols[c] + i); }
-__device__ __forceinline__ uint32_t qu_ld(float* const* cols, int c, int i) { return qld((const uint32_t*)cols[c] + i); }
-__device__ __forceinline__ void qf_st(float* const* cols, int c, int i, float v) { qst(cols[c] + i, v); }
-__device__ __forceinline__ void qu_st(float* const* cols, int c, int i, uint32_t v) { qst((uint32_t*)cols[c] + i, v); }
+
+// an entry of a queue of N columns
+template <int N> struct QRow {
+    uint32_t ST_GLOBAL* p;
+    __device__ __forceinline__ QRow(uint32_t* base, size_t i)
+        : p((uint32_t ST_GLOBAL*)base + (i >> 6) * (size_t)(N * 64) + (i & 63)) {}
+    __device__ __forceinline__ uint32_t u(int c) const { return qld((const uint32_t*)(p + 64 * c)); }
+    __device__ __forceinline__ float f(int c) const { return __uint_as_float(u(c)); }
+    __device__ __forceinline__ V3 v(int c) const { return V3{f(c), f(c + 1), f(c + 2)}; }
+    __device__ __forceinline__ void u(int c, uint32_t x) const { qst((uint32_t*)(p + 64 * c), x); }
+    __device__ __forceinline__ void f(int c, float x) const { u(c, __float_as_uint(x)); }
+    __device__ __forceinline__ void v(int c, V3 x) const { f(c, x.x); f(c + 1, x.y); f(c + 2, x.z); }
+    // without the hint: for a wave that writes every other entry, whose half lines are
+    // completed by its next stores (hinted, k_edge_camera took 841 us instead of 681 for
+    // the side rays of 32 views of 256^2 at 8 spp)
+    __device__ __forceinline__ void put(int c, uint32_t x) const { p[64 * c] = x; }
+};
+using RayRow = QRow<QNCOL>;
+using RecRow = QRow<RNCOL>;
+using ShRow = QRow<SNCOL>;
 
 // A wavefront pass starts from camera rays, made where they are traced, or from side
 // rays of primary edge samples, queued by k_edge_camera.

@@ -35,12 +35,12 @@ __device__ __forceinline__ long long canon(const DevCam& c, int x, int y, int j,
 }
 
 // final decision hash of a path: canonical debug slot, or the path's radiance slot
-__device__ __forceinline__ void final_hash(const FwdParams& p, float* const* r, int i, uint32_t h) {
+__device__ __forceinline__ void final_hash(const FwdParams& p, const RayRow& r, uint32_t h) {
     if (p.hash_by_q) {
-        p.hash_by_q[qu(r, QQ, i)] = h;
+        p.hash_by_q[r.u(QQ)] = h;
     } else if (p.dbg_hash) {
-        const DevCam& c = p.cams[qu(r, QVD, i) & 0xFFFFu];
-        p.dbg_hash[(c.pixoff + (long long)qu(r, QC0, i)) * p.spp + (qu(r, QC1, i) & 0xFFFFu)] = h;
+        const DevCam& c = p.cams[r.u(QVD) & 0xFFFFu];
+        p.dbg_hash[(c.pixoff + (long long)r.u(QC0)) * p.spp + (r.u(QC1) & 0xFFFFu)] = h;
     }
 }
 
@@ -69,14 +69,16 @@ __device__ __forceinline__ V3 path_dir(const FwdParams& p, const DevCam& c, cons
 // closest hit of queue entry i of bounce k >= 2.  ONE: the launch has one scene,
 // whose geometry is GW; else each ray looks its own up
 template <bool FAST, bool ONE>
-__device__ __forceinline__ void extend_one(const FwdParams& p, const Queues& q, float* const* r, int i, const TraceGeo& GW,
+__device__ __forceinline__ void extend_one(const FwdParams& p, const Queues& q, uint32_t* queue, uint32_t i, const TraceGeo& GW,
                                            TravStack& st) {
-    const TraceGeo G = ONE ? GW : lane_geo(p.scenes[p.cams[qu_ld(r, QVD, i) & 0xFFFFu].scene]);
-    const V3 o{qf(r, QOX, i), qf(r, QOY, i), qf(r, QOZ, i)}, d{qf(r, QDX, i), qf(r, QDY, i), qf(r, QDZ, i)};
+    const RayRow r(queue, i);
+    const TraceGeo G = ONE ? GW : lane_geo(p.scenes[p.cams[r.u(QVD) & 0xFFFFu].scene]);
+    const V3 o = r.v(QOX), d = r.v(QDX);
     float t;
-    const int f = trace_closest<FAST>(G, o, d, TMIN, (int)qu_ld(r, QEXCL, i), t, st);
-    qst(q.ht + i, t);
-    qst(q.hf + i, f);
+    const int f = trace_closest<FAST>(G, o, d, TMIN, (int)r.u(QEXCL), t, st);
+    const RecRow c(q.rec, i);
+    c.f(RT, t);
+    c.u(RF, (uint32_t)f);
 }
 
 // Closest hits of the first bounce, 64 consecutive rays per wave, traced in lockstep.
@@ -91,7 +93,6 @@ __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_extend(FwdParams p, 
     __shared__ uint32_t lds[LDS_STACK * TRACE_BLOCK];
     TravStack st = make_trav_stack(lds, q.spill, p.err, p.work ? p.work + 3 * WORK_EXTEND : nullptr);
     const TraceGeo GW = wave_geo(p.scene);
-    float* const* r = q.ray[1];
     const int n = SIDE ? q.cnt[1] : n_cam;
     if (!SIDE) {
         // counters of the launches after this one (its own were cleared before it
@@ -107,11 +108,12 @@ __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_extend(FwdParams p, 
         int f0 = -1;
         V3 o, d;
         TraceGeo G = GW;
+        const RayRow r(q.ray[1], (uint32_t)i);
         if (SIDE) {
             const DevScene& S = p.scene;                // a backward has one scene
-            o = ld3(p.cams[qu_ld(r, QVD, i) & 0xFFFFu].eye);
-            d = V3{qf(r, QDX, i), qf(r, QDY, i), qf(r, QDZ, i)};
-            const int4 E = S.edges[qu_ld(r, QEXCL, i) & 0x7FFFFFFFu];
+            o = ld3(p.cams[r.u(QVD) & 0xFFFFu].eye);
+            d = r.v(QDX);
+            const int4 E = S.edges[r.u(QEXCL) & 0x7FFFFFFFu];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int fe = j == 0 ? E.z : E.w;
@@ -133,11 +135,10 @@ __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_extend(FwdParams p, 
         }
         float t;
         const int f = trace_closest<FAST>(G, o, d, TMIN, -1, t, st, t0, f0);
-        qst(q.ht + i, t);
-        qst(q.hf + i, f);
-        if (!SIDE && f >= 0) {
-            qf_st(r, QDX, i, d.x); qf_st(r, QDY, i, d.y); qf_st(r, QDZ, i, d.z);
-        }
+        const RecRow c(q.rec, (uint32_t)i);
+        c.f(RT, t);
+        c.u(RF, (uint32_t)f);
+        if (!SIDE && f >= 0) r.v(QDX, d);
     });
 }
 
@@ -158,8 +159,6 @@ template <bool HASH, bool ONE, int FROM>
 __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Queues q, int k, long long q0) {
     __shared__ int resv[2 * (SHADE_BLOCK / 64 + 1)];
     const int n = q.cnt[k];
-    float* const* r = q.ray[k & 1];
-    float* const* rn = q.ray[(k + 1) & 1];
     const int stride = gridDim.x * blockDim.x;
     constexpr bool hashing = HASH;
     // with the shadow sum fused into k_shadow, the shading record keeps only what
@@ -170,6 +169,8 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
     for (int b0 = blockIdx.x * blockDim.x; b0 < n; b0 += stride) {
         const int i = b0 + (int)threadIdx.x;
         const bool active = i < n;
+        const RayRow r(q.ray[k & 1], (uint32_t)i);
+        const RecRow rec(q.rec, (uint32_t)i);
         bool emit = false;
         uint32_t rays = 0;          // shadow entries of this shading point that carry a ray
         V3 x{0.f, 0.f, 0.f}, wi{0.f, 0.f, 0.f}, beta{0.f, 0.f, 0.f};
@@ -181,18 +182,18 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
         if (active) {
             // an entry's words are asked for together, one trip to memory before the
             // gathers; of a first-bounce entry, the hit alone: most of them are misses
-            f = qld(q.hf + i);
+            f = (int)rec.u(RF);
             float ht = 0.0f;
             V3 o{0.f, 0.f, 0.f}, d{0.f, 0.f, 0.f};
             beta = V3{1.f, 1.f, 1.f};
             if (FROM == FROM_LATER) {
-                pq = qu_ld(r, QQ, i);
-                c0 = qu_ld(r, QC0, i);
-                c1 = qu_ld(r, QC1, i);
-                vd = qu_ld(r, QVD, i);
-                ht = qld(q.ht + i);
-                d = V3{qf(r, QDX, i), qf(r, QDY, i), qf(r, QDZ, i)};
-                beta = V3{qf(r, QBR, i), qf(r, QBG, i), qf(r, QBB, i)};
+                pq = r.u(QQ);
+                c0 = r.u(QC0);
+                c1 = r.u(QC1);
+                vd = r.u(QVD);
+                ht = rec.f(RT);
+                d = r.v(QDX);
+                beta = r.v(QBR);
             }
             if (FROM == FROM_CAMERA) {
                 pq = (uint32_t)(q0 + i);
@@ -207,50 +208,50 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                     c1 = cc.c1;
                     vd = (uint32_t)v;
                     // for the shadow kernels and the hashes of this bounce
-                    qu_st(r, QQ, i, pq);
-                    qu_st(r, QVD, i, vd);
-                    if (hashing) { qu_st(r, QC0, i, c0); qu_st(r, QC1, i, c1); }
+                    r.u(QQ, pq);
+                    r.u(QVD, vd);
+                    if (hashing) { r.u(QC0, c0); r.u(QC1, c1); }
                 }
                 if (FROM == FROM_SIDE) {
-                    pq = qu_ld(r, QQ, i);
-                    c0 = qu_ld(r, QC0, i);
-                    c1 = qu_ld(r, QC1, i);
-                    vd = qu_ld(r, QVD, i);
+                    pq = r.u(QQ);
+                    c0 = r.u(QC0);
+                    c1 = r.u(QC1);
+                    vd = r.u(QVD);
                 }
                 if (FROM != FROM_LATER && f >= 0) {
-                    ht = qld(q.ht + i);
-                    d = V3{qf(r, QDX, i), qf(r, QDY, i), qf(r, QDZ, i)};
+                    ht = rec.f(RT);
+                    d = r.v(QDX);
                 }
             }
             const DevScene& S = ONE ? p.scene : p.scenes[p.cams[vd & 0xFFFFu].scene];
             const Key key{p.seed, S.scene_id};
             const Ctr ctr{c0, c1, 0u, vd >> 16};
-            Hash h{hashing ? (FROM != FROM_LATER ? FNV_INIT : qu_ld(r, QHASH, i)) : 0u, hashing};
+            Hash h{hashing ? (FROM != FROM_LATER ? FNV_INIT : r.u(QHASH)) : 0u, hashing};
             push_face(h, f);
             // (the records belong to main paths: side paths come without them)
             if (FROM != FROM_SIDE && p.rec_face) qst(p.rec_face + (size_t)(k - 1) * p.rec_n + pq, f);
-            if (!fused) q.sface[i] = -1;
+            if (!fused) rec.u(RFACE, 0xFFFFFFFFu);
             if (f < 0) {
                 if (S.has_env && FROM == FROM_LATER) {
                     const int tex = env_texel_of(S, d);
                     h.push((uint32_t)tex);
-                    const float pp = qf(r, QPPREV, i);
+                    const float pp = r.f(QPPREV);
                     const float w = pp / (pp + S.texpdf[tex]);
                     const V3 c = mul(beta, env_rgb(S, tex)) * w;
                     float* L = q.L + 3 * (size_t)pq;
                     L[0] += c.x; L[1] += c.y; L[2] += c.z;
                 }
-                if (hashing) final_hash(p, r, i, h.h);
+                if (hashing) final_hash(p, r, h.h);
             } else if (k > p.B) {
-                if (hashing) final_hash(p, r, i, h.h);
-            } else if (FROM == FROM_SIDE && qld(q.hf + (i ^ 1)) == f) {
+                if (hashing) final_hash(p, r, h.h);
+            } else if (FROM == FROM_SIDE && (int)RecRow(q.rec, (uint32_t)(i ^ 1)).u(RF) == f) {
                 // the two side rays of a primary edge sample (queue slots 2j and
                 // 2j + 1 at bounce 1) met the same face first: the edge point is
                 // hidden behind it, there is no jump to measure, and both side
                 // paths end here with zero radiance
-                if (hashing) final_hash(p, r, i, h.h);
+                if (hashing) final_hash(p, r, h.h);
             } else {
-                o = FROM != FROM_LATER ? ld3(p.cams[vd & 0xFFFFu].eye) : V3{qf(r, QOX, i), qf(r, QOY, i), qf(r, QOZ, i)};
+                o = FROM != FROM_LATER ? ld3(p.cams[vd & 0xFFFFu].eye) : r.v(QOX);
                 x = o + d * ht;
                 V3 n = xyz(S.fnorm[f]);
                 const V3 wo = -d;
@@ -278,8 +279,10 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                     // k_shadow_sum reads the contribution of an unoccluded one)
                     const size_t e = (size_t)l * q.cap + i;
                     if (tmax >= 0.0f) {
-                        qst(q.sh[0] + e, wl.x); qst(q.sh[1] + e, wl.y); qst(q.sh[2] + e, wl.z); qst(q.sh[3] + e, tmax);
-                        qst(q.sh[4] + e, ct.x); qst(q.sh[5] + e, ct.y); qst(q.sh[6] + e, ct.z);
+                        const ShRow sh(q.sh, e);
+                        sh.v(SWX, wl);
+                        sh.f(STMAX, tmax);
+                        sh.v(SCR, ct);
                         rays |= 1u << l;
                     } else if (!fused) {
                         q.socc[e] = 0;
@@ -300,8 +303,10 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                     }
                     const size_t e = (size_t)S.nl * q.cap + i;
                     if (tmax >= 0.0f) {
-                        qst(q.sh[0] + e, we.x); qst(q.sh[1] + e, we.y); qst(q.sh[2] + e, we.z); qst(q.sh[3] + e, tmax);
-                        qst(q.sh[4] + e, ct.x); qst(q.sh[5] + e, ct.y); qst(q.sh[6] + e, ct.z);
+                        const ShRow sh(q.sh, e);
+                        sh.v(SWX, we);
+                        sh.f(STMAX, tmax);
+                        sh.v(SCR, ct);
                         rays |= 1u << S.nl;
                     } else if (!fused) {
                         q.socc[e] = 0;
@@ -323,14 +328,14 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                 // the shading record: the shadow rays' origin and excluded face (fused:
                 // read only through the listed entries)
                 if (!fused || rays) {
-                    qst(q.sface + i, f);
-                    qst(q.sx[0] + i, x.x); qst(q.sx[1] + i, x.y); qst(q.sx[2] + i, x.z);
+                    rec.u(RFACE, (uint32_t)f);
+                    rec.v(RX0, x);
                 }
-                if (!fused) q.sinfo[i] = info;
+                if (!fused) rec.u(RINFO, info);
                 if (fused && FROM != FROM_SIDE && p.rec_occ)
                     p.rec_occ[(size_t)(k - 1) * p.rec_n + pq] = 0u;
-                if (!fused) q.stex[i] = tex;
-                if (!fused) q.snext[i] = -1;
+                if (!fused) rec.u(RTEX, (uint32_t)tex);
+                if (!fused) rec.u(RNEXT, 0xFFFFFFFFu);
             }
             hv = h.h;
         }
@@ -349,43 +354,46 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
         }
         for (int so = oo.y; rays; rays &= rays - 1, ++so)
             qst(q.slist + so, (uint32_t)(__ffs(rays) - 1) * (uint32_t)q.cap + (uint32_t)i);
-        {
-            if (emit) {
-                qf_st(rn, QOX, o, x.x); qf_st(rn, QOY, o, x.y); qf_st(rn, QOZ, o, x.z);
-                qf_st(rn, QDX, o, wi.x); qf_st(rn, QDY, o, wi.y); qf_st(rn, QDZ, o, wi.z);
-                qu_st(rn, QEXCL, o, (uint32_t)f);
-                qf_st(rn, QPPREV, o, pb);
-                qu_st(rn, QQ, o, pq);
-                qu_st(rn, QC0, o, c0);
-                qu_st(rn, QC1, o, c1);
-                qu_st(rn, QVD, o, vd);
-                qf_st(rn, QBR, o, beta.x); qf_st(rn, QBG, o, beta.y); qf_st(rn, QBB, o, beta.z);
-                if (hashing) qu_st(rn, QHASH, o, hv);
-                if (!fused) q.snext[i] = o;
-            }
+        if (emit) {
+            const RayRow rn(q.ray[(k + 1) & 1], (uint32_t)o);
+            rn.v(QOX, x);
+            rn.v(QDX, wi);
+            rn.u(QEXCL, (uint32_t)f);
+            rn.f(QPPREV, pb);
+            rn.u(QQ, pq);
+            rn.u(QC0, c0);
+            rn.u(QC1, c1);
+            rn.u(QVD, vd);
+            rn.v(QBR, beta);
+            if (hashing) rn.u(QHASH, hv);
+            if (!fused) rec.u(RNEXT, (uint32_t)o);
         }
-        if (active && hashing) qu(r, QHASH, i) = hv;
+        if (active && hashing) r.u(QHASH, hv);
     }
 }
 
 // shadow ray w of the list of bounce k: occlusion code, or (fused) the
 // unoccluded contribution added and the occlusion recorded
 template <bool FAST, bool ONE>
-__device__ __forceinline__ void shadow_one(const FwdParams& p, const Queues& q, int k, float* const* r, int w,
-                                           bool fused, const TraceGeo& GW, TravStack& st) {
+__device__ __forceinline__ void shadow_one(const FwdParams& p, const Queues& q, int k, int w, bool fused,
+                                           const TraceGeo& GW, TravStack& st) {
     const uint32_t e = qld(q.slist + w);
-    const int i = (int)(fused ? e : e % (uint32_t)q.cap);      // (fused: one entry per shading point)
-    const int f = qld(q.sface + i);
-    const TraceGeo G = ONE ? GW : lane_geo(p.scenes[p.cams[qu_ld(r, QVD, i) & 0xFFFFu].scene]);
-    const float tmax = qld(q.sh[3] + e);
-    const V3 o{qld(q.sx[0] + i), qld(q.sx[1] + i), qld(q.sx[2] + i)}, dd{qld(q.sh[0] + e), qld(q.sh[1] + e), qld(q.sh[2] + e)};
+    const uint32_t i = fused ? e : e % (uint32_t)q.cap;        // (fused: one entry per shading point)
+    const RecRow rec(q.rec, i);
+    const RayRow r(q.ray[k & 1], i);
+    const ShRow sh(q.sh, e);
+    const int f = (int)rec.u(RFACE);
+    const TraceGeo G = ONE ? GW : lane_geo(p.scenes[p.cams[r.u(QVD) & 0xFFFFu].scene]);
+    const float tmax = sh.f(STMAX);
+    const V3 o = rec.v(RX0), dd = sh.v(SWX);
     const bool occluded = trace_any<FAST>(G, o, dd, TMIN, tmax, f, st);
     if (fused) {
         if (occluded) {
-            if (p.rec_occ) p.rec_occ[(size_t)(k - 1) * p.rec_n + qu_ld(r, QQ, i)] = 1u;
+            if (p.rec_occ) p.rec_occ[(size_t)(k - 1) * p.rec_n + r.u(QQ)] = 1u;
         } else {
-            float* L = q.L + 3 * (size_t)qu_ld(r, QQ, i);
-            L[0] += qld(q.sh[4] + e); L[1] += qld(q.sh[5] + e); L[2] += qld(q.sh[6] + e);
+            float* L = q.L + 3 * (size_t)r.u(QQ);
+            const V3 c = sh.v(SCR);
+            L[0] += c.x; L[1] += c.y; L[2] += c.z;
         }
     } else {
         q.socc[e] = occluded ? 1 : 2;
@@ -401,12 +409,11 @@ __global__ void __launch_bounds__(TRACE_BLOCK) SHADOW_OCC k_shadow(FwdParams p, 
     TravStack st = make_trav_stack(lds, q.spill, p.err, p.work ? p.work + 3 * WORK_SHADOW : nullptr);
     const TraceGeo G = wave_geo(p.scene);
     const int items = q.cnt[32 + k];
-    float* const* r = q.ray[k & 1];
     const bool fused = shadow_fused(p, q);
     // 64 consecutive listed rays per wave, traced in lockstep
     wave_tiles(q.take + TAKE_NC * 32 * (16 + k), (uint32_t)items, [&](uint32_t t) {
         const int w = (int)(t + __lane_id());
-        if (w < items) shadow_one<FAST, ONE>(p, q, k, r, w, fused, G, st);
+        if (w < items) shadow_one<FAST, ONE>(p, q, k, w, fused, G, st);
     });
 }
 
@@ -427,8 +434,6 @@ __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_trace_pair(FwdParams
     const TraceGeo G = wave_geo(p.scene);
     const int n = q.cnt[k + 1];
     const int items = q.cnt[32 + k];
-    float* const* rn = q.ray[(k + 1) & 1];
-    float* const* r = q.ray[k & 1];
     const bool fused = shadow_fused(p, q);
     // unsigned: with many lights the two counts together can pass 2^31 (each is
     // below 2^31, the grid below 2^21, so the sum and the next index fit 32 bits)
@@ -439,11 +444,11 @@ __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_trace_pair(FwdParams
         if (t < s64) {
             if (i < (uint32_t)items) {
                 st.work = wsh;
-                shadow_one<FAST, ONE>(p, q, k, r, (int)i, fused, G, st);
+                shadow_one<FAST, ONE>(p, q, k, (int)i, fused, G, st);
             }
         } else if (i < all) {
             st.work = wext;
-            extend_one<FAST, ONE>(p, q, rn, (int)(i - s64), G, st);
+            extend_one<FAST, ONE>(p, q, q.ray[(k + 1) & 1], i - s64, G, st);
         }
     });
 }
@@ -451,38 +456,38 @@ __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_trace_pair(FwdParams
 // shadow contributions of bounce k added per shading point in entry order
 __global__ void k_shadow_sum(FwdParams p, Queues q, int k) {
     const int n = q.cnt[k];
-    float* const* r = q.ray[k & 1];
-    float* const* rn = q.ray[(k + 1) & 1];
     const int stride = gridDim.x * blockDim.x;
     const bool hashing = p.dbg_hash || p.hash_by_q;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const int f = q.sface[i];
+        const RayRow r(q.ray[k & 1], (uint32_t)i);
+        const RecRow rec(q.rec, (uint32_t)i);
+        const int f = (int)rec.u(RFACE);
         if (f < 0) continue;
-        const DevScene& S = p.scenes[p.cams[qu(r, QVD, i) & 0xFFFFu].scene];
-        Hash h{hashing ? qu(r, QHASH, i) : 0u, hashing};
+        const DevScene& S = p.scenes[p.cams[r.u(QVD) & 0xFFFFu].scene];
+        Hash h{hashing ? r.u(QHASH) : 0u, hashing};
         V3 acc{0.f, 0.f, 0.f};
         const int nent = S.nl + (S.has_env ? 1 : 0);
         uint32_t occ = 0;
         for (int l = 0; l < nent; ++l) {
             const size_t e = (size_t)l * q.cap + i;
-            if (l == S.nl) h.push((uint32_t)q.stex[i]);
+            if (l == S.nl) h.push(rec.u(RTEX));
             const uint32_t code = q.socc[e];
-            if (code == 2u) acc = acc + V3{q.sh[4][e], q.sh[5][e], q.sh[6][e]};
+            if (code == 2u) acc = acc + ShRow(q.sh, e).v(SCR);
             if (code == 1u) occ |= 1u << l;
             h.push(code);
         }
-        if (p.rec_occ) p.rec_occ[(size_t)(k - 1) * p.rec_n + qu(r, QQ, i)] = occ;
-        const uint32_t info = q.sinfo[i];
+        if (p.rec_occ) p.rec_occ[(size_t)(k - 1) * p.rec_n + r.u(QQ)] = occ;
+        const uint32_t info = rec.u(RINFO);
         if (info & 1u) {
             h.push((info >> 1) & 1u);
             h.push((info >> 2) & 1u);
         }
-        float* L = q.L + 3 * (size_t)qu(r, QQ, i);
+        float* L = q.L + 3 * (size_t)r.u(QQ);
         L[0] += acc.x; L[1] += acc.y; L[2] += acc.z;
         if (hashing) {
-            const int o = q.snext[i];
-            if (o >= 0) qu(rn, QHASH, o) = h.h;
-            else final_hash(p, r, i, h.h);
+            const int o = (int)rec.u(RNEXT);
+            if (o >= 0) RayRow(q.ray[(k + 1) & 1], (uint32_t)o).u(QHASH, h.h);
+            else final_hash(p, r, h.h);
         }
     }
 }
