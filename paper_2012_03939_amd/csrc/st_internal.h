@@ -180,7 +180,7 @@ template <class Fn> __device__ __forceinline__ void wave_tiles(int* counters, ui
     }
 }
 
-// queue and path-state arrays of one wavefront chunk (SoA)
+// queue and path-state arrays of one wavefront chunk
 struct Queues {
     uint32_t* ray[2];        // QNCOL columns; queue of bounce k is ray[k & 1]
     uint32_t* rec;           // RNCOL columns; hits and shading points of the current bounce
