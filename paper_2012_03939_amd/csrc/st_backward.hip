@@ -281,6 +281,7 @@ k_adjoint(BwdParams p, long long total) {
                 const int tx = texel_of(S, f, xh);
                 if (S.tex_res) h.push((uint32_t)tx);
                 const Mat m = load_mat(S.mat + 7 * (size_t)tx);
+                const float lo = out_lambda(wo, n, m);
                 const uint32_t rocc = (REC || rec_occ) ? qld(rec_occ + ri) : 0u;
                 for (int l = 0; l < S.nl; ++l) {
                     const auto lt = S.lights + 6 * l;
@@ -313,7 +314,9 @@ k_adjoint(BwdParams p, long long total) {
                         if (!occ) {
                             fl |= R_ENV;
                             put(rwe, k - 1, we);
-                            put(rden, k - 1, pe + bsdf_pdf(we, wo, n, m.a, S.vndf));
+                            float pdf;
+                            brdf_eval_pdf(we, wo, n, m, lo, S.vndf, pdf);
+                            put(rden, k - 1, pe + pdf);
                             put(rtex, k - 1, tex);
                         }
                     }
@@ -354,7 +357,8 @@ k_adjoint(BwdParams p, long long total) {
                 V3 wi;
                 const int lobe = bsdf_sample(u, wo, n, m.a, S.vndf, wi);
                 const float ci = dot(n, wi);
-                const float pb = bsdf_pdf(wi, wo, n, m.a, S.vndf);
+                float pb;
+                const V3 fi = brdf_eval_pdf(wi, wo, n, m, lo, S.vndf, pb);
                 h.push((uint32_t)lobe);
                 if (!(ci > 0.0f) || !(pb > 0.0f)) { h.push(0u); put(rfl, k - 1, fl); break; }
                 h.push(1u);
@@ -362,7 +366,7 @@ k_adjoint(BwdParams p, long long total) {
                 put(rfl, k - 1, fl);
                 put(rwi, k - 1, wi);
                 put(rpb, k - 1, pb);
-                beta = mul(beta, brdf_eval(wi, wo, n, m)) * (ci / pb);
+                beta = mul(beta, fi) * (ci / pb);
                 pprev = pb;
                 o = xh; d = wi; excl = f;
             }
@@ -409,7 +413,7 @@ k_adjoint(BwdParams p, long long total) {
                 }
                 const V3 dirk = k == 0 ? d0 : sel(rwi, k - 1);
                 const Mat m = load_mat(S.mat + 7 * (size_t)texel_of(S, f, xh));
-                const V3 fv = brdf_eval(ud, -dirk, n, m);
+                const V3 fv = brdf_eval(ud, -dirk, n, m, out_lambda(-dirk, n, m));
                 const float cc = dot(mul(w, mul(sel(rbeta, k), fv)), Ls[0] - Ls[1]) * cv * (sel(rsw, k) / r2);
                 put(rsecc, k, cc);
                 put(rsecm, k, mv);
@@ -445,6 +449,9 @@ k_adjoint(BwdParams p, long long total) {
                     const V3 n = nu * sg;
                     const Mat m = load_mat(S.mat + 7 * (size_t)tx);
                     const V3 a = want_interior ? mul(w, sel(rbeta, k)) : V3{0.f, 0.f, 0.f};
+                    const float co = dot(n, wo);
+                    Lambda lo{0.0f, 0.0f, 0.0f};
+                    if (co > 0.0f) lo = smith_lambda_grad(co, alpha_eff(m.a));
                     V3 C{0.f, 0.f, 0.f}, gn{0.f, 0.f, 0.f}, gx = gxnext, gdummy{0.f, 0.f, 0.f};
                     float gm[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
                     for (int l = 0; l < S.nl; ++l) {
@@ -456,14 +463,13 @@ k_adjoint(BwdParams p, long long total) {
                         const float rr = sqrtf(r2);
                         const V3 wl = dl * (1.0f / rr);
                         const float cl = dot(n, wl);
-                        const V3 fv = brdf_eval(wl, wo, n, m);
+                        const V3 aI = mul(a, I);
+                        V3 gwl{0.f, 0.f, 0.f};
+                        const V3 fv = brdf_eval_backward(wl, wo, n, m, lo, aI * (cl / r2), gn, gwl, gm);
                         const V3 If = mul(I, fv);
                         C = C + If * (cl / r2);
-                        const V3 aI = mul(a, I);
                         const float gcl = dot(aI, fv) / r2;
                         const float gr2 = -dot(aI, fv) * cl / (r2 * r2);
-                        V3 gwl{0.f, 0.f, 0.f};
-                        brdf_backward(wl, wo, n, m, aI * (cl / r2), gn, gwl, gm);
                         gn = gn + wl * gcl;
                         gwl = gwl + n * gcl;
                         const V3 gd = (gwl - wl * dot(wl, gwl)) * (1.0f / rr) + dl * (2.0f * gr2);
@@ -474,10 +480,9 @@ k_adjoint(BwdParams p, long long total) {
                         const float den = sel(rden, k);
                         const V3 Le = env_rgb(S, sel(rtex, k));
                         const float ce = dot(n, we);
-                        const V3 fv = brdf_eval(we, wo, n, m);
-                        C = C + mul(Le, fv) * (ce / den);
                         const V3 aL = mul(a, Le);
-                        brdf_backward(we, wo, n, m, aL * (ce / den), gn, gdummy, gm);
+                        const V3 fv = brdf_eval_backward(we, wo, n, m, lo, aL * (ce / den), gn, gdummy, gm);
+                        C = C + mul(Le, fv) * (ce / den);
                         gn = gn + we * (dot(aL, fv) / den);
                     }
                     V3 Sk = C;
@@ -486,9 +491,8 @@ k_adjoint(BwdParams p, long long total) {
                         const float pb = sel(rpb, k);
                         const V3 S1 = (fl & R_ESC) ? sel(resc, k) : Snext;
                         const float ci = dot(n, wi);
-                        const V3 fv = brdf_eval(wi, wo, n, m);
                         const V3 uu = mul(a, S1);
-                        brdf_backward(wi, wo, n, m, uu * (ci / pb), gn, gdummy, gm);
+                        const V3 fv = brdf_eval_backward(wi, wo, n, m, lo, uu * (ci / pb), gn, gdummy, gm);
                         gn = gn + wi * (dot(uu, fv) / pb);
                         Sk = Sk + mul(fv, S1) * (ci / pb);
                     }
@@ -1062,7 +1066,7 @@ __device__ bool shadow_edge_one(const BwdParams& p, const DevScene& S, const Dev
     const float cl = dot(n, wl);
     if (!(cl > 0.0f)) return false;
     const Mat m = load_mat(S.mat + 7 * (size_t)texel_of(S, fr, zf));
-    const V3 fv = brdf_eval(wl, wo, n, m);
+    const V3 fv = brdf_eval(wl, wo, n, m, out_lambda(wo, n, m));
     const V3 I = ld3(lt + 3);
     const double dv = (double)(vsd[0] - vsd[1]);
     double cc = ((double)di[0] * fv.x * I.x + (double)di[1] * fv.y * I.y + (double)di[2] * fv.z * I.z) * dv *

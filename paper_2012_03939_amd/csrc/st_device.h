@@ -634,37 +634,41 @@ __device__ __forceinline__ V3 brdf_eval(V3 wi, V3 wo, V3 n, const Mat& m, float 
     }
     return m.kd * INV_PI_F + m.ks * spec;
 }
-__device__ __forceinline__ V3 brdf_eval(V3 wi, V3 wo, V3 n, const Mat& m) {
-    return brdf_eval(wi, wo, n, m, out_lambda(wo, n, m));
-}
 
-// pdf of the one-sample mixture: 1/2 cosine-weighted + 1/2 specular, whose
-// half-vectors follow D(h) cos(theta_h), or with vndf the normals visible from
-// wo, G1(wo) max(0, wo.h) D(h) / cos(theta_o) (Heitz and d'Eon 2014); either
-// becomes a pdf of wi through 1 / (4 |wo.h|)
-__device__ __forceinline__ float bsdf_pdf(V3 wi, V3 wo, V3 n, float alpha, bool vndf) {
-    const float ci = dot(n, wi);
-    if (!(ci > 0.0f)) return 0.0f;
-    const float a = alpha_eff(alpha);
-    const float pd = (1.0f - LOBE_SPEC_P) * ci * INV_PI_F;
+// f(wi, wo) and the pdf of wi, of the one-sample mixture: 1/2 cosine-weighted + 1/2
+// specular, whose half-vectors follow D(h) cos(theta_h), or with vndf the normals
+// visible from wo, G1(wo) max(0, wo.h) D(h) / cos(theta_o) (Heitz and d'Eon 2014);
+// either becomes a pdf of wi through 1 / (4 |wo.h|).  One half-vector, one D and the
+// shading point's Lambda(wo) serve both.
+__device__ __forceinline__ V3 brdf_eval_pdf(V3 wi, V3 wo, V3 n, const Mat& m, float lambda_o, bool vndf, float& pdf) {
+    const float ci = dot(n, wi), co = dot(n, wo);
+    pdf = 0.0f;
+    if (!(ci > 0.0f)) return V3{0.f, 0.f, 0.f};
+    const float a = alpha_eff(m.a);
     const V3 hv = wi + wo;
     const float hl = len(hv);
-    float ps = 0.0f;
+    float ps = 0.0f, spec = 0.0f;
     if (hl > 0.0f) {
         const V3 h = hv * (1.0f / hl);
         const float ch = dot(n, h);
-        if (!vndf) {
-            const float oh = fabsf(dot(wo, h));
-            if (ch > 0.0f && oh > 0.0f) ps = LOBE_SPEC_P * beckmann_D(n, h, ch, a) * ch / (4.0f * oh);
-        } else {
-            const float oh = dot(wo, h), co = dot(n, wo);
-            if (ch > 0.0f && oh > 0.0f && co > 0.0f) {
-                const float g1 = 1.0f / (1.0f + smith_lambda(co, a));
-                ps = LOBE_SPEC_P * g1 * beckmann_D(n, h, ch, a) / (4.0f * co);
+        if (ch > 0.0f) {
+            const float D = beckmann_D(n, h, ch, a);
+            const float oh = dot(wo, h);
+            if (!vndf) {
+                if (fabsf(oh) > 0.0f) ps = LOBE_SPEC_P * D * ch / (4.0f * fabsf(oh));
+            } else if (oh > 0.0f && co > 0.0f) {
+                const float g1 = 1.0f / (1.0f + lambda_o);
+                ps = LOBE_SPEC_P * g1 * D / (4.0f * co);
+            }
+            if (co > 0.0f) {
+                const float G = 1.0f / (1.0f + smith_lambda(ci, a) + lambda_o);
+                spec = D * G / (4.0f * ci * co);
             }
         }
     }
-    return pd + ps;
+    pdf = (1.0f - LOBE_SPEC_P) * ci * INV_PI_F + ps;
+    if (!(co > 0.0f)) return V3{0.f, 0.f, 0.f};
+    return m.kd * INV_PI_F + m.ks * spec;
 }
 
 // Visible-normal sample of the Beckmann lobe in the local frame (z = normal):
@@ -817,34 +821,41 @@ __device__ __forceinline__ int edge_tree_sample(const DevScene& S, V3 p, V3 nrm,
     return (int)S.etedge[code & 0x7FFFFFFF];
 }
 
-// Reverse-mode derivative of f(wi, wo, n, m) contracted with gf (rgb):
-// accumulates into gn, gwi (only needed when wi depends on the geometry) and gm[7].
-__device__ __forceinline__ float dlambda_dc(float c, float a, float& dla) {
+// Lambda of a direction with cosine c and its derivatives by c and by the roughness a
+struct Lambda { float v, dc, da; };
+__device__ __forceinline__ Lambda smith_lambda_grad(float c, float a) {
     // Lambda(x), x = c / (a sqrt(1-c^2)); dLambda/dx = -exp(-x^2) / (2 sqrt(pi) x^2)
-    dla = 0.0f;
-    if (c >= 1.0f) return 0.0f;
+    Lambda r{0.0f, 0.0f, 0.0f};
+    if (c >= 1.0f) return r;
     const float s = sqrtf(1.0f - c * c);
     const float x = c / (a * s);
-    if (x > 12.0f) return 0.0f;
-    const float dldx = -expf(-x * x) * (0.5f * INV_SQRT_PI_F) / (x * x);
-    dla = dldx * (-x / a);
-    return dldx / (a * s * s * s);
+    const float e = expf(-x * x);
+    r.v = (e * INV_SQRT_PI_F / x - erfcf(x)) * 0.5f;
+    if (x > 12.0f) return r;
+    const float dldx = -e * (0.5f * INV_SQRT_PI_F) / (x * x);
+    r.da = dldx * (-x / a);
+    r.dc = dldx / (a * s * s * s);
+    return r;
 }
 
-__device__ __forceinline__ void brdf_backward(V3 wi, V3 wo, V3 n, const Mat& m, V3 gf, V3& gn, V3& gwi,
-                                              float* gm) {
+// f(wi, wo, n, m) and the reverse-mode derivative of it contracted with gf (rgb), which
+// accumulates into gn, gwi (only needed when wi depends on the geometry) and gm[7].  lo:
+// Lambda of wo, the same for every wi of a shading point.  Value and derivative share
+// the half-vector, D and both Lambdas.
+__device__ __forceinline__ V3 brdf_eval_backward(V3 wi, V3 wo, V3 n, const Mat& m, const Lambda& lo, V3 gf, V3& gn,
+                                                 V3& gwi, float* gm) {
     const float ci = dot(n, wi), co = dot(n, wo);
-    if (!(ci > 0.0f) || !(co > 0.0f)) return;
+    if (!(ci > 0.0f) || !(co > 0.0f)) return V3{0.f, 0.f, 0.f};
     gm[0] += gf.x * INV_PI_F; gm[1] += gf.y * INV_PI_F; gm[2] += gf.z * INV_PI_F;
     const float a = alpha_eff(m.a);
     const V3 hv = wi + wo;
     const float hl = len(hv);
     const V3 h = hv * (1.0f / hl);
     const float ch = dot(n, h);
-    if (!(ch > 0.0f)) return;
+    if (!(ch > 0.0f)) return m.kd * INV_PI_F;
     const float D = beckmann_D(n, h, ch, a);
-    const float li = smith_lambda(ci, a), lo = smith_lambda(co, a);
-    const float G = 1.0f / (1.0f + li + lo);
+    const Lambda li = smith_lambda_grad(ci, a);
+    const float G = 1.0f / (1.0f + li.v + lo.v);
     const float K = D * G / (4.0f * ci * co);
     gm[3] += gf.x * K; gm[4] += gf.y * K; gm[5] += gf.z * K;
     const float glnK = dot(gf, m.ks) * K;       // gradient w.r.t. ln K
@@ -852,17 +863,16 @@ __device__ __forceinline__ void brdf_backward(V3 wi, V3 wo, V3 n, const Mat& m, 
     const float dlnD_dch = 2.0f / (c2 * ch * a * a) - 4.0f / ch;
     const V3 nh = cross(n, h);
     const float dlnD_da = 2.0f * dot(nh, nh) / (c2 * a * a * a) - 2.0f / a;
-    float dlia, dloa;
-    const float dli = dlambda_dc(ci, a, dlia), dlo = dlambda_dc(co, a, dloa);
-    if (m.a > ALPHA_MIN) gm[6] += glnK * (dlnD_da - G * (dlia + dloa));
-    const float gci = glnK * (-G * dli - 1.0f / ci);
-    const float gco = glnK * (-G * dlo - 1.0f / co);
+    if (m.a > ALPHA_MIN) gm[6] += glnK * (dlnD_da - G * (li.da + lo.da));
+    const float gci = glnK * (-G * li.dc - 1.0f / ci);
+    const float gco = glnK * (-G * lo.dc - 1.0f / co);
     const float gch = glnK * dlnD_dch;
     gn = gn + wi * gci + wo * gco + h * gch;
     // through h = normalize(wi + wo) (wo is fixed)
     const V3 gh = n * gch;
     const V3 ghv = (gh - h * dot(h, gh)) * (1.0f / hl);
     gwi = gwi + n * gci + ghv;
+    return m.kd * INV_PI_F + m.ks * K;
 }
 
 // ---------------------------------------------------------------------------
@@ -1002,6 +1012,7 @@ __device__ V3 trace_estimator(const DevScene& S, const TraceGeo& G, V3 o, V3 d, 
         const int tx = texel_of(S, f, x);
         if (S.tex_res) hash.push((uint32_t)tx);
         const Mat m = load_mat(S.mat + 7 * (size_t)tx);
+        const float lo = out_lambda(wo, n, m);
         for (int l = 0; l < S.nl; ++l) {
             const auto lt = S.lights + 6 * l;
             const V3 dl = ld3(lt) - x;
@@ -1014,7 +1025,7 @@ __device__ V3 trace_estimator(const DevScene& S, const TraceGeo& G, V3 o, V3 d, 
                 if (c > 0.0f) {
                     const bool occ = trace_any<FAST>(G, x, wl, TMIN, r * (1.0f - SHADOW_SHRINK), f, st);
                     code = occ ? 1u : 2u;
-                    if (!occ) L = L + mul(beta, mul(ld3(lt + 3), brdf_eval(wl, wo, n, m))) * (c / r2);
+                    if (!occ) L = L + mul(beta, mul(ld3(lt + 3), brdf_eval(wl, wo, n, m, lo))) * (c / r2);
                 }
             }
             hash.push(code);
@@ -1030,8 +1041,9 @@ __device__ V3 trace_estimator(const DevScene& S, const TraceGeo& G, V3 o, V3 d, 
                 const bool occ = trace_any<FAST>(G, x, we, TMIN, __int_as_float(0x7f800000), f, st);
                 code = occ ? 1u : 2u;
                 if (!occ) {
-                    const V3 fv = brdf_eval(we, wo, n, m);
-                    const float den = pe + bsdf_pdf(we, wo, n, m.a, S.vndf);
+                    float pdf;
+                    const V3 fv = brdf_eval_pdf(we, wo, n, m, lo, S.vndf, pdf);
+                    const float den = pe + pdf;
                     L = L + mul(beta, mul(env_rgb(S, tex), fv)) * (c / den);
                 }
             }
@@ -1042,11 +1054,12 @@ __device__ V3 trace_estimator(const DevScene& S, const TraceGeo& G, V3 o, V3 d, 
         V3 wi;
         const int lobe = bsdf_sample(u, wo, n, m.a, S.vndf, wi);
         const float ci = dot(n, wi);
-        const float pb = bsdf_pdf(wi, wo, n, m.a, S.vndf);
+        float pb;
+        const V3 fi = brdf_eval_pdf(wi, wo, n, m, lo, S.vndf, pb);
         hash.push((uint32_t)lobe);
         if (!(ci > 0.0f) || !(pb > 0.0f)) { hash.push(0u); break; }
         hash.push(1u);
-        beta = mul(beta, brdf_eval(wi, wo, n, m)) * (ci / pb);
+        beta = mul(beta, fi) * (ci / pb);
         p_prev = pb;
         o = x; d = wi; exclude = f;
     }

@@ -298,8 +298,9 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                     V3 ct{0.f, 0.f, 0.f};
                     if (c > 0.0f && pe > 0.0f) {
                         tmax = __int_as_float(0x7f800000);
-                        const float den = pe + bsdf_pdf(we, wo, n, m.a, S.vndf);
-                        ct = mul(beta, mul(env_rgb(S, tex), brdf_eval(we, wo, n, m, lo))) * (c / den);
+                        float pdf;
+                        const V3 fe = brdf_eval_pdf(we, wo, n, m, lo, S.vndf, pdf);
+                        ct = mul(beta, mul(env_rgb(S, tex), fe)) * (c / (pe + pdf));
                     }
                     const size_t e = (size_t)S.nl * q.cap + i;
                     if (tmax >= 0.0f) {
@@ -317,12 +318,12 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                     const float4 u = draw4(ctr, k, 2, key);
                     const int lobe = bsdf_sample(u, wo, n, m.a, S.vndf, wi);
                     const float ci = dot(n, wi);
-                    pb = bsdf_pdf(wi, wo, n, m.a, S.vndf);
+                    const V3 fi = brdf_eval_pdf(wi, wo, n, m, lo, S.vndf, pb);
                     info = 1u | ((uint32_t)lobe << 1);
                     if (ci > 0.0f && pb > 0.0f) {
                         info |= 4u;
                         emit = true;
-                        beta = mul(beta, brdf_eval(wi, wo, n, m, lo)) * (ci / pb);
+                        beta = mul(beta, fi) * (ci / pb);
                     }
                 }
                 // the shading record: the shadow rays' origin and excluded face (fused:
