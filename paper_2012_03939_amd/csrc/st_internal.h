@@ -143,10 +143,16 @@ enum RCol {
     RINFO,                          // bit 0: continued, bit 1: lobe, bit 2: emitted
     RTEX,                           // environment texel of its shadow ray
     RNEXT,                          // index in the next queue, -1: none
-    RNCOL
+    RNCOL,
+    RSLOT = RINFO, RVD = RTEX       // of a dense shadow record: the path's QQ and QVD words
 };
 
-// columns of a shadow entry (l * cap + i): direction, length, contribution
+// Columns of a shadow entry: direction, length, contribution.  With several entries per
+// shading point, entry l of point i lies at l * cap + i, its origin in record i.  With
+// one (fused), the entry that carries a ray and columns RX0 .. RVD of its record lie
+// densely, in the order of the shadow list, which is not written: of two side rays
+// usually one meets a face, and records at i left every other word of a line unwritten
+// (1.56 GB written for 1.0 GB of records in a launch of 16.8M side rays).
 enum SCol { SWX, SWY, SWZ, STMAX, SCR, SCG, SCB, SNCOL };
 
 // Counters from which the waves of a traversal kernel take their work (wave_tiles),

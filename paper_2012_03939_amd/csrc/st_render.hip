@@ -150,20 +150,19 @@ __host__ __device__ __forceinline__ bool shadow_fused(const FwdParams& p, const 
 }
 
 // shading of bounce k: escapes, next-event set-up and BRDF continuation.
-// HASH: decision hashes are asked for (p.dbg_hash or p.hash_by_q); compiled
-// apart, because the hash state alone made the compiler spill 11 more dwords.
+// MODE: one shadow entry per shading point (shadow_fused), several, or several with
+// decision hashes asked for (p.dbg_hash or p.hash_by_q); compiled apart, because what
+// one of them holds (an entry until its place is known; the hash) is spilled in all.
 // ONE: the launch has one scene.  FROM: where the entries come from: later bounces
 // (k >= 2), camera rays or side rays (k == 1).
 enum { FROM_LATER, FROM_CAMERA, FROM_SIDE };
-template <bool HASH, bool ONE, int FROM>
+enum { MODE_FUSED, MODE_LISTED, MODE_HASH };
+template <int MODE, bool ONE, int FROM>
 __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Queues q, int k, long long q0) {
     __shared__ int resv[2 * (SHADE_BLOCK / 64 + 1)];
     const int n = q.cnt[k];
     const int stride = gridDim.x * blockDim.x;
-    constexpr bool hashing = HASH;
-    // with the shadow sum fused into k_shadow, the shading record keeps only what
-    // k_shadow reads (face, point)
-    const bool fused = shadow_fused(p, q);
+    constexpr bool hashing = MODE == MODE_HASH, fused = MODE == MODE_FUSED;
     // every thread of a block runs the same number of iterations: the
     // compaction below reserves queue slots per block
     for (int b0 = blockIdx.x * blockDim.x; b0 < n; b0 += stride) {
@@ -175,6 +174,8 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
         uint32_t rays = 0;          // shadow entries of this shading point that carry a ray
         V3 x{0.f, 0.f, 0.f}, wi{0.f, 0.f, 0.f}, beta{0.f, 0.f, 0.f};
         float pb = 0.0f;
+        V3 ws{0.f, 0.f, 0.f}, cs{0.f, 0.f, 0.f};    // fused: the entry, until it has its place
+        float ts = 0.0f;
         int f = -1;
         uint32_t hv = 0;
         // path identity (slot, counters, camera | domain), carried to the continuation
@@ -208,8 +209,10 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                     c1 = cc.c1;
                     vd = (uint32_t)v;
                     // for the shadow kernels and the hashes of this bounce
-                    r.u(QQ, pq);
-                    r.u(QVD, vd);
+                    if (!fused) {
+                        r.u(QQ, pq);
+                        r.u(QVD, vd);
+                    }
                     if (hashing) { r.u(QC0, c0); r.u(QC1, c1); }
                 }
                 if (FROM == FROM_SIDE) {
@@ -279,10 +282,16 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                     // k_shadow_sum reads the contribution of an unoccluded one)
                     const size_t e = (size_t)l * q.cap + i;
                     if (tmax >= 0.0f) {
-                        const ShRow sh(q.sh, e);
-                        sh.v(SWX, wl);
-                        sh.f(STMAX, tmax);
-                        sh.v(SCR, ct);
+                        if (fused) {
+                            ws = wl;
+                            ts = tmax;
+                            cs = ct;
+                        } else {
+                            const ShRow sh(q.sh, e);
+                            sh.v(SWX, wl);
+                            sh.f(STMAX, tmax);
+                            sh.v(SCR, ct);
+                        }
                         rays |= 1u << l;
                     } else if (!fused) {
                         q.socc[e] = 0;
@@ -304,10 +313,16 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                     }
                     const size_t e = (size_t)S.nl * q.cap + i;
                     if (tmax >= 0.0f) {
-                        const ShRow sh(q.sh, e);
-                        sh.v(SWX, we);
-                        sh.f(STMAX, tmax);
-                        sh.v(SCR, ct);
+                        if (fused) {
+                            ws = we;
+                            ts = tmax;
+                            cs = ct;
+                        } else {
+                            const ShRow sh(q.sh, e);
+                            sh.v(SWX, we);
+                            sh.f(STMAX, tmax);
+                            sh.v(SCR, ct);
+                        }
                         rays |= 1u << S.nl;
                     } else if (!fused) {
                         q.socc[e] = 0;
@@ -326,9 +341,8 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
                         beta = mul(beta, fi) * (ci / pb);
                     }
                 }
-                // the shading record: the shadow rays' origin and excluded face (fused:
-                // read only through the listed entries)
-                if (!fused || rays) {
+                // the shading record: the shadow rays' origin and excluded face
+                if (!fused) {
                     rec.u(RFACE, (uint32_t)f);
                     rec.v(RX0, x);
                 }
@@ -351,6 +365,21 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
         if ((emit && o >= q.cap) || (rays && (long long)oo.y + __popc(rays) > (long long)q.cap * max(q.nent, 1))) {
             atomicOr(p.err, ERR_QUEUE);
             emit = false;
+            rays = 0;
+        }
+        if (fused) {
+            if (rays) {
+                const ShRow sh(q.sh, (uint32_t)oo.y);
+                sh.v(SWX, ws);
+                sh.f(STMAX, ts);
+                sh.v(SCR, cs);
+                const RecRow so(q.rec, (uint32_t)oo.y);
+                so.v(RX0, x);
+                so.u(RFACE, (uint32_t)f);
+                so.u(RSLOT, pq);
+                // (the counting traversals look their scene up by ray in any launch)
+                if (!ONE || !p.fast) so.u(RVD, vd);
+            }
             rays = 0;
         }
         for (int so = oo.y; rays; rays &= rays - 1, ++so)
@@ -378,21 +407,21 @@ __global__ void __launch_bounds__(SHADE_BLOCK) SHADE_OCC k_shade(FwdParams p, Qu
 template <bool FAST, bool ONE>
 __device__ __forceinline__ void shadow_one(const FwdParams& p, const Queues& q, int k, int w, bool fused,
                                            const TraceGeo& GW, TravStack& st) {
-    const uint32_t e = qld(q.slist + w);
-    const uint32_t i = fused ? e : e % (uint32_t)q.cap;        // (fused: one entry per shading point)
+    // fused: the records lie in list order (see SCol)
+    const uint32_t e = fused ? (uint32_t)w : qld(q.slist + w);
+    const uint32_t i = fused ? e : e % (uint32_t)q.cap;
     const RecRow rec(q.rec, i);
-    const RayRow r(q.ray[k & 1], i);
     const ShRow sh(q.sh, e);
     const int f = (int)rec.u(RFACE);
-    const TraceGeo G = ONE ? GW : lane_geo(p.scenes[p.cams[r.u(QVD) & 0xFFFFu].scene]);
+    const TraceGeo G = ONE ? GW : lane_geo(p.scenes[p.cams[(fused ? rec.u(RVD) : RayRow(q.ray[k & 1], i).u(QVD)) & 0xFFFFu].scene]);
     const float tmax = sh.f(STMAX);
     const V3 o = rec.v(RX0), dd = sh.v(SWX);
     const bool occluded = trace_any<FAST>(G, o, dd, TMIN, tmax, f, st);
     if (fused) {
         if (occluded) {
-            if (p.rec_occ) p.rec_occ[(size_t)(k - 1) * p.rec_n + r.u(QQ)] = 1u;
+            if (p.rec_occ) p.rec_occ[(size_t)(k - 1) * p.rec_n + rec.u(RSLOT)] = 1u;
         } else {
-            float* L = q.L + 3 * (size_t)r.u(QQ);
+            float* L = q.L + 3 * (size_t)rec.u(RSLOT);
             const V3 c = sh.v(SCR);
             L[0] += c.x; L[1] += c.y; L[2] += c.z;
         }
@@ -619,11 +648,15 @@ void launch_wavefront_bounces(const FwdParams& p, Queues& q, int n, long long q0
     const bool fused = shadow_fused(p, q), side = q0 < 0;
     const bool one = p.fast && p.nscenes == 1, hashing = p.dbg_hash || p.hash_by_q;
     using Shade = void (*)(FwdParams, Queues, int, long long);
-    constexpr Shade shades[2][2][3] = {      // [hashing][one scene][from]
-        {{k_shade<false, false, FROM_LATER>, k_shade<false, false, FROM_CAMERA>, nullptr},
-         {k_shade<false, true, FROM_LATER>, k_shade<false, true, FROM_CAMERA>, k_shade<false, true, FROM_SIDE>}},
-        {{k_shade<true, false, FROM_LATER>, k_shade<true, false, FROM_CAMERA>, nullptr},
-         {k_shade<true, true, FROM_LATER>, k_shade<true, true, FROM_CAMERA>, k_shade<true, true, FROM_SIDE>}}};
+    // (side rays come with one scene)
+    constexpr Shade shades[3][2][3] = {      // [mode][one scene][from]
+        {{k_shade<MODE_FUSED, false, FROM_LATER>, k_shade<MODE_FUSED, false, FROM_CAMERA>, nullptr},
+         {k_shade<MODE_FUSED, true, FROM_LATER>, k_shade<MODE_FUSED, true, FROM_CAMERA>, k_shade<MODE_FUSED, true, FROM_SIDE>}},
+        {{k_shade<MODE_LISTED, false, FROM_LATER>, k_shade<MODE_LISTED, false, FROM_CAMERA>, nullptr},
+         {k_shade<MODE_LISTED, true, FROM_LATER>, k_shade<MODE_LISTED, true, FROM_CAMERA>, k_shade<MODE_LISTED, true, FROM_SIDE>}},
+        {{k_shade<MODE_HASH, false, FROM_LATER>, k_shade<MODE_HASH, false, FROM_CAMERA>, nullptr},
+         {k_shade<MODE_HASH, true, FROM_LATER>, k_shade<MODE_HASH, true, FROM_CAMERA>, k_shade<MODE_HASH, true, FROM_SIDE>}}};
+    const int mode = hashing ? MODE_HASH : fused ? MODE_FUSED : MODE_LISTED;
     const auto extend = side ? (p.fast ? k_extend<true, true, true> : k_extend<false, true, true>)
                         : one ? k_extend<true, true, false>
                         : p.fast ? k_extend<true, false, false> : k_extend<false, false, false>;
@@ -637,7 +670,7 @@ void launch_wavefront_bounces(const FwdParams& p, Queues& q, int n, long long q0
     for (int k = 1; k <= last; ++k) {
         // bounce k is traced: shade it, then trace its shadow rays together with
         // the extension rays of bounce k + 1
-        ST_LAUNCH("k_shade", shades[hashing][p.nscenes == 1][k > 1 ? FROM_LATER : side ? FROM_SIDE : FROM_CAMERA],
+        ST_LAUNCH("k_shade", shades[mode][p.nscenes == 1][k > 1 ? FROM_LATER : side ? FROM_SIDE : FROM_CAMERA],
                   dim3(grid_for(n, SHADE_BLOCK, gmax)), dim3(SHADE_BLOCK), 0, st, p, q, k, q0);
         if (hook) hook->tick();
         if (k <= p.B && k < last) {
