@@ -362,7 +362,7 @@ __device__ __forceinline__ void wave_sync_lds() {
 // code, box (lower, upper), SAH cost; whoever finishes a subtree writes its half of
 // the parent's record and counts its arrival, the second to arrive goes on with the
 // parent.  A treelet reads one record per entry it opens, 8 lanes to a record.
-// Subtrees that lie inside a block's TL_SPAN leaves (a radix tree's nodes cover
+// Subtrees that lie inside a block's leaves (a radix tree's nodes cover
 // ranges of leaves, and node i's range has i at one end) are built in LDS; the nodes
 // above go through global memory with agent-scope accesses (coherent across the XCDs'
 // L2s without flushing them; a hand-off needs only the wave's own stores drained).
@@ -371,18 +371,20 @@ __device__ __forceinline__ void wave_sync_lds() {
 // ---------------------------------------------------------------------------
 constexpr int TL_LEAVES = 7;
 constexpr float TL_C_INNER = 1.2f;
-#ifndef ST_TL_SPAN
-#define ST_TL_SPAN 512
-#endif
-#ifndef ST_TL_PER_WAVE
-#define ST_TL_PER_WAVE 32
-#endif
-constexpr int TL_SPAN = ST_TL_SPAN;             // leaves per block
-constexpr int TL_PER_WAVE = ST_TL_PER_WAVE;     // leaves each wave starts from
-constexpr int TL_WAVES = TL_SPAN / TL_PER_WAVE;
+// A wave starts from PER leaves and a block is two waves, whose 2 PER leaves make the
+// part of the tree built in LDS.  The fewer leaves a wave has, the fewer treelets of one
+// level it does in turn; but the waves should all be resident (four a SIMD: 4,096), so PER
+// is the least of 16, 32 and 64 that keeps to that (tl_per_wave).  k_treelets at 320,
+// 5,120, 40,000, 100k and 500k faces: with 16 leaves 70, 108, 145, 211, 739 us, with 32 92, 127, 160,
+// 198, 558, with 64 117, 170, 197, 219, 466; blocks of 16 waves of 32, which left most
+// CUs without one, took 88, 186, 234, 257, 805.
+constexpr int TL_WAVES = 2;
 constexpr int TL_BLOCK = 64 * TL_WAVES;
+constexpr int TL_RESIDENT = 4096;
 constexpr int TL_GUARD = 1 << 16;
-static_assert(TL_PER_WAVE <= 64 && TL_BLOCK <= 1024, "leaves per wave");
+static inline int tl_per_wave(int nf) {
+    return nf <= 16 * TL_RESIDENT ? 16 : nf <= 32 * TL_RESIDENT ? 32 : 64;
+}
 
 __device__ __forceinline__ float tl_area(float dx, float dy, float dz) {
 #pragma clang fp contract(off)
@@ -711,20 +713,22 @@ __device__ __forceinline__ void tl_climb(const Mem& mem, TlHalf& h, int& up, boo
     }
 }
 
+template <int PER>
 __global__ __launch_bounds__(TL_BLOCK) void k_treelets(const int* __restrict__ kup, const int2* __restrict__ range,
                                                        const uint32_t* __restrict__ sface, const float4* __restrict__ bmin,
                                                        const float4* __restrict__ bmax, int n, uint32_t* rec, int* cnt,
                                                        uint32_t* err) {
-    __shared__ uint64_t recs[8 * TL_SPAN];
-    __shared__ int cnts[TL_SPAN];
+    constexpr int SPAN = PER * TL_WAVES;
+    __shared__ uint64_t recs[8 * SPAN];
+    __shared__ int cnts[SPAN];
     __shared__ TlLds lds[TL_WAVES];
     const int lane = threadIdx.x & 63, w = (int)(threadIdx.x >> 6);
     TlLds& T = lds[w];
-    const int lo = blockIdx.x * TL_SPAN, hi = min(n, lo + TL_SPAN) - 1;
-    for (int i = threadIdx.x; i < TL_SPAN; i += TL_BLOCK) cnts[i] = 0;
+    const int lo = blockIdx.x * SPAN, hi = min(n, lo + SPAN) - 1;
+    for (int i = threadIdx.x; i < SPAN; i += TL_BLOCK) cnts[i] = 0;
     const TlPlan plan = tl_plan(lane);
-    const int leaf = lo + w * TL_PER_WAVE + lane;
-    bool on = lane < TL_PER_WAVE && leaf <= hi;
+    const int leaf = lo + w * PER + lane;
+    bool on = lane < PER && leaf <= hi;
     TlHalf h;
     int up = -1;
     if (on) {
@@ -1327,7 +1331,9 @@ void launch_scene_geometry(SceneDev& s, hipStream_t st) {
     ST_LAUNCH("k_tree_init", k_tree_init, dim3(nb(nf, 256)), dim3(256), 0, st, sm, sf, nf, s.kup, s.krange, s.keys64,
               s.refit_cnt, s.bmin, s.bmax, s.V, s.F, s.aabb, s.tri, s.fleaf);
     if (nf > 1) {
-        ST_LAUNCH("k_treelets", k_treelets, dim3(nb(nf, TL_SPAN)), dim3(TL_BLOCK), 0, st, s.kup, s.krange, sf, s.bmin,
+        const int per = tl_per_wave(nf);
+        const auto treelets = per == 16 ? k_treelets<16> : per == 32 ? k_treelets<32> : k_treelets<64>;
+        ST_LAUNCH("k_treelets", treelets, dim3(nb(nf, per * TL_WAVES)), dim3(TL_BLOCK), 0, st, s.kup, s.krange, sf, s.bmin,
                   s.bmax, nf, s.trec, s.refit_cnt, s.err);
         ST_LAUNCH("k_tree_unpack", k_tree_unpack, dim3(nb(nf - 1, 256)), dim3(256), 0, st, s.trec, nf, s.child, s.parent,
                   s.aabb, s.refit_cnt);

@@ -55,3 +55,18 @@ def test_sort_of_many_tiles(B, nf):
     assert np.all(keys[1:] > keys[:-1])
     assert np.array_equal(np.sort((keys & 0xFFFFFFFF).astype(np.int64)), np.arange(nf))
     g.check_errors()
+
+
+@pytest.mark.parametrize("nf", [31, 32, 33, 65, 65536, 65537, 131072, 131073, 131137])
+def test_tree_bit_exact_at_wave_shares(B, nf):
+    """Around the leaf counts of a block and those at which a wave starts from more leaves."""
+    _say(f"case rebuild: {nf} faces against the oracle's tree, wave shares")
+    V, F = S.noise_sphere(82, 0.2, noise_seed=6)
+    F = F[np.random.default_rng(nf).permutation(F.shape[0])[:nf]]
+    V = V.astype(np.float32)
+    g = B.GPUScene(V, F, S.uniform_materials(nf))
+    for got, want in zip(g.lbvh(), O.lbvh(V, F, treelet_rounds=O.TREELET_ROUNDS)):
+        got = got.cpu().numpy()
+        want = want.view(got.dtype)
+        assert np.array_equal(got.reshape(-1).view(np.uint8), want.reshape(-1).view(np.uint8))
+    g.check_errors()
