@@ -84,7 +84,7 @@ typedef struct {
     float edge_spp_ratio;            /* primary edge samples per (pixel x spp) of each view; with
                                         ST_EDGE_SHADOW as many shadow-edge samples per (view, light) */
     int64_t queue_capacity;          /* wavefront chunk size in path samples (0: the scene's autotuned value,
-                                        else 2^24) */
+                                        else 2^25, or 2^24 where that needs too much memory) */
     uint32_t* debug_decision_hash;   /* device, optional: one FNV-1a hash of the discrete decisions per
                                         path sample, index ((pixel offset of view + y*W + x) * spp + j) */
     uint32_t* debug_edge_hash;       /* device, optional (backward): one hash per primary edge sample,

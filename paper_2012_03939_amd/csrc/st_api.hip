@@ -320,10 +320,13 @@ uint64_t record_key(const st_scene* sc, const st_camera* cams, int ncam, int spp
 }
 
 constexpr size_t REC_MAX_BYTES = 16ull << 30;
-// wavefront chunk (paths per pass of the bounce kernels) without tuning: each
+// Wavefront chunk (paths per pass of the bounce kernels) without tuning: each
 // launch ends in a drain where its longest rays run alone, so larger chunks
-// waste less; 2^24 paths hold about 3.3 GB of queues with one shadow entry
-constexpr long long DEFAULT_QUEUE_CAP = 1ll << 24;
+// waste less.  2^25 paths hold about 6.6 GB of queues with one shadow entry; where
+// those do not fit the caller's cap, the device, or (captured) the buffer that is
+// there, 2^24 paths.  2^23, 2^24, 2^25, 2^26 paths: 1024^2 view at 32 spp 5.15, 4.37, 4.00,
+// 4.00 ms; 24-view batch 17.8, 17.0, 16.7, 16.7; 40k-face step 79.4, 75.4, 73.5, 72.6.
+constexpr long long DEFAULT_QUEUE_CAP = 1ll << 25, FALLBACK_QUEUE_CAP = 1ll << 24;
 
 // chunk size for n items with at most cap per chunk: the same number of chunks,
 // of equal size (rounded up to an even multiple of 256), so that no chunk is a
@@ -383,9 +386,15 @@ void carve_queues(char* base, int cap, int nent, float* L, uint32_t* spill, Queu
     q.nent = nent;
 }
 
-int make_queues(st_scene* sc, int cap, int nent, float* L, Queues& q) {
-    cap = queue_cap(cap, nent);
+// queues of want paths, or of fallback (0: none) where those cannot be had
+int make_queues(st_scene* sc, long long want, long long fallback, int nent, float* L, Queues& q) {
+    int cap = queue_cap(want, nent);
     int rc = sc->qbuf.ensure(queue_bytes(cap, nent));
+    if (rc && fallback > 0 && fallback < want) {
+        (void)hipGetLastError();
+        cap = queue_cap(fallback, nent);
+        rc = sc->qbuf.ensure(queue_bytes(cap, nent));
+    }
     if (rc) return rc;
     carve_queues((char*)sc->qbuf.p, cap, nent, L, (uint32_t*)sc->spillbuf.p, q);
     return ST_OK;
@@ -408,11 +417,16 @@ int render_impl(st_scene* owner, st_scene* const* scenes, int nscenes, const st_
     }
     // workspace of the call, checked against the caller's cap before any kernel
     const bool mega = (o.flags & ST_FORWARD_MEGAKERNEL) != 0;
-    long long cap = o.queue_capacity > 0 ? o.queue_capacity : (owner->tuned_cap > 0 ? owner->tuned_cap : DEFAULT_QUEUE_CAP);
-    cap = std::min<long long>(cap, 1ll << 28);
-    cap = balanced_chunk(cs.total_paths, cap);
-    const size_t need = (size_t)cs.total_paths * 3 * sizeof(float) + SPILL_BYTES +
-                        (mega ? 0 : queue_bytes(queue_cap(cap, nent), nent));
+    const long long want_cap = o.queue_capacity > 0 ? o.queue_capacity : owner->tuned_cap;
+    const long long fallback = want_cap > 0 ? 0 : balanced_chunk(cs.total_paths, FALLBACK_QUEUE_CAP);
+    long long cap = balanced_chunk(cs.total_paths, std::min<long long>(want_cap > 0 ? want_cap : DEFAULT_QUEUE_CAP, 1ll << 28));
+    auto need_of = [&](long long chunk) {
+        return (size_t)cs.total_paths * 3 * sizeof(float) + SPILL_BYTES + (mega ? 0 : queue_bytes(queue_cap(chunk, nent), nent));
+    };
+    const size_t rec_bytes = (size_t)(2 * bounces + 1) * (size_t)cs.total_paths * sizeof(int);
+    // (the records below rather than the larger chunk)
+    if (fallback && o.max_workspace_bytes > 0 && need_of(cap) + rec_bytes > (size_t)o.max_workspace_bytes) cap = fallback;
+    const size_t need = need_of(cap);
     rc = over_budget(o, need);
     if (rc) return rc;
     rc = owner->Lbuf.ensure((size_t)cs.total_paths * 3 * sizeof(float));
@@ -439,7 +453,6 @@ int render_impl(st_scene* owner, st_scene* const* scenes, int nscenes, const st_
     p.rec_occ = nullptr;
     p.rec_n = 0;
     // hit records for the backward of a single-scene wavefront render
-    const size_t rec_bytes = (size_t)(2 * bounces + 1) * (size_t)cs.total_paths * sizeof(int);
     // (an optimisation of the backward: left out rather than exceed the cap)
     const bool want_rec = nscenes == 1 && !mega && scenes[0]->d.nl <= 30 && rec_bytes <= REC_MAX_BYTES &&
                           !(o.max_workspace_bytes > 0 && need + rec_bytes > (size_t)o.max_workspace_bytes);
@@ -460,7 +473,7 @@ int render_impl(st_scene* owner, st_scene* const* scenes, int nscenes, const st_
         launch_forward_mega(p, L, cs.total_paths, (uint32_t*)owner->spillbuf.p, TRACE_GRID, s);
     } else {
         Queues q;
-        rc = make_queues(owner, (int)cap, nent, L, q);
+        rc = make_queues(owner, cap, fallback, nent, L, q);
         if (rc) return rc;
         q.grid = owner->tuned_grid;
         launch_forward_wavefront(p, q, cs.total_paths, has_env_any, nent, s);
@@ -1088,9 +1101,10 @@ int st_render_backward(st_scene* sc, const st_camera* cams, int32_t ncam, int32_
     const bool defer_sec = (o.flags & ST_EDGE_SECONDARY) && !o.debug_decision_hash && cs.total_paths > 0 && ne > 0;
     const bool prim = (o.flags & ST_EDGE_PRIMARY) && cs.total_edges > 0 && ne > 0;
     const int nent_side = sc->d.nl + (sc->d.has_env ? 1 : 0);
-    long long side_cap = o.queue_capacity > 0 ? o.queue_capacity : (sc->tuned_cap > 0 ? sc->tuned_cap : DEFAULT_QUEUE_CAP);
-    side_cap = std::min<long long>(side_cap, 1ll << 28);
-    side_cap = balanced_chunk(2 * cs.total_edges, side_cap) & ~1ll;     // two side paths per edge sample
+    const long long want_cap = o.queue_capacity > 0 ? o.queue_capacity : sc->tuned_cap;
+    // (two side paths per edge sample)
+    const long long side_fallback = want_cap > 0 ? 0 : balanced_chunk(2 * cs.total_edges, FALLBACK_QUEUE_CAP) & ~1ll;
+    long long side_cap = balanced_chunk(2 * cs.total_edges, std::min<long long>(want_cap > 0 ? want_cap : DEFAULT_QUEUE_CAP, 1ll << 28)) & ~1ll;
     if (prim && 2 * cs.total_edges >= (1ll << 32)) return fail(ST_ERR_INVALID_ARG, "too many primary edge samples");
     // hit records of this pass's forward, when the scene holds them in a buffer
     // large enough (the adjoint still checks on the device that they are this
@@ -1105,10 +1119,14 @@ int st_render_backward(st_scene* sc, const st_camera* cams, int32_t ncam, int32_
         size_t need = SPILL_BYTES + pbytes + (defer_sec ? sec_workspace_bytes(cs.total_paths, bounces) : 0) +
                       (adj_listed ? adj_list_bytes(cs.total_paths) : 0) +
                       ((o.flags & 5u) && cs.total_paths > 0 ? adj_vrec_bytes(bounces) : 0);
-        if (prim)
+        if (prim) {
             need += (size_t)cs.total_edges * 6 * sizeof(float) +
-                    (o.debug_edge_hash ? (size_t)cs.total_edges * 2 * sizeof(uint32_t) : 0) +
-                    queue_bytes(queue_cap(side_cap, nent_side), nent_side);
+                    (o.debug_edge_hash ? (size_t)cs.total_edges * 2 * sizeof(uint32_t) : 0);
+            if (side_fallback && o.max_workspace_bytes > 0 &&
+                need + queue_bytes(queue_cap(side_cap, nent_side), nent_side) > (size_t)o.max_workspace_bytes)
+                side_cap = side_fallback;
+            need += queue_bytes(queue_cap(side_cap, nent_side), nent_side);
+        }
         rc = over_budget(o, need);
         if (rc) return rc;
     }
@@ -1213,13 +1231,14 @@ int st_render_backward(st_scene* sc, const st_camera* cams, int32_t ncam, int32_
             if (rc) return rc;
             hside = (uint32_t*)sc->sidehash.p;
         }
-        rc = make_queues(sc, (int)side_cap, nent_side, (float*)sc->sidebuf.p, q);
+        // (before the queues, which can do with less)
+        if (overlap) {
+            rc = sc->spill_aux.ensure(SPILL_BYTES);
+            if (rc) return rc;
+        }
+        rc = make_queues(sc, side_cap, side_fallback, nent_side, (float*)sc->sidebuf.p, q);
         if (rc) return rc;
         q.grid = sc->tuned_grid;
-    }
-    if (overlap) {
-        rc = sc->spill_aux.ensure(SPILL_BYTES);
-        if (rc) return rc;
     }
     // the adjoint's launch on the second stream, after the side paths' first
     // FORK_AFTER_LAUNCHES launches on this one (at once when there are none)
