@@ -192,7 +192,7 @@ struct Queues {
     uint32_t* rec;           // RNCOL columns; hits and shading points of the current bounce
     uint32_t* sh;            // SNCOL columns; shadow entries
     uint8_t* socc;           // outcome code of a shadow entry: 0 no ray, 1 occluded, 2 unoccluded
-    uint32_t* slist;         // shadow entries (l * cap + i) that carry a ray, compacted per bounce
+    uint32_t* slist;         // several entries per point: those (l * cap + i) that carry a ray, compacted per bounce
     int* cnt;                // ray counts per bounce (k), shadow-ray counts per bounce (32 + k)
     int* take;               // wave_tiles counters: set k (extension rays of bounce k), 16 + k (shadow rays of bounce k)
     uint32_t* spill;         // traversal stack spill

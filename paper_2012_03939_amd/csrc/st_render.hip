@@ -1,10 +1,10 @@
 // Forward rendering R(x, m, c_i) (Shape from Tracing, Sec. 3.2) as a wavefront
 // path tracer: per bounce a closest-hit kernel over a compacted ray queue, a
-// shading kernel (next-event estimation set-up, BRDF sampling, wave-ballot
-// compaction of the surviving paths) and a per-path shadow kernel that traces
-// the point-light and environment shadow rays and adds their contributions in a
-// fixed order.  Queues are structure-of-arrays in HBM; per-sample radiance is
-// kept for a final film pass that averages the samples of each pixel.
+// shading kernel (next-event estimation set-up, BRDF sampling, block-wise
+// compaction of the surviving paths and of the shadow entries) and the shadow rays
+// of the listed entries, whose contributions are added in a fixed order.  Queues lie
+// in HBM in blocks of 64 entries; per-sample radiance is kept for a final film pass
+// that averages the samples of each pixel.
 #include "st_internal.h"
 
 namespace st {
@@ -155,6 +155,10 @@ __host__ __device__ __forceinline__ bool shadow_fused(const FwdParams& p, const 
 // one of them holds (an entry until its place is known; the hash) is spilled in all.
 // ONE: the launch has one scene.  FROM: where the entries come from: later bounces
 // (k >= 2), camera rays or side rays (k == 1).
+// First bounces are bound by vector issue (80-89 % of the SIMD cycles, 55-66 % of the
+// lanes: the misses idle), later ones by memory latency.  Six waves per SIMD: with the
+// 80 registers the compiler spills at most 4 dwords; 5, 6 and 8 waves took 21.7, 19.8 and
+// 21.1 ms of a 40k-face step of 16 views of 512^2.
 enum { FROM_LATER, FROM_CAMERA, FROM_SIDE };
 enum { MODE_FUSED, MODE_LISTED, MODE_HASH };
 template <int MODE, bool ONE, int FROM>

@@ -53,7 +53,13 @@ def _short(name: str) -> str:
     n = name.split("(")[0]
     if n.startswith("void "):
         n = n[5:]
-    return n[4:] if n.startswith("st::") else n
+    n = n[4:] if n.startswith("st::") else n
+    # instantiations that one launch name covers (traversal variants, kinds of queue
+    # entries) are one row; the adjoint's passes stay apart, without their traversal variant
+    base, _, args = n.partition("<")
+    if base == "k_adjoint":
+        return base + "<" + ", ".join(args.rstrip(">").split(", ")[:3]) + ">"
+    return base if base.startswith("k_") else n
 
 
 def read_counters(d: str):
@@ -123,11 +129,14 @@ def pmc_summary(fetch_dir, write_dir, copy_fetch_dir, copy_write_dir, sq_dirs=()
 
 
 def trace_table(stats_csv: str, top: int = 24):
-    rows = []
+    calls, total, share = collections.Counter(), collections.Counter(), collections.Counter()
     with open(stats_csv) as fh:
         for r in csv.DictReader(fh):
-            rows.append((_short(r["Name"]), int(r["Calls"]), float(r["TotalDurationNs"]) / 1e6,
-                         float(r["AverageNs"]) / 1e3, float(r["Percentage"])))
+            k = _short(r["Name"])
+            calls[k] += int(r["Calls"])
+            total[k] += float(r["TotalDurationNs"]) / 1e6
+            share[k] += float(r["Percentage"])
+    rows = [(k, calls[k], total[k], total[k] / calls[k] * 1e3, share[k]) for k in calls]
     rows.sort(key=lambda r: -r[2])
     lines = ["| kernel | calls | total ms | avg us | % |", "|---|---|---|---|---|"]
     for name, calls, tot, avg, pct in rows[:top]:
