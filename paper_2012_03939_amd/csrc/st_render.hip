@@ -549,7 +549,13 @@ __global__ void __launch_bounds__(TRACE_BLOCK) k_forward_mega(FwdParams p, float
     }
 }
 
-// film: average the spp samples of each pixel in sample order
+// Film: the average of each pixel's spp samples, added in sample order.  Bound by the
+// read of 12 bytes per sample.  Threads take the pixels in the order of the samples
+// (8x8 tiles), so a wave reads 768 consecutive bytes of each sample plane, one 12-byte
+// load a lane, four planes in flight; in scan order each line of a plane went to eight
+// waves and was fetched twice (67M samples: 1.66 GB for 0.81, 297 us; now 135 us; a 1024^2
+// view at 32 spp 135 -> 64 us).
+typedef float film3 __attribute__((ext_vector_type(3), aligned(4)));
 __global__ void k_film(const DevCam* __restrict__ cams, const long long* __restrict__ pixoff, int ncam, int spp,
                        const float* __restrict__ L, long long npix, float* out, uint32_t* err,
                        unsigned long long* key_dev, unsigned long long key) {
@@ -558,19 +564,19 @@ __global__ void k_film(const DevCam* __restrict__ cams, const long long* __restr
     for (long long g = blockIdx.x * (long long)blockDim.x + threadIdx.x; g < npix; g += stride) {
         const int v = find_view(pixoff, ncam, g);
         const DevCam& c = cams[v];
-        const int p = (int)(g - c.pixoff);
-        const int x = p % c.W, y = p / c.W;
-        int pt;
-        if ((c.W & 7) == 0 && (c.H & 7) == 0) pt = (((y >> 3) * (c.W >> 3) + (x >> 3)) << 6) | ((y & 7) << 3) | (x & 7);
-        else pt = p;
+        int x, y, j0;
+        decode_path(c, g - c.pixoff, spp, x, y, j0);
         const long long hw = (long long)c.W * c.H;
+        const float* plane = L + 3 * (c.qoff + (g - c.pixoff));
         float a = 0.f, b = 0.f, cc = 0.f;
-        for (int j = 0; j < spp; ++j) {
-            const long long qq = c.qoff + (long long)j * hw + pt;
-            a += qld(L + 3 * qq); b += qld(L + 3 * qq + 1); cc += qld(L + 3 * qq + 2);
+#pragma unroll 4
+        for (int j = 0; j < spp; ++j, plane += 3 * hw) {
+            const film3 s = __builtin_nontemporal_load((const film3*)plane);
+            a += s.x; b += s.y; cc += s.z;
         }
         const float inv = 1.0f / (float)spp;
-        out[3 * g] = a * inv; out[3 * g + 1] = b * inv; out[3 * g + 2] = cc * inv;
+        float* const o = out + 3 * (c.pixoff + (long long)y * c.W + x);
+        o[0] = a * inv; o[1] = b * inv; o[2] = cc * inv;
         if (!isfinite(a + b + cc)) atomicOr(err, ERR_NAN);
     }
 }
