@@ -172,14 +172,10 @@ __device__ __forceinline__ void face_reduce_add(bool has, int f, int tx, const f
 // JOBS = false: one thread per path sample (qq < total).  With p.sec_mask set,
 // an accepted secondary edge sample only marks bit k of the path's mask; its
 // side paths, its direct term and its pseudo term (propagated back along the
-// path) are left to the JOBS = true pass, two lanes per marked (path, vertex),
-// which replay the path up to that vertex, trace one side path each and add that
-// sample alone.  Accepted samples are rare, so inline they would hold whole waves for
-// one lane's side paths; as jobs they fill the lanes.  The pass is bound by the length
-// of a job's chain of dependent traversals (a wave every third cycle of a SIMD): with one
-// lane per job, which replayed the whole path with its light and environment samples and
-// traced the side paths in turn, it took 1.68 ms in a 40k-face step of 16 views of 512^2,
-// 0.44 ms in one of 32 views of 256^2 on 5k faces; now 1.05 and 0.25.
+// path) are left to the JOBS = true pass, one thread per marked (path, vertex),
+// which replays the path with the interior term off and processes that vertex
+// alone.  Accepted samples are rare, so inline they would hold whole waves for
+// one lane's side paths; as jobs they fill the lanes.
 // RECM > 0: the main pass of a backward that holds the hit records of its
 // forward and defers secondary edges, compiled without any traversal (which
 // leaves the compiler far fewer values to spill; RECM = 1 also without the
@@ -210,17 +206,15 @@ k_adjoint(BwdParams p, long long total) {
     const long long stride = (long long)gridDim.x * blockDim.x;
     // the records pass walks the list of paths that have a vertex when it is given
     const bool listed = REC && !JOBS && p.adj_list != nullptr;
-    const long long count = JOBS ? 2ll * *p.sec_njobs : listed ? (long long)*p.adj_n : total;
+    const long long count = JOBS ? (long long)*p.sec_njobs : listed ? (long long)*p.adj_n : total;
     // the main pass gives each XCD consecutive paths (their hits share that XCD's
     // L2: 18.1 -> 15.8 ms); the job pass keeps the hardware order
     const long long b0 = JOBS ? (long long)blockIdx.x : (long long)grid_block();
-    // two neighbouring lanes per job, one for each of its side paths
-    const int side = (int)(threadIdx.x & 1u);
     for (long long it = b0 * blockDim.x + threadIdx.x; it < count; it += stride) {
         int ksel = -1;
         long long qq = it;
         if (JOBS) {
-            const int2 jb = p.sec_jobs[it >> 1];
+            const int2 jb = p.sec_jobs[it];
             qq = jb.x;
             ksel = jb.y;
         } else if (listed) {
@@ -257,9 +251,6 @@ k_adjoint(BwdParams p, long long total) {
             V3 o = ld3(c.eye), d = d0, beta{1.f, 1.f, 1.f};
             int excl = -1;
             float pprev = 0.0f;
-            // (both lanes of a job replay its path up to its vertex; one counts the rays)
-            TravStack sr = st;
-            if (JOBS && side) sr.work = nullptr;
             for (int k = 1; k <= p.B + 1; ++k) {
                 float t;
                 const size_t ri = (size_t)(k - 1) * p.rec_n + qq;
@@ -268,11 +259,11 @@ k_adjoint(BwdParams p, long long total) {
                     f = qld(rec_face + ri);
                     t = f >= 0 ? face_hit_t(S, f, o, d) : __int_as_float(0x7f800000);
                 } else {
-                    f = trace_closest<FAST>(G, o, d, TMIN, excl, t, sr);
+                    f = trace_closest<FAST>(G, o, d, TMIN, excl, t, st);
                 }
                 push_face(h, f);
                 if (f < 0) {
-                    if (!JOBS && S.has_env && k > 1) {
+                    if (S.has_env && k > 1) {
                         const int tex = env_texel_of(S, d);
                         h.push((uint32_t)tex);
                         const float wv = pprev / (pprev + S.texpdf[tex]);
@@ -291,8 +282,8 @@ k_adjoint(BwdParams p, long long total) {
                 if (S.tex_res) h.push((uint32_t)tx);
                 const Mat m = load_mat(S.mat + 7 * (size_t)tx);
                 const float lo = out_lambda(wo, n, m);
-                const uint32_t rocc = !JOBS && (REC || rec_occ) ? qld(rec_occ + ri) : 0u;
-                for (int l = 0; !JOBS && l < S.nl; ++l) {
+                const uint32_t rocc = (REC || rec_occ) ? qld(rec_occ + ri) : 0u;
+                for (int l = 0; l < S.nl; ++l) {
                     const auto lt = S.lights + 6 * l;
                     const V3 dl = ld3(lt) - xh;
                     const float r2 = dot(dl, dl);
@@ -309,7 +300,7 @@ k_adjoint(BwdParams p, long long total) {
                     }
                     h.push(code);
                 }
-                if (!JOBS && S.has_env) {
+                if (S.has_env) {
                     const float4 u = draw4(ctr, k, 1, key);
                     V3 we; float pe;
                     const int tex = env_sample(S, u, we, pe);
@@ -333,7 +324,7 @@ k_adjoint(BwdParams p, long long total) {
                 }
                 const bool continues = (k < p.B) || S.has_env;
                 put(rse, k - 1, -1);
-                if (want_secondary && (!JOBS || k - 1 == ksel) && continues && S.ne > 0 && *S.etotal > 0.0f) {
+                if (want_secondary && continues && S.ne > 0 && *S.etotal > 0.0f) {
                     const float4 u = draw4(ctr, k, 3, key);
                     // the edge (-2: the hierarchy found no edge in front of the tangent
                     // plane) and 1 / (density of the edge point per unit length)
@@ -361,7 +352,7 @@ k_adjoint(BwdParams p, long long total) {
                 put(rx, k - 1, xh);
                 put(rbeta, k - 1, beta);
                 nvtx = k;
-                if (!continues || (JOBS && k - 1 == ksel)) { put(rfl, k - 1, fl); break; }
+                if (!continues) { put(rfl, k - 1, fl); break; }
                 const float4 u = draw4(ctr, k, 2, key);
                 V3 wi;
                 const int lobe = bsdf_sample(u, wo, n, m.a, S.vndf, wi);
@@ -374,7 +365,7 @@ k_adjoint(BwdParams p, long long total) {
                 fl |= R_CONT;
                 put(rfl, k - 1, fl);
                 put(rwi, k - 1, wi);
-                if (!JOBS) put(rpb, k - 1, pb);
+                put(rpb, k - 1, pb);
                 beta = mul(beta, fi) * (ci / pb);
                 pprev = pb;
                 o = xh; d = wi; excl = f;
@@ -415,24 +406,15 @@ k_adjoint(BwdParams p, long long total) {
                 if (defer) { accepted |= 1u << k; continue; }
                 const V3 mm = mv * (1.0f / ml);
                 const Ctr sc{ctr.c0, ctr.c1, (uint32_t)(k + 1) << 16, 2u};
-                V3 jump;                                   // radiance on side 0 minus that on side 1
-                if (JOBS) {
+                V3 Ls[2];
+                for (int side = 0; side < 2; ++side) {
                     const V3 dir = normalize(ud + mm * (side == 0 ? -EPS_SECONDARY : EPS_SECONDARY));
-                    const V3 Lo = trace_estimator<FAST>(S, G, xh, dir, f, p.B - (k + 1), true, sc, key, h, st);
-                    jump = Lo - V3{__shfl_xor(Lo.x, 1), __shfl_xor(Lo.y, 1), __shfl_xor(Lo.z, 1)};
-                    if (side) { nvtx = 0; break; }         // side 0 goes on with the sample
-                } else {
-                    V3 Ls[2];
-                    for (int sd = 0; sd < 2; ++sd) {
-                        const V3 dir = normalize(ud + mm * (sd == 0 ? -EPS_SECONDARY : EPS_SECONDARY));
-                        Ls[sd] = trace_estimator<FAST>(S, G, xh, dir, f, p.B - (k + 1), true, sc, key, h, st);
-                    }
-                    jump = Ls[0] - Ls[1];
+                    Ls[side] = trace_estimator<FAST>(S, G, xh, dir, f, p.B - (k + 1), true, sc, key, h, st);
                 }
                 const V3 dirk = k == 0 ? d0 : sel(rwi, k - 1);
                 const Mat m = load_mat(S.mat + 7 * (size_t)texel_of(S, f, xh));
                 const V3 fv = brdf_eval(ud, -dirk, n, m, out_lambda(-dirk, n, m));
-                const float cc = dot(mul(w, mul(sel(rbeta, k), fv)), jump) * cv * (sel(rsw, k) / r2);
+                const float cc = dot(mul(w, mul(sel(rbeta, k), fv)), Ls[0] - Ls[1]) * cv * (sel(rsw, k) / r2);
                 put(rsecc, k, cc);
                 put(rsecm, k, mv);
                 put(rfl, k, sel(rfl, k) | R_SEC);
@@ -440,7 +422,6 @@ k_adjoint(BwdParams p, long long total) {
                 atomic_add3(p.dV + 3 * (size_t)E.y, mv * (cc * te));
             }
             if (defer && accepted) p.sec_mask[qq] = (uint8_t)accepted;
-            if (JOBS && side) nvtx = 0;                    // (a job not taken adds nothing either way)
         }
 
         // ---- reverse sweep ------------------------------------------------
@@ -473,8 +454,7 @@ k_adjoint(BwdParams p, long long total) {
                     if (co > 0.0f) lo = smith_lambda_grad(co, alpha_eff(m.a));
                     V3 C{0.f, 0.f, 0.f}, gn{0.f, 0.f, 0.f}, gx = gxnext, gdummy{0.f, 0.f, 0.f};
                     float gm[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                    // (a job's sample moves the points before it; the interior terms are not its)
-                    for (int l = 0; !JOBS && l < S.nl; ++l) {
+                    for (int l = 0; l < S.nl; ++l) {
                         if (!((fl >> (8 + l)) & 1u)) continue;
                         const auto lt = S.lights + 6 * l;
                         const V3 I = ld3(lt + 3);
@@ -495,7 +475,7 @@ k_adjoint(BwdParams p, long long total) {
                         const V3 gd = (gwl - wl * dot(wl, gwl)) * (1.0f / rr) + dl * (2.0f * gr2);
                         gx = gx - gd;
                     }
-                    if (!JOBS && (fl & R_ENV)) {
+                    if (fl & R_ENV) {
                         const V3 we = sel(rwe, k);
                         const float den = sel(rden, k);
                         const V3 Le = env_rgb(S, sel(rtex, k));
@@ -506,7 +486,7 @@ k_adjoint(BwdParams p, long long total) {
                         gn = gn + we * (dot(aL, fv) / den);
                     }
                     V3 Sk = C;
-                    if (!JOBS && (fl & R_CONT)) {
+                    if (fl & R_CONT) {
                         const V3 wi = sel(rwi, k);
                         const float pb = sel(rpb, k);
                         const V3 S1 = (fl & R_ESC) ? sel(resc, k) : Snext;
@@ -544,7 +524,7 @@ k_adjoint(BwdParams p, long long total) {
 #pragma unroll
                     for (int j = 0; j < 9; ++j) atomicAdd(fa + j, vals[j]);
 #pragma unroll
-                    for (int j = 0; !JOBS && j < 7; ++j) atomicAdd(ma + j, vals[9 + j]);
+                    for (int j = 0; j < 7; ++j) atomicAdd(ma + j, vals[9 + j]);
                 }
             }
         }
