@@ -2,6 +2,7 @@
 #pragma once
 
 #include "st_device.h"
+#include "st_tiles.h"
 #include "../../include/shapetrace.h"
 
 #include <functional>
@@ -157,33 +158,29 @@ enum SCol { SWX, SWY, SWZ, STMAX, SCR, SCG, SCB, SNCOL };
 
 // Counters from which the waves of a traversal kernel take their work (wave_tiles),
 // each on its own 128-byte line.
-constexpr int TAKE_NC = 16, TAKE_SETS = 32;
+constexpr int TAKE_SETS = 32;
 constexpr int TAKE_INTS = TAKE_SETS * TAKE_NC * 32;
 
 // The tiles of 64 consecutive rays, of n, that this wave traces: fn(first ray of
 // the tile).  The first tile is the wave's own number; the others are taken from
-// the counters, of which counter c hands out every TAKE_NC-th tile, so that a wave
-// whose tiles were cheap (views and sample planes repeat with the grid's stride:
-// the same block met background, or the object, every time) goes on to others.
-// The next tile is taken before the current one is traced, which hides the
-// atomic's round trip.  A fixed share of the tiles per wave (a grid stride) kept
-// 3.9 of 8 waves per SIMD busy on average over the camera rays of 8 views of
-// 256^2; with this, 6.7 (1024^2, 32 spp render 7.72 -> 5.57 ms; those views 3.30 ->
-// 2.85 ms; 40k-face step of 16 views of 512^2 95.2 -> 87.5 ms).
+// the counters (hand_out_tiles), so that a wave whose tiles were cheap (views and
+// sample planes repeat with the grid's stride: the same block met background, or
+// the object, every time) goes on to others.  The next tile is taken before the
+// current one is traced, which hides the atomic's round trip.  A fixed share of
+// the tiles per wave (a grid stride) kept 3.9 of 8 waves per SIMD busy on average
+// over the camera rays of 8 views of 256^2; with this, 6.7 (1024^2, 32 spp render
+// 7.72 -> 5.57 ms; those views 3.30 -> 2.85 ms; 40k-face step of 16 views of 512^2
+// 95.2 -> 87.5 ms).
 template <class Fn> __device__ __forceinline__ void wave_tiles(int* counters, uint32_t n, Fn fn) {
     const uint32_t waves = gridDim.x * (TRAV_BLOCK / 64), tiles = (n + 63u) >> 6;
     const uint32_t w = blockIdx.x * (TRAV_BLOCK / 64) + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t c = w % TAKE_NC;
-    for (uint32_t t = w; t < tiles;) {
-        uint32_t next = tiles;
-        if (tiles > waves) {
-            int v = 0;
-            if (__lane_id() == 0) v = atomicAdd(counters + 32 * c, 1);
-            next = waves + (uint32_t)__builtin_amdgcn_readfirstlane(v) * TAKE_NC + c;
-        }
-        fn(t << 6);
-        t = next;
-    }
+    hand_out_tiles(w, waves, tiles,
+                   [&](uint32_t c) {
+                       int v = 0;
+                       if (__lane_id() == 0) v = atomicAdd(counters + 32 * c, 1);
+                       return (uint32_t)__builtin_amdgcn_readfirstlane(v);
+                   },
+                   [&](uint32_t t) { fn(t << 6); });
 }
 
 // queue and path-state arrays of one wavefront chunk
