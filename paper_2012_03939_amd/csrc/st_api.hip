@@ -43,25 +43,44 @@ struct GrowBuf {
     size_t cap = 0;
     bool captured = false;            // p was used by a captured launch
     std::vector<void*> retired;       // earlier allocations captured graphs may still use
+    bool holds(size_t bytes) const { return p && bytes <= cap; }
+    static size_t with_slack(size_t bytes) { return std::max<size_t>(bytes + bytes / 8, 256); }
+    void give_up() {
+        if (captured) retired.push_back(p);
+        else if (p) hipFree(p);
+        p = nullptr;
+        cap = 0;
+        captured = false;
+    }
     int ensure(size_t bytes) {
-        if (bytes <= cap && p) {
+        if (holds(bytes)) {
             if (g_capturing) captured = true;
             return ST_OK;
         }
         if (g_capturing)
             return fail(ST_ERR_INVALID_ARG, "workspace would grow during graph capture: make one uncaptured call "
                                             "with the same shapes first");
-        if (p) {
-            if (captured) retired.push_back(p);
-            else hipFree(p);
-            p = nullptr;
-            cap = 0;
-            captured = false;
-        }
-        const size_t want = std::max<size_t>(bytes + bytes / 8, 256);
+        give_up();
+        const size_t want = with_slack(bytes);
         if (hipMalloc(&p, want) != hipSuccess) { p = nullptr; return fail(ST_ERR_OOM, "device allocation failed"); }
         cap = want;
         return ST_OK;
+    }
+    // Growth that the caller can do without: the held allocation is given up only for one
+    // that is there.  False: as before.
+    bool ensure_spare(size_t bytes) {
+        if (holds(bytes)) return ensure(bytes) == ST_OK;
+        if (g_capturing) return false;
+        const size_t want = with_slack(bytes);
+        void* q = nullptr;
+        if (hipMalloc(&q, want) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        give_up();
+        p = q;
+        cap = want;
+        return true;
     }
     void release() {
         if (p) hipFree(p);
@@ -168,6 +187,7 @@ struct st_scene {
     void* arena = nullptr;             // the arrays of st_scene_create
     long long tuned_cap = 0;           // autotuned wavefront chunk size (0: none)
     int tuned_grid = 0;                // autotuned traversal grid (0: none)
+    size_t refused_queues = ~(size_t)0;    // least queue bytes that were found not to be spare
     // hit records of the last single-scene wavefront render, for its backward;
     // which forward they belong to is the device word d.rec_key
     GrowBuf recbuf;
@@ -387,15 +407,19 @@ void carve_queues(char* base, int cap, int nent, float* L, uint32_t* spill, Queu
     q.nent = nent;
 }
 
-// queues of want paths, or of fallback (0: none) where those cannot be had
+// Queues of want paths, or of fallback (0: none) where those cannot be spared.  What was
+// refused once is not asked for again, so that later calls of the same shapes keep the
+// buffer that the first one left.
 int make_queues(st_scene* sc, long long want, long long fallback, int nent, float* L, Queues& q) {
     int cap = queue_cap(want, nent);
-    int rc = sc->qbuf.ensure(queue_bytes(cap, nent));
-    if (rc && fallback > 0 && fallback < want) {
-        (void)hipGetLastError();
+    size_t bytes = queue_bytes(cap, nent);
+    if (fallback > 0 && fallback < want && !sc->qbuf.holds(bytes) &&
+        (bytes >= sc->refused_queues || !sc->qbuf.ensure_spare(bytes))) {
+        if (!g_capturing) sc->refused_queues = std::min(sc->refused_queues, bytes);
         cap = queue_cap(fallback, nent);
-        rc = sc->qbuf.ensure(queue_bytes(cap, nent));
+        bytes = queue_bytes(cap, nent);
     }
+    const int rc = sc->qbuf.ensure(bytes);
     if (rc) return rc;
     carve_queues((char*)sc->qbuf.p, cap, nent, L, (uint32_t*)sc->spillbuf.p, q);
     return ST_OK;
