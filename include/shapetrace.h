@@ -84,7 +84,10 @@ typedef struct {
     float edge_spp_ratio;            /* primary edge samples per (pixel x spp) of each view; with
                                         ST_EDGE_SHADOW as many shadow-edge samples per (view, light) */
     int64_t queue_capacity;          /* wavefront chunk size in path samples (0: the scene's autotuned value,
-                                        else 2^25, or 2^24 where that needs too much memory) */
+                                        else 2^25, whose queues hold 200 to 730 bytes a path by the number
+                                        of shadow rays at a point; or 2^24 when with 2^25 less than half of
+                                        the device's memory would stay free, max_workspace_bytes does not
+                                        allow them, or a capture finds a smaller workspace) */
     uint32_t* debug_decision_hash;   /* device, optional: one FNV-1a hash of the discrete decisions per
                                         path sample, index ((pixel offset of view + y*W + x) * spp + j) */
     uint32_t* debug_edge_hash;       /* device, optional (backward): one hash per primary edge sample,

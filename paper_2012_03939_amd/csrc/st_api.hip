@@ -66,14 +66,16 @@ struct GrowBuf {
         cap = want;
         return ST_OK;
     }
-    // Growth that the caller can do without: the held allocation is given up only for one
-    // that is there.  False: as before.
+    // Growth that the caller can do without: only while half of the device's memory stays
+    // free beside it, and only then is the held allocation given up.  False: as before.
     bool ensure_spare(size_t bytes) {
         if (holds(bytes)) return ensure(bytes) == ST_OK;
         if (g_capturing) return false;
+        size_t room = 0, total = 0;
         const size_t want = with_slack(bytes);
         void* q = nullptr;
-        if (hipMalloc(&q, want) != hipSuccess) {
+        if (hipMemGetInfo(&room, &total) != hipSuccess || room < want || room - want < total / 2 ||
+            hipMalloc(&q, want) != hipSuccess) {
             (void)hipGetLastError();
             return false;
         }
@@ -343,10 +345,11 @@ uint64_t record_key(const st_scene* sc, const st_camera* cams, int ncam, int spp
 constexpr size_t REC_MAX_BYTES = 16ull << 30;
 // Wavefront chunk (paths per pass of the bounce kernels) without tuning: each
 // launch ends in a drain where its longest rays run alone, so larger chunks
-// waste less.  2^25 paths hold about 6.6 GB of queues with one shadow entry; where
-// those do not fit the caller's cap, the device, or (captured) the buffer that is
-// there, 2^24 paths.  2^23, 2^24, 2^25, 2^26 paths: 1024^2 view at 32 spp 5.15, 4.37, 4.00,
-// 4.00 ms; 24-view batch 17.8, 17.0, 16.7, 16.7; 40k-face step 79.4, 75.4, 73.5, 72.6.
+// waste less.  2^25 paths hold about 6.6 GB of queues with one shadow entry (24 GB with
+// 17); where those do not fit the caller's cap, leave less than half of the device's
+// memory free, or (captured) are not in the buffer that is there, 2^24 paths.  2^23, 2^24,
+// 2^25, 2^26 paths: 1024^2 view at 32 spp 5.15, 4.37, 4.00, 4.00 ms; 24-view batch 17.8,
+// 17.0, 16.7, 16.7; 40k-face step 79.4, 75.4, 73.5, 72.6.
 constexpr long long DEFAULT_QUEUE_CAP = 1ll << 25, FALLBACK_QUEUE_CAP = 1ll << 24;
 
 // chunk size for n items with at most cap per chunk: the same number of chunks,

@@ -1,6 +1,6 @@
-"""The wavefront queues beside a program that holds most of the device's memory: nothing is
-allocated by later calls of the same shapes, and a captured graph's workspace is not given
-up for a larger one that cannot be had."""
+"""The wavefront queues beside a program that holds most of the device's memory: the larger
+default chunk is left out, nothing is allocated by later calls of the same shapes, and a
+captured graph's workspace is not given up for one that cannot be had."""
 import sys
 
 import numpy as np
@@ -82,3 +82,27 @@ def test_no_room_for_the_larger_queues(B):
     finally:
         del held
         torch.cuda.empty_cache()
+
+
+def test_less_than_half_of_the_memory_free(B):
+    print(f"case queue memory: {SIZE}^2 at {SPP} spp, 17 shadow entries, 45 % of the memory free", flush=True)
+    sys.stdout.flush()
+    g = _scene(B)
+    cams = [S.look_at_origin((0.4, 1.2, 3.0), SIZE, SIZE)]
+    out = torch.empty((SIZE * SIZE, 3), device="cuda")
+    held = _leave(int(0.45 * torch.cuda.mem_get_info()[1]))
+    try:
+        before = _free()
+        want = g.render(cams, SPP, 1, seed=1, out=out).clone()
+        after = _free()
+        # 1 GiB for radiance, hit records, spill stack and the copy of the image
+        assert before - after <= SMALL + GB
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    # with the memory back, the same call keeps what it has
+    assert torch.equal(out, want)
+    before = _free()
+    g.render(cams, SPP, 1, seed=1, out=out)
+    assert _free() == before and torch.equal(out, want)
+    g.check_errors()
