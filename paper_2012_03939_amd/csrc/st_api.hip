@@ -1147,8 +1147,7 @@ int st_render_backward(st_scene* sc, const st_camera* cams, int32_t ncam, int32_
     const size_t pbytes = sizeof(double) * ((size_t)ncam * ne + (size_t)ncam * (ne + 1) + ncam) +
                           sizeof(int) * ((size_t)ncam << pglog) + sizeof(double) * 2 * (size_t)ncam * ne +
                           sizeof(double) * ((size_t)nls * ne + (size_t)nls * (ne + 1) + nls) +
-                          sizeof(int) * ((size_t)nls << pglog) +
-                          sizeof(double) * (size_t)(ncam + nls) * cdf_tiles(ne) + 11 * 256;
+                          sizeof(int) * ((size_t)nls << pglog) + 9 * 256;
     // workspace of the call, checked against the caller's cap before any kernel:
     // spill stack, edge tables, deferred secondary-edge jobs and, for the primary
     // edges, the side paths' radiance (and hashes) and their wavefront queues
@@ -1211,17 +1210,19 @@ int st_render_backward(st_scene* sc, const st_camera* cams, int32_t ncam, int32_
     p.fast = !p.work && sc->d.nf <= TRAV_FAST_FACES ? 1 : 0;
     p.spill = (uint32_t*)sc->spillbuf.p;
     p.pw = c.take<double>((size_t)ncam * ne);
-    p.ptiles = c.take<double>((size_t)ncam * cdf_tiles(ne));
     p.pcdf = c.take<double>((size_t)ncam * (ne + 1));
     p.ptotal = c.take<double>(ncam);
     p.pguide = c.take<int>((size_t)ncam << pglog);
     p.pglog = pglog;
     p.pacc = c.take<double>(2 * (size_t)ncam * ne);
+    p.ptiles = p.pacc;                       // (cleared and used after the CDFs are made)
     p.lw = c.take<double>((size_t)nls * ne);
-    p.ltiles = c.take<double>((size_t)nls * cdf_tiles(ne));
     p.lcdf = c.take<double>((size_t)nls * (ne + 1));
     p.ltotal = c.take<double>(nls);
     p.lguide = c.take<int>((size_t)nls << pglog);
+    // (written after the CDFs are made; a double per 1,024 edges is within its 2^pglog >= ne
+    // words, for a single edge within the slack behind this last array)
+    p.ltiles = (double*)p.lguide;
     p.facc = sc->d.facc;
     p.macc = sc->d.macc;
     p.ntex = sc->d.ntex;

@@ -157,8 +157,9 @@ enum RCol {
 enum SCol { SWX, SWY, SWZ, STMAX, SCR, SCG, SCB, SNCOL };
 
 // Counters from which the waves of a traversal kernel take their work (wave_tiles),
-// each on its own 128-byte line.
-constexpr int TAKE_SETS = 32;
+// each on its own 128-byte line: set 0 for the extension rays of the first bounce, set k
+// for the launch that traces the shadow rays of bounce k (at most 8).
+constexpr int TAKE_SETS = 16;
 constexpr int TAKE_INTS = TAKE_SETS * TAKE_NC * 32;
 
 // The tiles of 64 consecutive rays, of n, that this wave traces: fn(first ray of
@@ -191,7 +192,7 @@ struct Queues {
     uint8_t* socc;           // outcome code of a shadow entry: 0 no ray, 1 occluded, 2 unoccluded
     uint32_t* slist;         // several entries per point: those (l * cap + i) that carry a ray, compacted per bounce
     int* cnt;                // ray counts per bounce (k), shadow-ray counts per bounce (32 + k)
-    int* take;               // wave_tiles counters: set k (extension rays of bounce k), 16 + k (shadow rays of bounce k)
+    int* take;               // wave_tiles counters, TAKE_SETS sets of TAKE_NC
     uint32_t* spill;         // traversal stack spill
     float* L;                // per path sample radiance [total, 3] (processing order)
     int cap;                 // chunk capacity in paths
@@ -314,14 +315,14 @@ struct BwdParams {
     uint32_t* spill;
     double* pcdf;            // per-view primary edge CDF [ncam, ne+1]
     double* pw;              // per-view primary edge weights [ncam, ne]
-    double* ptiles;          // their sums over tiles of CDF_TILE [ncam, cdf_tiles(ne)]
+    double* ptiles;          // their sums over tiles of CDF_TILE [ncam, cdf_tiles(ne)], in pacc until the CDFs are made
     double* ptotal;          // [ncam]
     int* pguide;             // per-view guide tables of pcdf [ncam, 2^pglog]
     int pglog;
     double* pacc;            // per (view, edge): sums of c (1-t) and c t over its primary edge samples [ncam, ne, 2]
     int ne;
     double* lw;              // per-light shadow-edge weights [nl, ne]
-    double* ltiles;          // their tile sums [nl, cdf_tiles(ne)]
+    double* ltiles;          // their tile sums [nl, cdf_tiles(ne)], in lguide until the CDFs are made
     double* lcdf;            // per-light shadow-edge CDF [nl, ne+1]
     double* ltotal;          // [nl]
     int* lguide;             // per-light guide tables [nl, 2^pglog]

@@ -97,11 +97,11 @@ __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_extend(FwdParams p, 
     if (!SIDE) {
         // counters of the launches after this one (its own were cleared before it
         // when it needs them)
-        clear_counters(q, n, 1);
+        clear_counters(q, n, 0);
         // the hit records are rewritten from here on: their key is cleared until k_film
         if (q0 == 0 && blockIdx.x == 0 && threadIdx.x == 0 && p.rec_key_dev) *p.rec_key_dev = 0ull;
     }
-    wave_tiles(q.take + TAKE_NC * 32, (uint32_t)n, [&](uint32_t tile) {
+    wave_tiles(q.take, (uint32_t)n, [&](uint32_t tile) {
         const int i = (int)(tile + __lane_id());
         if (i >= n) return;
         float t0 = __int_as_float(0x7f800000);
@@ -445,7 +445,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) SHADOW_OCC k_shadow(FwdParams p, 
     const int items = q.cnt[32 + k];
     const bool fused = shadow_fused(p, q);
     // 64 consecutive listed rays per wave, traced in lockstep
-    wave_tiles(q.take + TAKE_NC * 32 * (16 + k), (uint32_t)items, [&](uint32_t t) {
+    wave_tiles(q.take + TAKE_NC * 32 * k, (uint32_t)items, [&](uint32_t t) {
         const int w = (int)(t + __lane_id());
         if (w < items) shadow_one<FAST, ONE>(p, q, k, w, fused, G, st);
     });
@@ -473,7 +473,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) EXTEND_OCC k_trace_pair(FwdParams
     // below 2^31, the grid below 2^21, so the sum and the next index fit 32 bits)
     const uint32_t s64 = ((uint32_t)items + 63u) & ~63u;
     const uint32_t all = s64 + (uint32_t)n;
-    wave_tiles(q.take + TAKE_NC * 32 * (16 + k), all, [&](uint32_t t) {
+    wave_tiles(q.take + TAKE_NC * 32 * k, all, [&](uint32_t t) {
         const uint32_t i = t + __lane_id();
         if (t < s64) {
             if (i < (uint32_t)items) {
