@@ -1112,17 +1112,26 @@ __device__ __forceinline__ int find_view_from(const long long* off, int ncam, in
 // tile's sum (cdf_tile_sum), the next one adds the tiles before (cdf_tile_write).
 // One block over all values took 133 us for 60,000 edges (uncoalesced chunks, a
 // serial scan of 1,024 partial sums); the two kernels take 9.
+//
+// Sums of different groupings of the same values differ by a rounding, so the values
+// must not step back, nor rise over a weight of zero, where the groupings meet: a
+// search would pick an edge that no sample may have.  A tile starts and ends at sums
+// over tiles, all by one tree (a sum over more of its inputs is never less, and the
+// same when they are zeros); inside, a value is the largest so far at a positive
+// weight, at the tile's last one the tile's end.
 // ---------------------------------------------------------------------------
 constexpr int CDF_BLOCK = 256, CDF_PER = 4, CDF_TILE = CDF_BLOCK * CDF_PER;
 __host__ __device__ __forceinline__ int cdf_tiles(int n) { return (n + CDF_TILE - 1) / CDF_TILE; }
-// exclusive sum of v over the block's threads, in thread order, and the block's total
-__device__ __forceinline__ double block_excl_sum(double v, double& total, double* lds /* CDF_BLOCK / 64 */) {
+// exclusive scan of v >= 0 over the block's threads, in thread order, and the block's
+// total; op: sum or maximum
+template <class Op>
+__device__ __forceinline__ double block_excl(double v, double& total, double* lds /* CDF_BLOCK / 64 */, Op op) {
     double inc = v;
     const int lane = (int)__lane_id(), w = (int)(threadIdx.x >> 6);
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const double x = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += x;
+        if (lane >= o) inc = op(inc, x);
     }
     const double up = __shfl_up(inc, 1, 64);
     __syncthreads();
@@ -1131,11 +1140,14 @@ __device__ __forceinline__ double block_excl_sum(double v, double& total, double
     double before = 0.0, all = 0.0;
 #pragma unroll
     for (int k = 0; k < CDF_BLOCK / 64; ++k) {
-        if (k < w) before += lds[k];
-        all += lds[k];
+        if (k < w) before = op(before, lds[k]);
+        all = op(all, lds[k]);
     }
     total = all;
-    return before + (lane > 0 ? up : 0.0);
+    return op(before, lane > 0 ? up : 0.0);
+}
+__device__ __forceinline__ double block_excl_sum(double v, double& total, double* lds) {
+    return block_excl(v, total, lds, [](double a, double b) { return a + b; });
 }
 __device__ __forceinline__ void cdf_tile_sum(double thread_sum, double* tile_sums) {
     __shared__ double lds[CDF_BLOCK / 64];
@@ -1147,14 +1159,17 @@ __device__ __forceinline__ void cdf_tile_sum(double thread_sum, double* tile_sum
 __device__ __forceinline__ double cdf_tile_write(const double* __restrict__ w, int n, const double* __restrict__ tile_sums,
                                                  double* __restrict__ out, double* total_out) {
     __shared__ double lds[CDF_BLOCK / 64];
+    __shared__ int some[CDF_BLOCK / 64];
     const int t = threadIdx.x, b = blockIdx.x, nt = cdf_tiles(n);
-    double bs = 0.0, as = 0.0, before, total, dummy;
+    double bs = 0.0, es = 0.0, as = 0.0, start, end, total, dummy;
     for (int i = t; i < nt; i += CDF_BLOCK) {
         const double v = tile_sums[i];
         as += v;
         if (i < b) bs += v;
+        if (i <= b) es += v;
     }
-    block_excl_sum(bs, before, lds);
+    block_excl_sum(bs, start, lds);
+    block_excl_sum(es, end, lds);
     block_excl_sum(as, total, lds);
     const int i0 = b * CDF_TILE + t * CDF_PER;
     double v[CDF_PER], s = 0.0;
@@ -1163,11 +1178,28 @@ __device__ __forceinline__ double cdf_tile_write(const double* __restrict__ w, i
         v[q] = i0 + q < n ? w[i0 + q] : 0.0;
         s += v[q];
     }
-    double acc = before + block_excl_sum(s, dummy, lds);
+    const uint64_t have = __ballot(s > 0.0);
+    if (__lane_id() == 0) some[t >> 6] = have != 0;
+    const double acc0 = start + block_excl_sum(s, dummy, lds);      // (synchronises the block)
+    bool last = (have >> (t & 63)) == 1;      // no later thread of the wave, or of the waves after
+    for (int k = (t >> 6) + 1; k < CDF_BLOCK / 64; ++k) last = last && !some[k];
+    double most = 0.0, acc = acc0;
 #pragma unroll
     for (int q = 0; q < CDF_PER; ++q) {
         acc += v[q];
-        if (i0 + q < n) out[i0 + q + 1] = total > 0.0 ? acc / total : 0.0;
+        if (v[q] > 0.0) most = fmax(most, fmin(acc, end));
+    }
+    if (last) most = end;
+    double at = fmax(start, block_excl(most, dummy, lds, [](double a, double c) { return fmax(a, c); }));
+    acc = acc0;
+#pragma unroll
+    for (int q = 0; q < CDF_PER; ++q) {
+        acc += v[q];
+        bool ends = last;
+#pragma unroll
+        for (int r = q + 1; r < CDF_PER; ++r) ends = ends && !(v[r] > 0.0);
+        if (v[q] > 0.0) at = ends ? end : fmax(at, fmin(acc, end));
+        if (i0 + q < n) out[i0 + q + 1] = total > 0.0 ? at / total : 0.0;
     }
     if (b == 0 && t == 0) {
         out[0] = 0.0;
