@@ -1133,7 +1133,9 @@ __device__ __forceinline__ bool shadow_edge_sample(const BwdParams& p, const Dev
 // the fp64 tail alone would take 174 registers and leave room for two, and few lanes
 // reach it (3.5M samples over 9,680 faces: 1,473 us at two waves, 1,235 at four, 1,298
 // at six).  The tail's 15 atomics per sample, mostly of a whole wave on the same
-// vertices, took 350 us of that; summed in the wave first the kernel takes 948 us.
+// vertices, took 350 us of that; summed in the wave first the kernel takes 948 us, and
+// the gradient is closer to that of a 64-bit BRDF and the same decisions (37 seeds: median
+// error 3.6e-7 instead of 8.2e-7, at most 1.1e-5 either way).
 #ifndef ST_SE_WAVES
 #define ST_SE_WAVES 4
 #endif

@@ -333,6 +333,14 @@ __device__ __forceinline__ float aload(const float* p) {
     return __uint_as_float(__hip_atomic_load((const uint32_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
+// Before a wave counts its arrival at a node of a bottom-up pass: what it stored below is
+// complete.  Not a release in the language's sense (a fence would write back and
+// invalidate the L2 at every link of the chain); it holds because every store and load of
+// the data handed over is a relaxed agent-scope access, which gfx950 takes past the L1s and
+// the eight L2s to where all of them see it, because the counter of outstanding accesses
+// reaches zero only when such a store is there, and because the loads come after the
+// arrival's atomic has returned.  Plain accesses must not be handed over by it, but for
+// those to a block's own LDS.
 __device__ __forceinline__ void handoff_release() {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);     // no compiler motion across this point
     __builtin_amdgcn_s_waitcnt(0);               // every store of this wave has completed

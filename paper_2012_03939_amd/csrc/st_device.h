@@ -264,7 +264,9 @@ constexpr float FAST_TFAR = 0x1.a36e2ap+114f;    // the largest distance a FAST 
 // out: which of two triangles a ray near their common edge meets first hangs on
 // them, and left to contraction the order of the two products that start the
 // first barycentric sum differed from one call site to another.  YFIRST: that sum
-// starts from the y product (the tests outside a traversal), else from x.
+// starts from the y product (the tests outside a traversal: a side ray's edge faces,
+// the brute-force search), else from x.  Whether a ray within a rounding of a
+// triangle's edge meets it can so differ between the two; t is the same in both.
 template <bool YFIRST = false>
 __device__ __forceinline__ bool tri_test(const gchar* rec, V3 o, V3 d, float tmin, float tmax, float& t, int& face) {
 #pragma clang fp contract(off)
@@ -423,8 +425,9 @@ __device__ __forceinline__ void count_work(const TravStack& st, uint32_t visits,
 }
 
 // closest hit with t in (tmin, inf) excluding one face; ties go to the smaller face id.
-// (t0, f0): a hit already known (f0 >= 0, from the same triangle test), which
-// only prunes the traversal: the result is the least (t, face) either way
+// (t0, f0): a hit already known (f0 >= 0), which prunes the traversal and is its
+// result unless a nearer one is met; tested YFIRST, it can be one that the
+// traversal's own test lets pass by a rounding at the triangle's edge
 template <bool FAST = false>
 __device__ int trace_closest(const TraceGeo& G, V3 o, V3 d, float tmin, int exclude, float& thit, TravStack& st,
                              float t0 = __int_as_float(0x7f800000), int f0 = -1) {
