@@ -1158,6 +1158,7 @@ int st_render_backward(st_scene* sc, const st_camera* cams, int32_t ncam, int32_
     // (two side paths per edge sample)
     const long long side_fallback = want_cap > 0 ? 0 : balanced_chunk(2 * cs.total_edges, FALLBACK_QUEUE_CAP) & ~1ll;
     long long side_cap = balanced_chunk(2 * cs.total_edges, std::min<long long>(want_cap > 0 ? want_cap : DEFAULT_QUEUE_CAP, 1ll << 28)) & ~1ll;
+    side_cap = std::max(side_cap, 2ll);     // (a chunk of one path holds no sample)
     if (prim && 2 * cs.total_edges >= (1ll << 32)) return fail(ST_ERR_INVALID_ARG, "too many primary edge samples");
     // hit records of this pass's forward, when the scene holds them in a buffer
     // large enough (the adjoint still checks on the device that they are this

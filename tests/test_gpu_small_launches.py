@@ -110,3 +110,21 @@ def test_few_edge_samples(B, nl, size):
     for x, y in zip(a, b):
         # the recorded hit's distance from its plane, and float32 sums in another order
         assert rel_l2(x, y) < GRAD_RTOL
+
+
+@pytest.mark.parametrize("cap", [1, 2, 3, 129])
+def test_smallest_side_chunks(B, cap):
+    """A backward in chunks of the fewest paths: two, the side paths of one edge sample."""
+    import ctypes
+    _say(f"case smallest side chunks: {cap}")
+    g = B.GPUScene.from_scene(_scene(3, False))
+    cams = [S.look_at_origin((0.3, 0.9, 3.1), 8, 8)]
+    d = torch.ones((64, 3), device="cuda")
+    want = g.backward(cams, 1, 1, d, 2, B.ST_EDGE_PRIMARY)[0].cpu().numpy()
+    dV, dM = torch.empty((g.nv, 3), device="cuda"), torch.empty((g.ntex, 7), device="cuda")
+    o = B.make_opts(flags=B.ST_EDGE_PRIMARY, queue_capacity=cap)
+    B._check(B.load().st_render_backward(g.h, B.make_cameras(cams), 1, 1, 1, 2, ctypes.byref(o), B._ptr(d), B._ptr(dV),
+                                         B._ptr(dM), B._stream()))
+    g.check_errors()
+    # float64 sums of the same terms in another order, rounded to float32
+    assert np.abs(want).max() > 0 and rel_l2(dV.cpu().numpy(), want) < 1e-6
